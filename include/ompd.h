@@ -71,10 +71,13 @@ enum { OMPD_MAP_TO = 1, OMPD_MAP_FROM = 2, OMPD_MAP_ALLOC = 4, OMPD_FIRSTPRIVATE
                                              (same results) instead of one kernel per phase */
 /* Schedule of the sweeps (results do not depend on it).  WALK: one block
  * after another in block order, the states of recent blocks kept in LDS
- * (best when a CFG has few blocks per level).  LEVEL: the blocks of a level
- * (blocks that no chain of edges other than BACK edges orders) in parallel,
- * a level at a time (best when levels are wide).  Neither flag: the library
- * picks per CFG from its shape. */
+ * (15 words of variables per wavefront).  LEVEL: the blocks sorted by level
+ * (a level holds blocks that no chain of edges other than BACK edges orders),
+ * up to four words of variables per workgroup, whose wavefronts share the
+ * levels (as many as an idle GPU has room for).  Neither flag: by level, with
+ * as many wavefronts per workgroup as the launch leaves room for.  CFGs of
+ * more than 32,000 blocks, of 65,535 edges or more, and those whose strips
+ * do not fit in the scratch they are given take the walk. */
 #define OMPD_F_SCHED_LEVEL (1u << 4)
 #define OMPD_F_SCHED_WALK (1u << 5)
 /* Placement variants (section "Data-Flow Analysis", the loop rule, and
@@ -260,7 +263,8 @@ int ompd_plan_autotune(ompd_plan* plan, void* stream, int32_t trials, float* bes
 /* Schedule per size bucket (what the autotuner chooses first, then the
  * launch configuration with that schedule): bucket k holds the CFGs with
  * fewer than 256, 1,024, 4,096, 16,384 blocks, or more (k = 0..4); per_bucket[k]
- * is -1 (the library's rule), 0 (walk) or 1 (level); CFGs whose schedule the
+ * is -1 (the library's rule: by level, wavefronts by the launch's load),
+ * 0 (walk) or 1 (level); CFGs whose schedule the
  * plan's flags name, and CFGs too large for the level schedule, keep theirs.
  * The autotuner times each bucket alone under both schedules.  Results are
  * bit-identical for every choice.  ompd_plan_describe reports the choice. */
@@ -279,8 +283,10 @@ int ompd_plan_configure(ompd_plan* plan, int64_t lds_bytes, int32_t wg_per_cu);
  * (AVEin, eager copies), pending copies, pending pass (valid in both
  * spaces), delayed placement, placement pass (the copies), loop-entry
  * refinement and its pass (0 ms unless a CFG asks for it), final
- * validity, final pass (AVFin, map-kind masks), map kinds (*n_kernels =
- * 13), or ingest and the per-tile kernel (*n_kernels = 2) after
+ * validity, final pass (AVFin, map-kind masks), map kinds, then for the CFGs
+ * solved by level the rows into strips, next use and validity, their rows
+ * out, the phases from the pending copies on, and their rows out
+ * (*n_kernels = 18), or ingest and the per-tile kernel (*n_kernels = 2) after
  * ompd_plan_split_kernels(plan, 0).  At most `capacity` are written.
  * OMPD_E_INVAL if profiling is off. */
 int ompd_plan_profile(ompd_plan* plan, int32_t enable);

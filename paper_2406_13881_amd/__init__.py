@@ -25,7 +25,7 @@ import numpy as np
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _SO = os.path.join(_HERE, "libompd.so")
-_SOURCES = ["csrc/ompd_kernels.hip", "csrc/ompd_runtime.hip", "csrc/ompd_serving.hip", "csrc/ompd_program.hip"]
+_SOURCES = ["csrc/ompd_kernels.hip", "csrc/ompd_strip.hip", "csrc/ompd_runtime.hip", "csrc/ompd_serving.hip", "csrc/ompd_program.hip"]
 
 OMPD_OK = 0
 OMPD_E_INVAL = -1
@@ -635,7 +635,8 @@ class Plan:
 
     KERNELS = ("ompd_k_prep", "ompd_k_nu", "ompd_k_ave", "ompd_k_post_ave", "ompd_k_mayp", "ompd_k_post_mayp",
                "ompd_k_later", "ompd_k_post_later", "ompd_k_live", "ompd_k_post_live", "ompd_k_avf",
-               "ompd_k_post_avf", "ompd_k_varkind")
+               "ompd_k_post_avf", "ompd_k_varkind", "ompd_k_tin", "ompd_k_strip_a", "ompd_k_tmid", "ompd_k_strip_b",
+               "ompd_k_tout")
     KERNELS_TILE = ("ompd_k_prep", "ompd_k_solve")
 
     def split_kernels(self, split: bool = True):
@@ -648,9 +649,9 @@ class Plan:
 
     def kernel_ms(self) -> Dict[str, float]:
         """Per-kernel durations (ms) of the last profiled run."""
-        buf = (ctypes.c_float * 16)()
+        buf = (ctypes.c_float * 24)()
         n = _i32(0)
-        _check(lib().ompd_plan_kernel_ms(self.h, buf, 16, ctypes.byref(n)))
+        _check(lib().ompd_plan_kernel_ms(self.h, buf, 24, ctypes.byref(n)))
         names = self.KERNELS if n.value == len(self.KERNELS) else self.KERNELS_TILE
         return {k: float(buf[i]) for i, k in enumerate(names[:n.value])}
 

@@ -99,11 +99,72 @@ struct DevCfg {
     int32_t* lorder;    // [nb] the blocks by level (level schedule)
     int32_t* loff;      // [nb + 1] start of each level in lorder
     int32_t* info;
+    // Strip schedule (these share the CFG's scratch with the walk's arrays above; one of the two
+    // is in use).  Positions: the blocks by level.  Units: the words, then (block arrays only) one
+    // word of reachability facts.  Block arrays [units][nb] and edge arrays [words][ne + 1] hold
+    // pairs of words, host and device.
+    int32_t units;              // units per strip workgroup (1, 2 or 4)
+    int32_t spread;             // the launch leaves compute units idle: fewer blocks per wavefront
+    int32_t waves;              // wavefronts per strip workgroup
+    int32_t strip_ok;           // host side: the strips can hold the CFG
+    int32_t want;               // WANT_* bits: the block and edge outputs the caller asked for
+    uint64_t *p_rw;             // reads and writes
+    uint64_t *p_1;              // states: next use; delayed copies; refinement; final validity
+    uint64_t *p_2;              // states: eager validity out; pending copies; then copies before blocks
+    uint64_t *p_3;              // eager validity in; then final validity in
+    uint64_t *p_g;              // [words][ne + 1] eager copies by edge; then the placed copies
+    uint64_t *p_b;              // [words][ne + 1] (one word) valid in both spaces on the edge
+    uint32_t *rec_sf, *rec_sb;  // [passes][4 / units][16] lane records (two words), forward and backward
+    uint32_t *link;             // [ne + 1] edges by the block they enter: positions of their ends, loop entry
+    int32_t *eid, *erec;        // [ne + 1] edge of each entry of `link`, [ne] the entry of each edge
+    uint32_t *x_f, *x_b;        // cross links: neighbour position | reader's pass << 16
+    int32_t *est_f, *est_b;     // [nb + 1] first edge into each position, out of each position from the last
+    uint32_t *loc_f, *loc_b;    // [nb] pass of a position | its first lane << 16
+    uint16_t *pos;              // [nb] position of a block
+    uint16_t *last_f, *last_b;  // [nb] last pass of its run that reads a position
+    uint8_t* facts;             // [nb] by position: FACT_* bits
+    int32_t *s_kc, *s_lorder, *s_loff;   // [nb + 1] ingest cursor; [nb] blocks by level; [nb + 1] level starts
+    int32_t* hdr;               // SH_* words
 };
+
+// DevCfg::want bits
+enum : int32_t { WANT_NU_H = 1, WANT_NU_D = 2, WANT_AVE_H = 4, WANT_AVE_D = 8, WANT_AVF_H = 16, WANT_AVF_D = 32,
+                 WANT_IE_H = 64, WANT_IE_D = 128, WANT_IG_H = 256, WANT_IG_D = 512 };
+enum : int32_t { FACT_AFTER = 1, FACT_BEFORE = 2 };   // a DEVICE block reaches it / it reaches one
+// strip header words: passes and cross links of each direction
+enum : int32_t { SH_PASS_F = 0, SH_PASS_B = 1, SH_X_F = 2, SH_X_B = 3, SH_WORDS = 8 };
+// entries of a CFG's edge arrays: one per edge and one for the block without any
+constexpr int strip_records(int ne) { return ne + 1; }
+// words and rows of a transpose item
+constexpr int STRIP_T_WORDS = 16, STRIP_T_ROWS = 64;
+// most wavefronts of a strip workgroup, and the control words of its LDS
+constexpr int STRIP_MAX_WAVES = 8;
+constexpr int STRIP_CTL_WORDS = 64;
+// passes whose results a wavefront keeps in LDS (64 lanes, a pair of words each)
+constexpr int STRIP_RING = 8;
+// LDS of a strip workgroup: a ring per wavefront, two bit maps (block changed in this round, pass
+// to be visited), control words
+constexpr int strip_bit_words(int nb) { return (nb + 32) / 32; }
+constexpr size_t strip_lds(int nb, int waves)
+{
+    return (size_t)waves * STRIP_RING * 1024 + 8 * (size_t)strip_bit_words(nb) + 4 * STRIP_CTL_WORDS;
+}
+// most blocks of a CFG on the strip schedule (positions are 15-bit numbers)
+constexpr int STRIP_MAX_BLOCKS = 32000;
+// units of a strip: as many as a pass of narrow levels fills; a large CFG has wider levels, which
+// fill a pass with fewer units
+constexpr int strip_units(int nb, int wd) { return nb >= 10000 || wd < 1 ? 1 : wd < 3 ? 2 : 4; }
+// LDS bytes of the ingest kernel's peel: 16-bit successor CSR, degrees, order (0: it does not fit
+// 16 bits, and the peel runs in global memory)
+constexpr size_t strip_prep_lds(int nb, int ne)
+{
+    return ne >= 65536 ? 0 : 2 * ((size_t)((nb + 2) & ~1) + ((ne + 1) & ~1) + 2 * (size_t)((nb + 1) & ~1));
+}
 
 // How a CFG's phases visit its blocks: one block after another along the
 // block order (the walk), or a level at a time with the blocks of a level in
 // parallel.  Results do not depend on it.
+// SCHED_LEVEL: the strip kernels (ompd_strip.hip).
 enum : int32_t { SCHED_WALK = 0, SCHED_LEVEL = 1 };
 
 // record meta word: neighbour count | flags
@@ -147,8 +208,6 @@ inline int tiles_of(int wd) { return wd <= 0 ? 1 : (wd + TILE_WORDS - 1) / TILE_
 // steps (phase_inputs(ph) words of WORD_BYTES each), their 16-byte
 // descriptors, then one state of identity words (STATE_BYTES).
 constexpr int CTL_BYTES = 256;
-// Threads of a level-schedule workgroup.
-constexpr int LEVEL_THREADS = 64;
 // then the blocks of the last BLK_RING planned steps (the helper stores results by them; at least
 // the result ring plus the input ring, so that an entry is not reused before its step is stored)
 constexpr int BLK_RING = 128;
@@ -166,10 +225,10 @@ inline size_t phase_lds(int ph, int ring_slots)
            STATE_BYTES;
 }
 // Work counters (int32) of one solve launch: phases 0..5, passes 8..11 and 14 (refinement), map
-// kinds 12, per-tile kernel 13, level kernels 16..21.
+// kinds 12, per-tile kernel 13.
 constexpr int N_COUNTERS = 32;
 // Kernels of one solve launch, in launch order (prep excluded; the two of the refinement are
-// launched only when a CFG asks for it, their profile marks always).
-constexpr int N_SOLVE_KERNELS = 12;
+// launched only when a CFG asks for it, their profile marks always); the walk's, then the strips'.
+constexpr int N_SOLVE_KERNELS = 17;
 
 }  // namespace ompd

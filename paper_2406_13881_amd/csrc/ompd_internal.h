@@ -39,9 +39,18 @@ struct LaunchDims {
     int grid_edge = 1;
     size_t lds_tile = 0;         // the per-tile kernel: LDS of its largest phase
     int grid_tile = 1;
-    int n_level = 0;             // level tiles: the last n_level entries of the tile array
-    size_t lds_level = 0;        // LDS of a level workgroup (the largest level CFG's column state)
-    int grid_level = 1;
+    int n_walk = 0;              // CFGs on the walk
+    // strip schedule
+    int n_strip = 0;             // CFGs on it
+    int n_level = 0;             // strip tiles: the last n_level entries of the tile array
+    int n_tblock = 0, n_tedge = 0;   // transpose items: the last entries of the item array, blocks first
+    size_t lds_prep = 0;         // LDS of the strip ingest (the largest CFG's peel that fits)
+    // launches of each strip kernel: consecutive strip tiles whose workgroups have the same number
+    // of wavefronts
+    struct Bucket { int first, n, waves; size_t lds; };
+    static constexpr int MAX_BUCKETS = 6;
+    int n_buckets = 0;
+    Bucket bucket[MAX_BUCKETS] = {};
 };
 
 // Tunable launch configuration of a plan; results never depend on it.
@@ -81,7 +90,6 @@ struct ompd_plan {
     size_t scratch_bytes = 0;
     int max_nb = 2;
     LaunchDims dims;
-    size_t lds_prep = 0;
     hipGraph_t g_prep = nullptr, g_solve = nullptr;
     hipGraphExec_t gx_prep = nullptr, gx_solve = nullptr;
     hipStream_t last_stream = nullptr;
@@ -95,32 +103,36 @@ int ompd_fail(int code, const std::string& msg);
 std::string ompd_status_message(int i, const int32_t* info);
 
 struct ScratchOff {
-    size_t aveout, mayp, later, flg, eag, both, nu, ave, ie, ig, avf, vk, bnd, pp, pi, pe, tmp, recf, recb, stf, stb,
-        lorder, loff, fp, info;
+    // the walk's arrays
+    size_t aveout, mayp, later, flg, eag, both, pp, pi, pe, tmp, recf, recb, stf, stb, lorder, loff;
+    // the strips' arrays, in the same bytes (strip: the CFG can take the strip schedule)
+    bool strip;
+    int rows;    // rows of a pass its lane records have room for
+    size_t s_rw, s_1, s_2, s_3, s_g, s_b, s_recf, s_recb, s_link, s_eid, s_erec, s_xf, s_xb, s_estf, s_estb, s_locf,
+        s_locb, s_kc, s_lorder, s_loff, s_pos, s_lastf, s_lastb, s_facts, s_hdr;
+    // both schedules
+    size_t nu, ave, ie, ig, avf, vk, bnd, fp, info;
 };
-size_t ompd_cfg_scratch(const ompd_cfg& g, const ompd_result& r, ScratchOff& o);
+// Scratch of one CFG, offsets relative to its base.  The strips' arrays take the walk's place; a
+// CFG with many edges per block needs more for them, which `rows` grants: at least that many rows of a pass
+// in the lane records (0: no more bytes than the walk, or the CFG is left to it).
+size_t ompd_cfg_scratch(const ompd_cfg& g, const ompd_result& r, ScratchOff& o, int rows);
 void ompd_fill_devcfg(const ompd_cfg& g, const ompd_result& r, char* base, const ScratchOff& o, uint32_t flags,
                       int32_t wait_ticks, ompd::DevCfg& d, uint64_t* bnd_host, uint64_t* bnd_dev = nullptr);
-// Blocks from which a CFG takes the level schedule when the caller names none
-// (in a launch that fills the GPU the walk's throughput wins below this; a
-// 16,386-block CFG runs 3.6x faster on levels), and the most blocks a CFG on
-// the level schedule may have (its column's state, 8 bytes per block, must
-// fit a workgroup's LDS; larger CFGs take the walk whatever the caller asks).
-constexpr int OMPD_LEVEL_MIN_BLOCKS = 12288;
-constexpr int OMPD_LEVEL_MAX_BLOCKS = 20000;
-int ompd_default_sched(int n_blocks, int n_vars);
-// A level tile keeps a whole column of its CFG in LDS, so a CU runs one at a time: the level
-// schedule has the lower latency per CFG but the lower throughput per CU.  When the CFGs that
-// the default rule put on it have more level tiles than this many rounds of the CUs take, they
-// go back to the walk (the launch is throughput-bound then).  Serving C2-shaped requests: 3
-// rounds gave a p50 of 243-453 ms at half load, 5 rounds 189 ms at the same capacity (~146
-// requests/s), 8 rounds 149 ms but a capacity of 133 requests/s.
-constexpr int OMPD_LEVEL_ROUNDS = 5;
-// ... and a launch with at most n_cu / OMPD_IDLE_FRACTION walk tiles moves the CFGs that the rule
-// put on the walk to the level schedule (one round of level tiles at most): alone, a CFG usually
-// finishes sooner there.
-constexpr int OMPD_IDLE_FRACTION = 4;
-void ompd_settle_sched(ompd::DevCfg* h, int n, int n_cu);
+// WANT_* bits of the outputs a caller asked for.
+int32_t ompd_want(const ompd_result& r);
+// Transpose items of a CFG on the strip schedule.
+inline size_t ompd_transpose_items(size_t nb, size_t ne, size_t wd)
+{
+    const size_t runs = wd ? (wd + ompd::STRIP_T_WORDS - 1) / ompd::STRIP_T_WORDS : 1;
+    auto chunks = [](size_t rows) { return (rows + ompd::STRIP_T_ROWS - 1) / ompd::STRIP_T_ROWS; };
+    return runs * (chunks(nb) + (wd ? chunks(ne + 1) : 0));
+}
+int ompd_strip_rows(const ompd_cfg* g, int n);
+// Settle the schedule of each CFG of a launch (a CFG whose schedule the caller names, or that the
+// strips cannot hold, keeps the walk or the strips; the others take the strips, or the walk when
+// the launch asks for the per-tile kernel), and the shape of its strips.
+void ompd_settle_sched(ompd::DevCfg* h, int n, int n_cu, bool split = true);
 // Default bound of a kernel wait without progress (the longest legitimate wait is one step of
 // the other wavefront, microseconds).
 constexpr int64_t OMPD_WAIT_DEFAULT_NS = 2000000000ll;
@@ -129,10 +141,9 @@ struct Shape {
     std::vector<ompd::Tile> tiles;
     std::vector<ompd::EdgeItem> items;
     LaunchDims dims;
-    size_t lds_prep = 0;
 };
 int ompd_make_shape(ompd_ctx* ctx, const std::vector<ompd::DevCfg>& cfgs, const PlanConfig& pc, Shape& sh);
-int ompd_launch_prep(const ompd::DevCfg* d_cfgs, int n, int32_t* d_counter, size_t lds, int ring_slots, hipStream_t s);
+int ompd_launch_prep(const ompd::DevCfg* d_cfgs, int n, int32_t* d_counter, const LaunchDims& dims, hipStream_t s);
 int ompd_launch_solve(const ompd::DevCfg* d_cfgs, const ompd::Tile* d_tiles, int n_tiles, const ompd::EdgeItem* d_items,
                       int n_items, int32_t* d_counter, const LaunchDims& dims, hipStream_t s,
                       hipEvent_t* after = nullptr);

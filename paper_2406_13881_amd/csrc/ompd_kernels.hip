@@ -30,28 +30,9 @@
 // any split of the variable axis is exact.
 #include <hip/hip_runtime.h>
 
-#include "ompd_device.h"
-
-#define OMPD_E_INVAL_ (-1)
-#define OMPD_E_DEVICE_ (-3)
-#define OMPD_E_NOCONVERGE_ (-4)
+#include "ompd_common.h"
 
 namespace ompd {
-
-// Views of generic pointers as global-memory pointers: loads and stores
-// through them compile to global_load/global_store, which only count
-// against vmcnt, so a wait for LDS does not also drain outstanding
-// global prefetches (flat accesses would count against both).
-#define GAS __attribute__((address_space(1)))
-template <typename T>
-__device__ __forceinline__ const GAS T* G(const T* p) { return (const GAS T*)p; }
-template <typename T>
-__device__ __forceinline__ GAS T* G(T* p) { return (GAS T*)p; }
-
-__device__ __forceinline__ void set_status(int32_t* info, int32_t code)
-{
-    atomicCAS(&info[INFO_STATUS], 0, code);
-}
 
 // Step flags (the x word of a step entry and of a step descriptor).  Bits 0-1 / 2-3: where the
 // state of neighbour 0 / 1 is found: 0 nowhere (missing), 1 the block computed last, 2 the ring,
@@ -73,8 +54,6 @@ constexpr int DD_DEV = 5;                   // the bit of DF_DEV
 static_assert(DF_DEV == 1u << DD_DEV && DF_MASK < 1u << DD_LAST0, "descriptor bits");
 // all ones if bit `bit` of the wave-uniform word fl is set, else zero
 __device__ __forceinline__ uint32_t fmask(uint32_t fl, int bit) { return (uint32_t)((int32_t)(fl << (31 - bit)) >> 31); }
-// Does an edge of kind k stop the delay?  Loop entries do, unless the placement is pure lazy.
-__device__ __forceinline__ bool is_le(const DevCfg& c, uint8_t k) { return k == 2 && !(c.placement & PL_LAZY); }
 // A step entry (two int4, one per walk position): x flags; y the ring distances of neighbours
 // 0 and 1 (bits 0-7, 8-15; flag code 2 only); z the far neighbour; w how many steps before the
 // current one its state was computed (this sweep's or, when SF_BACK, the previous sweep's); then
@@ -116,32 +95,6 @@ __device__ __forceinline__ void make_step(const int4& r0, const int4& r1, int b,
     t1 = make_int4(b, cnt > 0 ? (int)(e0 & 0x7FFFFFFFu) : 0, cnt > 1 ? (int)(e1 & 0x7FFFFFFFu) : 0, -1);
 }
 
-// Inclusive prefix sum of a[0..n) in global memory by one workgroup.
-__device__ void block_scan_inclusive(int32_t* a, int n, int32_t* sh)
-{
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, nw = blockDim.x >> 6;
-    int carry = 0;
-    for (int base = 0; base < n; base += blockDim.x) {
-        int i = base + threadIdx.x;
-        int x = (i < n) ? a[i] : 0;
-        for (int d = 1; d < 64; d <<= 1) {
-            int y = __shfl_up(x, d, 64);
-            if (lane >= d) x += y;
-        }
-        if (lane == 63) sh[wv] = x;
-        __syncthreads();
-        int off = carry, tot = 0;
-        for (int j = 0; j < nw; ++j) {
-            if (j < wv) off += sh[j];
-            tot += sh[j];
-        }
-        __syncthreads();
-        if (i < n) a[i] = x + off;
-        carry += tot;
-    }
-    __syncthreads();
-}
-
 // --------------------------------------------------------------------------
 // ingest / normalise
 // --------------------------------------------------------------------------
@@ -152,85 +105,11 @@ ompd_k_prep(const DevCfg* __restrict__ cfgs, int n_cfgs, int32_t* __restrict__ s
     __shared__ int32_t s_scan[16];
     const int ci = blockIdx.x;
     if (ci == 0 && threadIdx.x < N_COUNTERS) solve_counter[threadIdx.x] = 0;   // work counters of the solve kernels
-    if (ci >= n_cfgs) return;
+    if (ci >= n_cfgs || cfgs[ci].sched == SCHED_LEVEL) return;   // (the strips have an ingest kernel of their own)
     const DevCfg c = cfgs[ci];
     const int tid = threadIdx.x, nt = blockDim.x;
     const int nb = c.nb, ne = c.ne, wd = c.wd;
-    if (tid == 0) s_err = 0;
-    for (int i = tid; i < INFO_WORDS; i += nt) c.info[i] = 0;
-    if (c.var_kind)
-        for (int i = tid; i < 4 * wd; i += nt) c.vk_acc[i] = 0;
-    for (int w = tid; w < wd; w += nt) c.fp[w] = 0;
-    __syncthreads();
-
-    // validation, stage 1: pointers, kinds, spaces
-    int err = 0;
-    if (tid == 0 && (c.succ_ptr[0] != 0 || c.succ_ptr[nb] != ne)) err = 1;
-    for (int b = tid; b < nb; b += nt) {
-        int a = c.succ_ptr[b], z = c.succ_ptr[b + 1];
-        if (z < a || a < 0 || z > ne) err = 1;
-        if (c.space[b] > 1) err = 1;
-    }
-    for (int e = tid; e < ne; e += nt)
-        if (c.kind[e] > 2) err = 1;
-    if (tid == 0 && (c.space[c.entry] != 0 || c.space[c.exit] != 0)) err = 1;
-    if (err) atomicOr(&s_err, 1);
-    __syncthreads();
-    if (s_err) { if (tid == 0) c.info[INFO_STATUS] = OMPD_E_INVAL_; return; }
-
-    // stage 2: successor targets, ENTRY/EXIT rules, bit rows, boundaries, calls
-    if (tid == 0 && c.succ_ptr[c.exit + 1] != c.succ_ptr[c.exit]) err = 1;
-    for (int e = tid; e < ne; e += nt) {
-        int q = c.succ_idx[e];
-        if (q < 0 || q >= nb || q == c.entry) err = 1;
-        else if (q == c.exit && c.kind[e] != 0) err = 1;
-    }
-    for (int e = c.succ_ptr[c.entry] + tid; e < c.succ_ptr[c.entry + 1]; e += nt)
-        if (c.kind[e] == 1) err = 1;
-    for (int b = tid; b < nb; b += nt)
-        if (c.succ_ptr[b + 1] - c.succ_ptr[b] > (int)REC_COUNT) err = 1;
-    if (wd > 0) {
-        const uint64_t last = (c.nv & 63) ? ((1ull << (c.nv & 63)) - 1ull) : ~0ull;
-        for (int w = tid; w < wd; w += nt) {
-            uint64_t m = (w == wd - 1) ? last : ~0ull;
-            if (c.R[(size_t)c.entry * wd + w] | c.W[(size_t)c.entry * wd + w] |
-                c.R[(size_t)c.exit * wd + w] | c.W[(size_t)c.exit * wd + w]) err = 1;
-            uint64_t eh = c.ev_h[w], ed = c.ev_d[w];
-            if ((eh | ed | c.lx_h[w] | c.lx_d[w]) & ~m) err = 1;
-            if (!(c.placement & PL_SUMMARY) && ((eh | ed) & m) != m) err = 1;   // a summary evaluation may leave gaps
-        }
-        for (int b = tid; b < nb; b += nt)
-            if ((c.R[(size_t)b * wd + wd - 1] | c.W[(size_t)b * wd + wd - 1]) & ~last) err = 1;
-    }
-    if (c.call) {
-        for (int b = tid; b < nb; b += nt) {
-            int k = c.call[b];
-            if (k >= 0 && (k >= c.n_sums || c.space[b] != 0 || b == c.entry || b == c.exit)) err = 1;
-        }
-    }
-    if (err) atomicOr(&s_err, 1);
-    __syncthreads();
-    if (s_err) { if (tid == 0) c.info[INFO_STATUS] = OMPD_E_INVAL_; return; }
-
-    // firstprivate variables: marked scalars that no DEVICE block writes (the OR of the device
-    // blocks' writes gathers in c.fp first)
-    if (c.scalar && wd > 0) {
-        for (size_t i = tid; i < (size_t)nb * wd; i += nt) {
-            const int b = (int)(i / wd), w = (int)(i % wd);
-            if (c.space[b]) {
-                const uint64_t x = c.W[i];
-                if (x) atomicOr((unsigned long long*)&c.fp[w], (unsigned long long)x);
-            }
-        }
-        __syncthreads();
-        const uint64_t last = (c.nv & 63) ? ((1ull << (c.nv & 63)) - 1ull) : ~0ull;
-        for (int w = tid; w < wd; w += nt) {
-            // the atomics above ran in L2: read their result there, past this CU's cache
-            const uint64_t dw = __hip_atomic_load(&c.fp[w], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            c.fp[w] = c.scalar[w] & ~dw & (w == wd - 1 ? last : ~0ull);
-        }
-        __syncthreads();
-    }
+    if (!validate_cfg(c, s_err)) return;
     // predecessor CSR
     int32_t* pp = c.pred_ptr;
     for (int b = tid; b <= nb; b += nt) pp[b] = 0;
@@ -285,19 +164,16 @@ ompd_k_prep(const DevCfg* __restrict__ cfgs, int n_cfgs, int32_t* __restrict__ s
         RB[2 * b + 1] = r1;
     }
     __syncthreads();
-    // Walk order (walk schedule): the caller's ids when every edge other than BACK goes from a
-    // lower to a higher id (the source order a front end emits; the sweeps then reach the fixed
-    // point in loop depth + 1), else the order of the peel below, in which every such edge goes
-    // forward too;
+    // Walk order: the caller's ids when every edge other than BACK goes from a lower to a higher id
+    // (the source order a front end emits; the sweeps then reach the fixed point in loop depth + 1),
+    // else the order in which the graph peels from ENTRY over the edges other than BACK (round by
+    // round; blocks left over, on a cycle closed by an edge not marked BACK or unreachable, which
+    // the validity phase rejects, follow in id order), in which every such edge goes forward too;
     // then lorder[i] is the block at forward walk position i and loff[b] the position of block b.
-    // Levels (level schedule): peel the graph from ENTRY over the edges other than BACK; the
-    // blocks of a round form a level.  Blocks left over (a cycle closed by an edge not marked
-    // BACK, or unreachable ones, which the validity phase rejects) get a level each, in id order.
-    const bool lv = c.sched == SCHED_LEVEL;
     __shared__ int s_unord;
     if (tid == 0) s_unord = 0;
     __syncthreads();
-    if (!lv) {
+    {
         int un = 0;
         for (int b = tid; b < nb; b += nt)
             for (int e = c.succ_ptr[b]; e < c.succ_ptr[b + 1]; ++e)
@@ -306,7 +182,7 @@ ompd_k_prep(const DevCfg* __restrict__ cfgs, int n_cfgs, int32_t* __restrict__ s
         __syncthreads();
     }
     const bool unord = s_unord != 0;
-    if (lv || unord) {
+    if (unord) {
         __shared__ int s_tail;
         int32_t* deg = c.tmp;
         for (int b = tid; b < nb; b += nt) {
@@ -316,9 +192,8 @@ ompd_k_prep(const DevCfg* __restrict__ cfgs, int n_cfgs, int32_t* __restrict__ s
         }
         if (tid == 0) { c.lorder[0] = c.entry; s_tail = 1; }
         __syncthreads();
-        int fa = 0, fb = 1, nl = 0;
+        int fa = 0, fb = 1;
         while (fa < fb) {
-            if (tid == 0 && lv) c.loff[nl] = fa;
             for (int i = fa + tid; i < fb; i += nt) {
                 const int b = c.lorder[i];
                 for (int e = c.succ_ptr[b]; e < c.succ_ptr[b + 1]; ++e) {
@@ -330,115 +205,25 @@ ompd_k_prep(const DevCfg* __restrict__ cfgs, int n_cfgs, int32_t* __restrict__ s
             __syncthreads();
             fa = fb;
             fb = s_tail;
-            ++nl;
             __syncthreads();
         }
         if (fb < nb) {
-            // leftovers: blocks never placed, one level each
-            __shared__ int s_n;
+            // leftovers: blocks never placed
             for (int i = tid; i < fb; i += nt) deg[c.lorder[i]] = -1;
             __syncthreads();
             if (tid == 0) {
                 int n = fb;
                 for (int b = 0; b < nb; ++b)
-                    if (deg[b] != -1) {
-                        c.lorder[n] = b;
-                        if (lv) c.loff[nl] = n;
-                        ++nl;
-                        ++n;
-                    }
-                s_n = nl;
+                    if (deg[b] != -1) c.lorder[n++] = b;
             }
             __syncthreads();
-            nl = s_n;
         }
-        if (tid == 0) {
-            if (lv) c.loff[nl] = nb;
-            c.info[INFO_LEVELS] = lv ? nl : 0;
-        }
-        __syncthreads();
-        if (!lv)
-            for (int i = tid; i < nb; i += nt) c.loff[c.lorder[i]] = i;
+        for (int i = tid; i < nb; i += nt) c.loff[c.lorder[i]] = i;
         __syncthreads();
     }
-    if (tid == 0) c.info[INFO_ORDER] = lv || !unord;
+    if (tid == 0) c.info[INFO_ORDER] = !unord;
     int4* SF = reinterpret_cast<int4*>(c.step_f);
     int4* SB = reinterpret_cast<int4*>(c.step_b);
-    if (lv) {
-        // Re-check lists of the level schedule (what the walk's step entries carry, for levels):
-        // the blocks that read a neighbour whose level is not below their own (a BACK edge into
-        // them, or a self loop), that is a predecessor of a forward phase or a successor of a
-        // backward one.  Each block's level goes to the spare word of its records first.  The
-        // forward list fills c.tmp from the front, the backward one from the back (entry nb
-        // first), each ended by -1; if the two do not fit in its nb + 1 words, c.tmp[0] = -2 and
-        // the level kernels confirm with a sweep instead.
-        const int nlv = c.info[INFO_LEVELS];
-        for (int l = 0; l < nlv; ++l)
-            for (int k = c.loff[l] + tid; k < c.loff[l + 1]; k += nt) {
-                const int b = c.lorder[k];
-                reinterpret_cast<int32_t*>(RF + 2 * b + 1)[3] = l;
-                reinterpret_cast<int32_t*>(RB + 2 * b + 1)[3] = l;
-            }
-        __syncthreads();
-        auto lev = [&](int b) -> int { return reinterpret_cast<const int32_t*>(RF + 2 * b + 1)[3]; };
-        auto back_in = [&](int b, int dir) -> bool {
-            const int lb = lev(b);
-            if (!dir) {
-                for (int j = pp[b]; j < pp[b + 1]; ++j)
-                    if (lev(c.pred_idx[j]) >= lb) return true;
-            }
-            else {
-                for (int e = c.succ_ptr[b]; e < c.succ_ptr[b + 1]; ++e)
-                    if (lev(c.succ_idx[e]) <= lb) return true;
-            }
-            return false;
-        };
-        __shared__ int s_lw[2][4];
-        const int wv = tid >> 6;
-        int cnt2[2] = {0, 0};
-        for (int pass = 0; pass < 2; ++pass) {   // 0: count, 1: write
-            if (pass == 1 && cnt2[0] + cnt2[1] >= nb) {
-                if (tid == 0) c.tmp[0] = -2;
-                break;
-            }
-            int base[2] = {0, 0};
-            for (int b0 = 0; b0 < nb; b0 += nt) {
-                const int b = b0 + tid;
-                const bool f = b < nb && back_in(b, 0), g = b < nb && back_in(b, 1);
-                const uint64_t mf = __ballot(f), mg = __ballot(g);
-                if ((tid & 63) == 0) { s_lw[0][wv] = __popcll(mf); s_lw[1][wv] = __popcll(mg); }
-                __syncthreads();
-                const uint64_t below = (1ull << (tid & 63)) - 1ull;
-                int af = base[0], ag = base[1];
-                for (int k = 0; k < wv; ++k) { af += s_lw[0][k]; ag += s_lw[1][k]; }
-                af += __popcll(mf & below);
-                ag += __popcll(mg & below);
-                if (pass == 1) {
-                    if (f) c.tmp[af] = b;
-                    if (g) c.tmp[nb - ag] = b;
-                }
-                for (int k = 0; k < (nt >> 6); ++k) { base[0] += s_lw[0][k]; base[1] += s_lw[1][k]; }
-                __syncthreads();
-            }
-            if (pass == 0) { cnt2[0] = base[0]; cnt2[1] = base[1]; }
-            else if (tid == 0) { c.tmp[base[0]] = -1; c.tmp[nb - base[1]] = -1; }
-        }
-        __syncthreads();
-        // level schedule (no walk steps): the records in level order, the block in the last word,
-        // so that a level's positions lead to their records in one load
-        for (int k = tid; k < nb; k += nt) {
-            const int b = c.lorder[k];
-            int4 t1 = RF[2 * b + 1];
-            t1.w = b;
-            SF[2 * k] = RF[2 * b];
-            SF[2 * k + 1] = t1;
-            t1 = RB[2 * b + 1];
-            t1.w = b;
-            SB[2 * k] = RB[2 * b];
-            SB[2 * k + 1] = t1;
-        }
-        return;
-    }
     // step entries in walk order: forward position i is block i (or lorder[i]), backward position i
     // the block at forward position nb - 1 - i
     const int32_t* pos = unord ? c.loff : nullptr;
@@ -1605,550 +1390,6 @@ __device__ __forceinline__ void solve_phase(const DevCfg& c, int s0, int nw, int
 }
 
 // ---------------------------------------------------------------------------
-// Level schedule: the same phases with the blocks of a level in parallel.
-// The ingest kernel sorts a CFG's blocks into levels (a block's level is one
-// more than the highest level of its predecessors over edges other than
-// BACK, found by peeling the graph from ENTRY); no edge other than BACK joins
-// two blocks of one level, so a sweep visits the levels in order (backward:
-// in reverse) and all blocks of a level at once, each against its
-// neighbours' latest states: Gauss-Seidel across levels, Jacobi within one.
-// A level tile is one 32-bit column of a CFG (half of a 64-bit word: 32
-// variables) or its flag column; one workgroup holds the column's state of
-// every block in LDS (8 bytes per block: host and device halves), so a
-// level costs LDS reads of the neighbours, the blocks' inputs from global
-// memory and a barrier.  At the end of a phase the state goes to the same
-// rows the walk writes, so the passes and later phases read the same arrays
-// whatever schedule produced them.
-// One wavefront per level tile: a level of a few dozen blocks keeps one wavefront busy, and a
-// barrier inside a single wavefront costs no cross-wave synchronisation (a wider level takes
-// several passes of the wavefront).
-constexpr int LV_THREADS = LEVEL_THREADS;
-
-template <int PH>
-__device__ __forceinline__ void level_phase(const DevCfg& c, int hc, uint32_t* SH, uint32_t* SD)
-{
-    constexpr bool with_flags = PH == PH_NU || PH == PH_AVE;
-    constexpr bool BWD = PH == PH_NU || PH == PH_LIVE;
-    const bool flg = hc < 0;
-    if (flg && !with_flags) return;
-    if ((PH == PH_MAYP || PH == PH_LATER) && (c.placement & PL_EAGER)) return;
-    if (PH == PH_LIVE && !refines(c.placement)) return;
-    const int nb = c.nb, wd = c.wd, tid = threadIdx.x;
-    const int w = flg ? 0 : hc >> 1;
-    const bool hi = !flg && (hc & 1);
-    const u64 vm64 = (w == wd - 1 && (c.nv & 63)) ? ((1ull << (c.nv & 63)) - 1ull) : ~0ull;
-    const uint32_t vm = flg ? 3u : (uint32_t)(hi ? vm64 >> 32 : vm64);
-    typedef uint32_t hw;
-    const size_t wo = (size_t)w;
-    // the column's half of row b of a block vector / of edge e of an edge vector
-    auto in = [&](const u64* a, int b) -> hw {
-        return reinterpret_cast<const GAS uint32_t*>(G(a) + (size_t)b * wd + wo)[hi ? 1 : 0];
-    };
-    auto vec = [&](const u64* a) -> hw { return reinterpret_cast<const GAS uint32_t*>(G(a) + wo)[hi ? 1 : 0]; };
-    auto sum = [&](int ci, int r) -> hw { return in(c.sums, ci * SUM_ROWS + r); };
-    // the column's firstprivate variables (none for the flag column)
-    const hw fph = (flg || !wd) ? 0u : reinterpret_cast<const GAS uint32_t*>(G(c.fp) + wo)[hi ? 1 : 0];
-    const int32_t* REC = BWD ? c.rec_b : c.rec_f;
-    const int* LO = c.lorder;
-    const int* LF = c.loff;
-    const int nlev = G(c.info)[INFO_LEVELS];
-    GAS u64* FLG = G(c.flg);   // the flag columns of tile slot 0
-    // neighbour j of a record (j >= 2 from the CSR); edge id with LOOP_ENTRY in bit 31
-    auto nbr = [&](const Rec& r, int j, int& p, uint32_t& e) {
-        if (j == 0) { p = r.n0; e = r.e0; return; }
-        if (j == 1) { p = r.n1; e = r.e1; return; }
-        if (BWD) { p = G(c.succ_idx)[r.ovf + j]; e = (uint32_t)(r.ovf + j); return; }
-        p = G(c.pred_idx)[r.ovf + j];
-        const int ee = G(c.pred_eid)[r.ovf + j];
-        e = (uint32_t)ee | (is_le(c, G(c.kind)[ee]) ? 0x80000000u : 0u);
-    };
-    auto eid = [&](uint32_t e) -> int { return (int)(e & 0x7FFFFFFFu); };
-    // next use after a call block (OR over its successors; final when validity runs)
-    auto nu_after = [&](int b, hw& lh, hw& ld) {
-        lh = 0; ld = 0;
-        for (int e = G(c.succ_ptr)[b]; e < G(c.succ_ptr)[b + 1]; ++e) {
-            const int q = G(c.succ_idx)[e];
-            lh |= in(c.nu_h, q);
-            ld |= in(c.nu_d, q);
-        }
-    };
-    auto valid_out = [&](int b, const Rec& r, hw ih, hw id, hw wr, hw rr, hw& oh, hw& od) {
-        const bool dev = r.meta & REC_DEV;
-        hw ah = dev ? (ih & ~wr) : (ih | wr);
-        hw ad = dev ? ((id | wr) & ~(rr & fph)) : (id & ~wr);
-        if ((r.meta & REC_CALL) && !flg) {
-            hw lh, ld;
-            nu_after(b, lh, ld);
-            const int ci = r.ci;
-            ah = tsel(ah, lh, sum(ci, SUM_TH + 0), sum(ci, SUM_TH + 1), sum(ci, SUM_TH + 2), sum(ci, SUM_TH + 3));
-            ad = tsel(ad, ld, sum(ci, SUM_TD + 0), sum(ci, SUM_TD + 1), sum(ci, SUM_TD + 2), sum(ci, SUM_TD + 3));
-        }
-        oh = ah & vm;
-        od = ad & vm;
-    };
-    auto stop = [&](int b, const Rec& r, hw rr, hw ww, hw& sh, hw& sd) {
-        if (r.meta & REC_EXIT) { sh = vec(c.lx_h); sd = vec(c.lx_d); return; }
-        const bool dev = r.meta & REC_DEV;
-        hw uh = dev ? (rr & fph) : rr, ud = dev ? (rr & ~fph) : 0u;
-        if (r.meta & REC_CALL) {
-            const int ci = r.ci;
-            const hw mw = sum(ci, SUM_MAYW_H) | sum(ci, SUM_MAYW_D);
-            uh |= sum(ci, SUM_MAYR_H) | mw;
-            ud |= sum(ci, SUM_MAYR_D) | mw;
-        }
-        sh = uh | (dev ? 0u : ww);
-        sd = ud | (dev ? ww : 0u);
-    };
-    // the new state of block b from its neighbours' states in LDS
-    auto transfer = [&](int b, hw& vh, hw& vd) {
-        const Rec r = ldrec_v(REC, b);
-        const int cnt = (int)(r.meta & REC_COUNT);
-        const bool dev = r.meta & REC_DEV;
-        if constexpr (PH == PH_NU) {
-            if (r.meta & REC_EXIT) { vh = flg ? 1u : vec(c.lx_h); vd = flg ? 0u : vec(c.lx_d); return; }
-            hw oh = 0, od = 0;
-            for (int j = 0; j < cnt; ++j) {
-                int q; uint32_t e;
-                nbr(r, j, q, e);
-                oh |= SH[q];
-                od |= SD[q];
-            }
-            const hw rr = flg ? 2u : in(c.R, b), ww = flg ? (dev ? 2u : 0u) : in(c.W, b);
-            if ((r.meta & REC_CALL) && !flg) {
-                oh = sum(r.ci, SUM_NU0_H) | (sum(r.ci, SUM_NU1_H) & oh);
-                od = sum(r.ci, SUM_NU0_D) | (sum(r.ci, SUM_NU1_D) & od);
-            }
-            vh = (dev ? (rr & fph) : rr) | (~ww & oh);
-            vd = (dev ? (rr & ~fph) : 0u) | (~ww & od);
-        } else if constexpr (PH == PH_AVE) {
-            hw ih, id;
-            if (r.meta & REC_ENTRY) { ih = flg ? 2u : vec(c.ev_h); id = flg ? 0u : vec(c.ev_d); }
-            else {
-                hw mh = ~0u, md = ~0u;
-                for (int j = 0; j < cnt; ++j) {
-                    int p; uint32_t e;
-                    nbr(r, j, p, e);
-                    mh &= SH[p];
-                    md &= SD[p];
-                }
-                ih = (flg ? 0u : in(c.nu_h, b)) | mh;
-                id = (flg ? 0u : in(c.nu_d, b)) | md;
-            }
-            valid_out(b, r, ih & vm, id & vm, flg ? (dev ? 2u : 0u) : in(c.W, b), flg ? 0u : in(c.R, b), vh, vd);
-        } else if constexpr (PH == PH_MAYP) {
-            if (r.meta & REC_ENTRY) { vh = 0; vd = 0; return; }
-            hw mh = 0, md = 0;
-            for (int j = 0; j < cnt; ++j) {
-                int p; uint32_t e;
-                nbr(r, j, p, e);
-                if (e & 0x80000000u) continue;   // loop entry: nothing stays pending
-                mh |= in(c.eag_h, eid(e)) | SH[p];
-                md |= in(c.eag_d, eid(e)) | SD[p];
-            }
-            hw sth, std_;
-            stop(b, r, in(c.R, b), in(c.W, b), sth, std_);
-            vh = mh & ~sth & vm;
-            vd = md & ~std_ & vm;
-        } else if constexpr (PH == PH_LATER) {
-            if (r.meta & REC_ENTRY) { vh = 0; vd = 0; return; }
-            hw allh = ~0u, alld = ~0u, anyh = 0, anyd = 0;
-            for (int j = 0; j < cnt; ++j) {
-                int p; uint32_t e;
-                nbr(r, j, p, e);
-                const hw le = (e & 0x80000000u) ? ~0u : 0u;
-                const hw lh = in(c.eag_h, eid(e)) | SH[p], ld = in(c.eag_d, eid(e)) | SD[p];
-                const hw bo = in(c.both, eid(e));
-                allh &= lh | bo;
-                alld &= ld | bo;
-                anyh |= lh & ~le;
-                anyd |= ld & ~le;
-            }
-            hw sth, std_;
-            stop(b, r, in(c.R, b), in(c.W, b), sth, std_);
-            vh = allh & anyh & vm & ~sth;
-            vd = alld & anyd & vm & ~std_;
-        } else if constexpr (PH == PH_LIVE) {
-            hw oh = 0, od = 0;
-            for (int j = 0; j < cnt; ++j) {
-                int q; uint32_t e;
-                nbr(r, j, q, e);
-                const hw gh = in(c.ig_h, eid(e)), gd = in(c.ig_d, eid(e));
-                oh |= (SH[q] & ~gh) | gd;
-                od |= (SD[q] & ~gd) | gh;
-            }
-            hw rh, rd, kh = 0u, kd = 0u;
-            if (r.meta & REC_EXIT) { rh = vec(c.lx_h); rd = vec(c.lx_d); }
-            else if (r.meta & REC_CALL) { rh = ~0u; rd = ~0u; }
-            else {
-                const hw rr = in(c.R, b), ww = in(c.W, b);
-                rh = dev ? (rr & fph) : rr;
-                rd = dev ? (rr & ~fph) : 0u;
-                kh = dev ? 0u : ww;
-                kd = dev ? (ww | (rr & fph)) : 0u;
-            }
-            const hw ih = in(c.ie_h, b), id = in(c.ie_d, b);
-            const hw ah = rh | (oh & ~kh), ad = rd | (od & ~kd);
-            vh = ((ah & ~ih) | id) & vm;
-            vd = ((ad & ~id) | ih) & vm;
-        } else {   // PH_AVF
-            hw ih, id;
-            if (r.meta & REC_ENTRY) { ih = vec(c.ev_h); id = vec(c.ev_d); }
-            else {
-                hw mh = ~0u, md = ~0u;
-                for (int j = 0; j < cnt; ++j) {
-                    int p; uint32_t e;
-                    nbr(r, j, p, e);
-                    mh &= SH[p] | in(c.ig_h, eid(e));
-                    md &= SD[p] | in(c.ig_d, eid(e));
-                }
-                ih = in(c.ie_h, b) | mh;
-                id = in(c.ie_d, b) | md;
-            }
-            valid_out(b, r, ih & vm, id & vm, in(c.W, b), in(c.R, b), vh, vd);
-        }
-    };
-    // The common block (not ENTRY, EXIT or a call) in two halves: its global inputs (rows of the
-    // block and of its first two edges, constant within the phase) into X, and the new state from
-    // X and its neighbours' states in LDS (further neighbours' edge rows loaded there).
-    constexpr int NXL = PH == PH_NU ? 2 : PH == PH_AVE ? 4 : PH == PH_MAYP ? 6 : 8;
-    // (the flag column reads a word of its own flag rows instead, which always exist, and uses
-    // constants: no branch, so that the loads of a round go out together)
-    const GAS uint32_t* safe = reinterpret_cast<const GAS uint32_t*>(FLG);
-    auto at = [&](const u64* a, int i) -> hw {
-        const GAS uint32_t* p = reinterpret_cast<const GAS uint32_t*>(G(a) + (size_t)i * wd + wo) + (hi ? 1 : 0);
-        return *(flg ? safe : p);
-    };
-    auto is_fast = [&](uint32_t meta) { return !(meta & (REC_ENTRY | REC_EXIT | REC_CALL)); };
-    // Neighbours 2 .. cnt-1 of a block with more than two, folded into the accumulators by
-    // `fold(state h, state d, edge row h, edge row d, third edge row, loop entry)`: eight at a
-    // time, first their CSR entries, then their states and edge rows, every slot loaded (past
-    // the last neighbour the last one again: each phase's meet is idempotent).
-    auto extra = [&](const int4& r0, const int4& r1, auto&& fold) {
-        const int cnt = (int)((uint32_t)r0.x & REC_COUNT), ovf = r1.y;
-        for (int j0 = 2; j0 < cnt; j0 += 8) {
-            int pj[8], ej[8];
-#pragma unroll
-            for (int t = 0; t < 8; ++t) {
-                const int jj = ovf + (j0 + t < cnt ? j0 + t : cnt - 1);
-                if constexpr (BWD) { pj[t] = G(c.succ_idx)[jj]; ej[t] = jj; }
-                else { pj[t] = G(c.pred_idx)[jj]; ej[t] = G(c.pred_eid)[jj]; }
-            }
-            hw g0[8], g1[8], g2[8];
-            bool le[8];
-#pragma unroll
-            for (int t = 0; t < 8; ++t) {
-                le[t] = false;
-                g0[t] = g1[t] = g2[t] = 0u;
-                if constexpr (PH == PH_MAYP || PH == PH_LATER) {
-                    le[t] = is_le(c, G(c.kind)[ej[t]]);
-                    g0[t] = at(c.eag_h, ej[t]);
-                    g1[t] = at(c.eag_d, ej[t]);
-                    if constexpr (PH == PH_LATER) g2[t] = at(c.both, ej[t]);
-                }
-                if constexpr (PH == PH_LIVE || PH == PH_AVF) {
-                    g0[t] = at(c.ig_h, ej[t]);
-                    g1[t] = at(c.ig_d, ej[t]);
-                }
-            }
-#pragma unroll
-            for (int t = 0; t < 8; ++t) fold(SH[pj[t]], SD[pj[t]], g0[t], g1[t], g2[t], le[t]);
-        }
-    };
-    auto gather = [&](const int4& r0, const int4& r1, hw* X) {
-        // every load is issued whatever the block, at a clamped index (a missing edge reads
-        // edge 0), so that a round issues the same loads every time
-        const int b = r1.w;
-        const int cnt = (int)((uint32_t)r0.x & REC_COUNT);
-        int e0 = r0.w & 0x7FFFFFFF, e1 = r1.x & 0x7FFFFFFF;
-        if (cnt < 1 || e0 >= c.ne) e0 = 0;
-        if (cnt < 2 || e1 >= c.ne) e1 = e0;
-        if constexpr (PH == PH_NU) { X[0] = at(c.R, b); X[1] = at(c.W, b); }
-        if constexpr (PH == PH_AVE) { X[0] = at(c.nu_h, b); X[1] = at(c.nu_d, b); X[2] = at(c.W, b); X[3] = at(c.R, b); }
-        if constexpr (PH == PH_MAYP || PH == PH_LATER) {
-            X[0] = at(c.eag_h, e0); X[1] = at(c.eag_d, e0); X[2] = at(c.eag_h, e1); X[3] = at(c.eag_d, e1);
-        }
-        if constexpr (PH == PH_MAYP) { X[4] = at(c.R, b); X[5] = at(c.W, b); }
-        if constexpr (PH == PH_LATER) { X[4] = at(c.both, e0); X[5] = at(c.both, e1); X[6] = at(c.R, b); X[7] = at(c.W, b); }
-        if constexpr (PH == PH_LIVE || PH == PH_AVF) {
-            X[0] = at(c.ig_h, e0); X[1] = at(c.ig_d, e0); X[2] = at(c.ig_h, e1); X[3] = at(c.ig_d, e1);
-        }
-        if constexpr (PH == PH_LIVE) { X[4] = at(c.R, b); X[5] = at(c.W, b); X[6] = at(c.ie_h, b); X[7] = at(c.ie_d, b); }
-        if constexpr (PH == PH_AVF) { X[4] = at(c.ie_h, b); X[5] = at(c.ie_d, b); X[6] = at(c.W, b); X[7] = at(c.R, b); }
-    };
-    auto apply = [&](const int4& r0, const int4& r1, const hw* X, hw& vh, hw& vd) {
-        const uint32_t meta = (uint32_t)r0.x;
-        const int cnt = (int)(meta & REC_COUNT);
-        const bool dev = meta & REC_DEV;
-        const int nbr0 = r0.y, nbr1 = r0.z;
-        const bool le0 = (uint32_t)r0.w & 0x80000000u, le1 = (uint32_t)r1.x & 0x80000000u;
-        if constexpr (PH == PH_NU) {
-            hw oh = 0, od = 0;
-            if (cnt > 0) { oh |= SH[nbr0]; od |= SD[nbr0]; }
-            if (cnt > 1) { oh |= SH[nbr1]; od |= SD[nbr1]; }
-            if (cnt > 2) extra(r0, r1, [&](hw sh, hw sd, hw, hw, hw, bool) { oh |= sh; od |= sd; });
-            const hw rr = flg ? 2u : X[0], ww = flg ? (dev ? 2u : 0u) : X[1];
-            vh = (dev ? (rr & fph) : rr) | (~ww & oh);
-            vd = (dev ? (rr & ~fph) : 0u) | (~ww & od);
-        } else if constexpr (PH == PH_AVE) {
-            hw mh = ~0u, md = ~0u;
-            if (cnt > 0) { mh &= SH[nbr0]; md &= SD[nbr0]; }
-            if (cnt > 1) { mh &= SH[nbr1]; md &= SD[nbr1]; }
-            if (cnt > 2) extra(r0, r1, [&](hw sh, hw sd, hw, hw, hw, bool) { mh &= sh; md &= sd; });
-            const hw ih = ((flg ? 0u : X[0]) | mh) & vm, id = ((flg ? 0u : X[1]) | md) & vm;
-            const hw wr = flg ? (dev ? 2u : 0u) : X[2], rr = flg ? 0u : X[3];
-            const hw ah = dev ? (ih & ~wr) : (ih | wr);
-            const hw ad = dev ? ((id | wr) & ~(rr & fph)) : (id & ~wr);
-            vh = ah & vm;
-            vd = ad & vm;
-        } else if constexpr (PH == PH_MAYP || PH == PH_LATER) {
-            const hw rr = X[PH == PH_MAYP ? 4 : 6], ww = X[PH == PH_MAYP ? 5 : 7];
-            const hw sth = (dev ? (rr & fph) : rr) | (dev ? 0u : ww);
-            const hw std_ = (dev ? (rr & ~fph) : 0u) | (dev ? ww : 0u);
-            if constexpr (PH == PH_MAYP) {
-                hw mh = 0, md = 0;
-                if (cnt > 0 && !le0) { mh |= X[0] | SH[nbr0]; md |= X[1] | SD[nbr0]; }
-                if (cnt > 1 && !le1) { mh |= X[2] | SH[nbr1]; md |= X[3] | SD[nbr1]; }
-                if (cnt > 2)
-                    extra(r0, r1, [&](hw sh, hw sd, hw gh, hw gd, hw, bool l) {
-                        if (!l) { mh |= gh | sh; md |= gd | sd; }
-                    });
-                vh = mh & ~sth & vm;
-                vd = md & ~std_ & vm;
-            } else {
-                hw allh = ~0u, alld = ~0u, anyh = 0, anyd = 0;
-                if (cnt > 0) {
-                    const hw lh = X[0] | SH[nbr0], ld = X[1] | SD[nbr0];
-                    allh &= lh | X[4];
-                    alld &= ld | X[4];
-                    if (!le0) { anyh |= lh; anyd |= ld; }
-                }
-                if (cnt > 1) {
-                    const hw lh = X[2] | SH[nbr1], ld = X[3] | SD[nbr1];
-                    allh &= lh | X[5];
-                    alld &= ld | X[5];
-                    if (!le1) { anyh |= lh; anyd |= ld; }
-                }
-                if (cnt > 2)
-                    extra(r0, r1, [&](hw sh, hw sd, hw gh, hw gd, hw bo, bool l) {
-                        const hw lh = gh | sh, ld = gd | sd;
-                        allh &= lh | bo;
-                        alld &= ld | bo;
-                        if (!l) { anyh |= lh; anyd |= ld; }
-                    });
-                vh = allh & anyh & vm & ~sth;
-                vd = alld & anyd & vm & ~std_;
-            }
-        } else if constexpr (PH == PH_LIVE) {
-            hw oh = 0, od = 0;
-            if (cnt > 0) { oh |= (SH[nbr0] & ~X[0]) | X[1]; od |= (SD[nbr0] & ~X[1]) | X[0]; }
-            if (cnt > 1) { oh |= (SH[nbr1] & ~X[2]) | X[3]; od |= (SD[nbr1] & ~X[3]) | X[2]; }
-            if (cnt > 2)
-                extra(r0, r1, [&](hw sh, hw sd, hw gh, hw gd, hw, bool) {
-                    oh |= (sh & ~gh) | gd;
-                    od |= (sd & ~gd) | gh;
-                });
-            const hw rr = X[4], ww = X[5];
-            const hw rh = dev ? (rr & fph) : rr, rd = dev ? (rr & ~fph) : 0u;
-            const hw kh = dev ? 0u : ww, kd = dev ? (ww | (rr & fph)) : 0u;
-            const hw ih = X[6], id = X[7];
-            const hw ah = rh | (oh & ~kh), ad = rd | (od & ~kd);
-            vh = ((ah & ~ih) | id) & vm;
-            vd = ((ad & ~id) | ih) & vm;
-        } else {   // PH_AVF
-            hw mh = ~0u, md = ~0u;
-            if (cnt > 0) { mh &= SH[nbr0] | X[0]; md &= SD[nbr0] | X[1]; }
-            if (cnt > 1) { mh &= SH[nbr1] | X[2]; md &= SD[nbr1] | X[3]; }
-            if (cnt > 2) extra(r0, r1, [&](hw sh, hw sd, hw gh, hw gd, hw, bool) { mh &= sh | gh; md &= sd | gd; });
-            const hw ih = (X[4] | mh) & vm, id = (X[5] | md) & vm, wr = X[6], rr = X[7];
-            const hw ah = dev ? (ih & ~wr) : (ih | wr);
-            const hw ad = dev ? ((id | wr) & ~(rr & fph)) : (id & ~wr);
-            vh = ah & vm;
-            vd = ad & vm;
-        }
-    };
-    // After a sweep that changed something: would the next one change nothing?  Only blocks
-    // that read a neighbour whose level is not below their own can see other states in the
-    // next sweep than in this one; the ingest kernel lists them in c.tmp (forward phases from
-    // the front, backward ones from the back, -1 ends a list, c.tmp[0] = -2: no lists).  If
-    // none of them, evaluated against the states in LDS, changes, then level by level the next
-    // sweep repeats this one and the states are the fixed point.
-    auto settled = [&]() -> bool {
-        const GAS int32_t* LST = G(c.tmp);
-        if (LST[0] == -2) return false;
-        bool diff = false;
-        for (int j0 = 0;; j0 += LV_THREADS) {
-            const int idx = BWD ? nb - (j0 + tid) : j0 + tid;
-            const int b = (idx >= 0 && idx <= nb) ? LST[idx] : -1;
-            const u64 endm = __ballot(b < 0);
-            const int t = endm ? (int)__builtin_ctzll(endm) : LV_THREADS;
-            if (tid < t) {
-                hw vh, vd;
-                transfer(b, vh, vd);
-                if (vh != SH[b] || vd != SD[b]) diff = true;
-            }
-            if (__syncthreads_or(diff) || t < LV_THREADS) break;
-        }
-        return !__syncthreads_or(diff);
-    };
-    const hw init = (PH == PH_AVE || PH == PH_AVF) ? vm : 0u;
-    for (int b = tid; b < nb; b += LV_THREADS) { SH[b] = init; SD[b] = init; }
-    __syncthreads();
-    const int cap = c.sweep_cap > 0 ? c.sweep_cap : 2 * nb + 2;
-    int sweeps = 0;
-    bool good = true;
-    // Super-steps of S levels: the loads of S levels go out in three rounds (their bounds, then
-    // the records of the thread's positions in them, in level order with the block in the last
-    // word, then the rows of those blocks and their first two edges), every load issued whatever
-    // the level (indices clamped), so that each round is one latency for S levels; then the S
-    // levels are computed one after another.  Lane tid takes position LF[lv] + tid of each
-    // level (and every LV_THREADS-th one after it, with direct loads, as do calls, ENTRY and
-    // EXIT).
-    constexpr int S = 8;
-    const int4* LR = reinterpret_cast<const int4*>(BWD ? c.step_b : c.step_f);
-    int2 bq[S];
-    int4 r0q[S], r1q[S];
-    hw xq[S][NXL];
-    int chg = 0;
-    for (;;) {
-        for (int li0 = 0; li0 < nlev; li0 += S) {
-            const int ns = nlev - li0 < S ? nlev - li0 : S;
-#pragma unroll
-            for (int v = 0; v < S; ++v) {
-                const int li = li0 + v < nlev ? li0 + v : nlev - 1;
-                const int lv = BWD ? nlev - 1 - li : li;
-                bq[v].x = G(LF)[lv];
-                bq[v].y = G(LF)[lv + 1];
-            }
-#pragma unroll
-            for (int v = 0; v < S; ++v) {
-                typedef int v4i __attribute__((ext_vector_type(4)));
-                int k = bq[v].x + tid;
-                if (k >= nb) k = nb - 1;
-                const GAS v4i* p = reinterpret_cast<const GAS v4i*>(G(LR)) + 2 * (size_t)k;
-                const v4i x = p[0], y = p[1];
-                r0q[v] = make_int4(x.x, x.y, x.z, x.w);
-                r1q[v] = make_int4(y.x, y.y, y.z, y.w);
-            }
-#pragma unroll
-            for (int v = 0; v < S; ++v) gather(r0q[v], r1q[v], xq[v]);
-#pragma unroll
-            for (int v = 0; v < S; ++v) {
-                if (v < ns) {
-                    const int2 q = bq[v];
-                    if (q.x + tid < q.y) {
-                        const int4 r0 = r0q[v], r1 = r1q[v];
-                        const int b = r1.w;
-                        hw vh, vd;
-                        if (is_fast((uint32_t)r0.x)) apply(r0, r1, xq[v], vh, vd);
-                        else transfer(b, vh, vd);
-                        if (vh != SH[b] || vd != SD[b]) {
-                            SH[b] = vh;
-                            SD[b] = vd;
-                            chg = 1;
-                        }
-                    }
-                    // positions past the first LV_THREADS of a wide level
-                    for (int k = q.x + tid + LV_THREADS; k < q.y; k += LV_THREADS) {
-                        const int bb = LO[k];
-                        hw vh, vd;
-                        transfer(bb, vh, vd);
-                        if (vh != SH[bb] || vd != SD[bb]) {
-                            SH[bb] = vh;
-                            SD[bb] = vd;
-                            chg = 1;
-                        }
-                    }
-                    // the level's LDS writes before the next level's reads (no wait for the
-                    // loads: none is in flight here)
-                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-                    __builtin_amdgcn_s_barrier();
-                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-                }
-            }
-        }
-        ++sweeps;
-        if (!__syncthreads_or(chg)) break;
-        if (settled()) break;
-        if (sweeps >= cap) {
-            if (tid == 0) set_status(c.info, OMPD_E_NOCONVERGE_);
-            good = false;
-            break;
-        }
-        chg = 0;
-    }
-    if (tid == 0) atomicMax(&c.info[INFO_SWEEPS + PH], sweeps);
-    // the state to the rows of the phase (flag column: tile slot 0's columns)
-    if (flg) {
-        const int fl = PH == PH_NU ? 0 : 2;
-        for (int b = tid; b < nb; b += LV_THREADS) {
-            FLG[(size_t)fl * nb + b] = SH[b];
-            FLG[(size_t)(fl + 1) * nb + b] = SD[b];
-        }
-    } else {
-        // (the refinement keeps its state in the pending-copy rows, free after the placement)
-        u64* h = PH == PH_NU ? c.nu_h : PH == PH_MAYP || PH == PH_LIVE ? c.mayp_h : PH == PH_LATER ? c.later_h : c.aveout_h;
-        u64* d = PH == PH_NU ? c.nu_d : PH == PH_MAYP || PH == PH_LIVE ? c.mayp_d : PH == PH_LATER ? c.later_d : c.aveout_d;
-        for (int b = tid; b < nb; b += LV_THREADS) {
-            reinterpret_cast<GAS uint32_t*>(G(h) + (size_t)b * wd + wo)[hi ? 1 : 0] = SH[b];
-            reinterpret_cast<GAS uint32_t*>(G(d) + (size_t)b * wd + wo)[hi ? 1 : 0] = SD[b];
-        }
-    }
-    if constexpr (PH == PH_AVE) {
-        if (!flg || !good) return;
-        // reachability: every block reached from ENTRY and reaching EXIT; the label facts
-        int bad = 0;
-        for (int b = tid; b < nb; b += LV_THREADS) {
-            const u64 fnu = FLG[b], fnud = FLG[(size_t)nb + b];
-            const hw fave = SH[b];
-            if (!(fnu & 1) || (fave & 1)) bad = 1;
-            if (c.after_dev) G(c.after_dev)[b] = (uint8_t)(((fave >> 1) & 1) ^ 1);
-            if (c.before_dev) G(c.before_dev)[b] = (uint8_t)((fnud >> 1) & 1);
-        }
-        if (__syncthreads_or(bad) && tid == 0) set_status(c.info, OMPD_E_INVAL_);
-    }
-}
-
-// One persistent kernel per phase over the level tiles (one workgroup of LV_THREADS per tile,
-// the column's state in dynamic LDS).  A tile (cfg, s0, nw, fslot): s0 = the 32-bit column
-// (word s0 / 2, its high half when s0 is odd) or -1 for the flag column.
-template <int PH>
-__device__ __forceinline__ void level_kernel(const DevCfg* __restrict__ cfgs, const Tile* __restrict__ tiles,
-                                             int n_tiles, int32_t* __restrict__ counter)
-{
-    extern __shared__ __align__(16) u64 lds[];
-    __shared__ int s_tile, s_skip;
-    for (;;) {
-        if (threadIdx.x == 0) s_tile = atomicAdd(&counter[16 + PH], 1);
-        __syncthreads();
-        const int t = s_tile;
-        __syncthreads();
-        if (t >= n_tiles) break;
-        const Tile tl = tiles[t];
-        const DevCfg c = cfgs[tl.cfg];
-        if (threadIdx.x == 0) s_skip = G(c.info)[INFO_STATUS] != 0;
-        __syncthreads();
-        if (!s_skip) {
-            uint32_t* SH = reinterpret_cast<uint32_t*>(lds);
-            level_phase<PH>(c, tl.s0, SH, SH + c.nb);
-        }
-        __syncthreads();
-    }
-}
-#define OMPD_LEVEL_KERNEL(name, ph)                                                                          \
-    extern "C" __global__ void __launch_bounds__(LV_THREADS) name(const DevCfg* __restrict__ cfgs,          \
-                                                                   const Tile* __restrict__ tiles,           \
-                                                                   int n_tiles, int32_t* __restrict__ counter) \
-    {                                                                                                        \
-        level_kernel<ph>(cfgs, tiles, n_tiles, counter);                                                     \
-    }
-OMPD_LEVEL_KERNEL(ompd_k_lv_nu, PH_NU)
-OMPD_LEVEL_KERNEL(ompd_k_lv_ave, PH_AVE)
-OMPD_LEVEL_KERNEL(ompd_k_lv_mayp, PH_MAYP)
-OMPD_LEVEL_KERNEL(ompd_k_lv_later, PH_LATER)
-OMPD_LEVEL_KERNEL(ompd_k_lv_avf, PH_AVF)
-OMPD_LEVEL_KERNEL(ompd_k_lv_live, PH_LIVE)
-
-// ---------------------------------------------------------------------------
 // Edge-parallel passes (no iteration): one wavefront per (tile, 64-block
 // chunk) item; the item's nw words are spread over the lanes 64 / nw times
 // (lane = block slot * nw + word), so that a narrow item keeps that many
@@ -2357,9 +1598,9 @@ __device__ __forceinline__ void tile_phase(const DevCfg& c, const Tile& tl, u64*
         __syncthreads();
         return;
     }
-    // a CFG on the level schedule is solved by the level kernels; lanes past 2 LANES hold no word
+    // lanes past 2 LANES hold no word
     // (the walk order the ingest kernel chose: the block ids, or its own)
-    if (c.sched != SCHED_LEVEL && (threadIdx.x & 63) < 2 * LANES) {
+    if ((threadIdx.x & 63) < 2 * LANES) {
         if (__builtin_amdgcn_readfirstlane(G(c.info)[INFO_ORDER]))
             solve_phase<PH, true>(c, tl.s0, tl.nw, tl.fslot, lds, ring_slots);
         else

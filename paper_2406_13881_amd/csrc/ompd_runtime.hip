@@ -28,17 +28,14 @@ extern "C" __global__ void ompd_k_post_later(const DevCfg*, const Tile*, const E
 extern "C" __global__ void ompd_k_post_avf(const DevCfg*, const Tile*, const EdgeItem*, int, int32_t*);
 extern "C" __global__ void ompd_k_live(const DevCfg*, const Tile*, int, int32_t*, int);
 extern "C" __global__ void ompd_k_post_live(const DevCfg*, const Tile*, const EdgeItem*, int, int32_t*);
-extern "C" __global__ void ompd_k_lv_live(const DevCfg*, const Tile*, int, int32_t*);
 extern "C" __global__ void ompd_k_varkind(const DevCfg*, const Tile*, int, int32_t*);
 extern "C" __global__ void ompd_k_solve(const DevCfg*, const Tile*, int, int32_t*, int);
-extern "C" __global__ void ompd_k_lv_nu(const DevCfg*, const Tile*, int, int32_t*);
-extern "C" __global__ void ompd_k_lv_ave(const DevCfg*, const Tile*, int, int32_t*);
-extern "C" __global__ void ompd_k_lv_mayp(const DevCfg*, const Tile*, int, int32_t*);
-extern "C" __global__ void ompd_k_lv_later(const DevCfg*, const Tile*, int, int32_t*);
-extern "C" __global__ void ompd_k_lv_avf(const DevCfg*, const Tile*, int, int32_t*);
-static const void* const k_levels[N_PHASES] = {(const void*)ompd_k_lv_nu, (const void*)ompd_k_lv_ave,
-                                               (const void*)ompd_k_lv_mayp, (const void*)ompd_k_lv_later,
-                                               (const void*)ompd_k_lv_avf, (const void*)ompd_k_lv_live};
+extern "C" __global__ void ompd_k_sprep(const DevCfg*, int, int);
+extern "C" __global__ void ompd_k_tin(const DevCfg*, const EdgeItem*);
+extern "C" __global__ void ompd_k_strip_a(const DevCfg*, const Tile*);
+extern "C" __global__ void ompd_k_tmid(const DevCfg*, const EdgeItem*);
+extern "C" __global__ void ompd_k_strip_b(const DevCfg*, const Tile*);
+extern "C" __global__ void ompd_k_tout(const DevCfg*, const EdgeItem*);
 static const void* const k_phases[N_PHASES] = {(const void*)ompd_k_nu, (const void*)ompd_k_ave,
                                                (const void*)ompd_k_mayp, (const void*)ompd_k_later,
                                                (const void*)ompd_k_avf, (const void*)ompd_k_live};
@@ -113,8 +110,8 @@ extern "C" int ompd_ctx_create(ompd_ctx** out, int device_ordinal, uint64_t budg
     // dynamic LDS limit per kernel = device limit minus the kernel's static LDS
     int dyn = (int)lds_max;
     for (const void* k : {k_phases[0], k_phases[1], k_phases[2], k_phases[3], k_phases[4], k_phases[5],
-                          (const void*)ompd_k_prep, (const void*)ompd_k_solve, k_levels[0], k_levels[1], k_levels[2],
-                          k_levels[3], k_levels[4], k_levels[5]}) {
+                          (const void*)ompd_k_prep, (const void*)ompd_k_solve, (const void*)ompd_k_sprep,
+                          (const void*)ompd_k_strip_a, (const void*)ompd_k_strip_b}) {
         hipFuncAttributes fa{};
         int st = 0;
         if (hipFuncGetAttributes(&fa, k) == hipSuccess) st = (int)fa.sharedSizeBytes;
@@ -201,19 +198,62 @@ static int check_cfg_host(const ompd_cfg& g, int i)
     return OMPD_OK;
 }
 
-// Scratch of one CFG, offsets relative to its base (each 256-aligned).
-size_t ompd_cfg_scratch(const ompd_cfg& g, const ompd_result& r, ScratchOff& o)
+size_t ompd_cfg_scratch(const ompd_cfg& g, const ompd_result& r, ScratchOff& o, int rows)
 {
     size_t total = 0;
     auto take = [&](size_t bytes) { size_t x = total; total += align256(bytes); return x; };
-    size_t wd = (size_t)(g.n_vars + 63) / 64;
-    size_t bv = (size_t)g.n_blocks * wd * 8, ev = (size_t)g.n_edges * wd * 8;
+    const size_t wd = (size_t)(g.n_vars + 63) / 64, nb = (size_t)g.n_blocks, ne = (size_t)g.n_edges;
+    const size_t bv = nb * wd * 8, ev = ne * wd * 8;
     o.aveout = take(2 * bv);
     o.mayp = take(2 * bv);
     o.later = take(2 * bv);
     o.eag = take(2 * ev);
     o.both = take(ev);
-    o.flg = take((size_t)tiles_of((int)wd) * 4 * (size_t)g.n_blocks * 8);
+    o.flg = take((size_t)tiles_of((int)wd) * 4 * nb * 8);
+    o.pp = take(4 * (nb + 1));
+    o.pi = take(4 * std::max<size_t>(ne, 1));
+    o.pe = take(4 * std::max<size_t>(ne, 1));
+    o.tmp = take(4 * (nb + 1));
+    o.recf = take(32 * nb);
+    o.recb = take(32 * nb);
+    o.stf = take(32 * nb);
+    o.stb = take(32 * nb);
+    o.lorder = take(4 * nb);
+    o.loff = take(4 * (nb + 1));
+    const size_t walk = total;
+    total = 0;
+    auto put = [&](size_t bytes) { size_t x = total; total += (bytes + 63) & ~(size_t)63; return x; };
+    const size_t units = wd + 1, nrec = (size_t)strip_records(g.n_edges);
+    o.rows = std::max(rows, 4 / strip_units(g.n_blocks, (int)wd));
+    const size_t recs = 128 * nb * o.rows;   // (at most a pass per block)
+    o.s_rw = put(16 * units * nb);
+    o.s_1 = put(16 * units * nb);
+    o.s_2 = put(16 * units * nb);
+    o.s_3 = put(16 * units * nb);
+    o.s_g = put(16 * wd * nrec);
+    o.s_b = put(8 * wd * nrec);
+    o.s_recf = put(recs);
+    o.s_recb = put(recs);
+    o.s_link = put(4 * nrec);
+    o.s_eid = put(4 * nrec);
+    o.s_erec = put(4 * ne);
+    o.s_xf = put(4 * (ne + 2));
+    o.s_xb = put(4 * (ne + 2));
+    o.s_estf = put(4 * (nb + 1));
+    o.s_estb = put(4 * (nb + 1));
+    o.s_locf = put(4 * nb);
+    o.s_locb = put(4 * nb);
+    o.s_kc = put(4 * (nb + 1));
+    o.s_lorder = put(4 * nb);
+    o.s_loff = put(4 * (nb + 1));
+    o.s_pos = put(2 * nb);
+    o.s_lastf = put(2 * nb);
+    o.s_lastb = put(2 * nb);
+    o.s_facts = put(nb);
+    o.s_hdr = put(4 * SH_WORDS);
+    // positions are 15-bit numbers, edge entries 16-bit ones
+    o.strip = nb <= (size_t)STRIP_MAX_BLOCKS && ne < 65535 && (rows > 0 || total <= walk);
+    total = align256(o.strip ? std::max(walk, total) : walk);
     o.nu = (r.nu_host && r.nu_dev) ? SIZE_MAX : take(2 * bv);
     o.ave = (r.ave_host && r.ave_dev) ? SIZE_MAX : take(2 * bv);
     o.ie = (r.ins_entry_to_host && r.ins_entry_to_dev) ? SIZE_MAX : take(2 * bv);
@@ -222,56 +262,54 @@ size_t ompd_cfg_scratch(const ompd_cfg& g, const ompd_result& r, ScratchOff& o)
     o.vk = r.var_kind ? take(4 * wd * 8) : SIZE_MAX;
     o.fp = take(wd * 8 + 8);
     o.bnd = take(4 * wd * 8);
-    o.pp = take(4 * ((size_t)g.n_blocks + 1));
-    o.pi = take(4 * (size_t)std::max(g.n_edges, 1));
-    o.pe = take(4 * (size_t)std::max(g.n_edges, 1));
-    o.tmp = take(4 * ((size_t)g.n_blocks + 1));
-    o.recf = take(32 * (size_t)g.n_blocks);
-    o.recb = take(32 * (size_t)g.n_blocks);
-    o.stf = take(32 * (size_t)g.n_blocks);
-    o.stb = take(32 * (size_t)g.n_blocks);
-    o.lorder = take(4 * (size_t)g.n_blocks);
-    o.loff = take(4 * ((size_t)g.n_blocks + 1));
     o.info = take(4 * INFO_WORDS);
     return total;
 }
 
-// The schedule of a CFG when the caller names none: the level schedule for
-// large CFGs, whose levels hold enough blocks to keep a workgroup busy.
-int ompd_default_sched(int n_blocks, int n_vars)
+int32_t ompd_want(const ompd_result& r)
 {
-    (void)n_vars;
-    return n_blocks >= OMPD_LEVEL_MIN_BLOCKS ? SCHED_LEVEL : SCHED_WALK;
+    return (r.nu_host ? WANT_NU_H : 0) | (r.nu_dev ? WANT_NU_D : 0) | (r.ave_host ? WANT_AVE_H : 0) |
+           (r.ave_dev ? WANT_AVE_D : 0) | (r.avf_host ? WANT_AVF_H : 0) | (r.avf_dev ? WANT_AVF_D : 0) |
+           (r.ins_entry_to_host ? WANT_IE_H : 0) | (r.ins_entry_to_dev ? WANT_IE_D : 0) |
+           (r.ins_edge_to_host ? WANT_IG_H : 0) | (r.ins_edge_to_dev ? WANT_IG_D : 0);
 }
 
-void ompd_settle_sched(DevCfg* h, int n, int n_cu)
+// Rows of a pass for a launch.  A pass holds 4 rows of 16 lanes: one row of edges for 4 words of
+// variables does the least work per word, 4 rows for one word the fewest passes.  A lone CFG of 8002
+// blocks and 24 words solves in 3.1 ms with one row, 2.6 ms with four; 1024 CFGs (4266 strips of 4
+// words) in 12.1 ms with one row, 16.4 ms with two, 27.2 ms with four.
+int ompd_strip_rows(const ompd_cfg* g, int n)
 {
-    auto by_rule = [&](const DevCfg& d) { return d.sched == SCHED_LEVEL && d.sched_rule; };
-    int64_t tiles = 0;
-    for (int i = 0; i < n; ++i)
-        if (by_rule(h[i])) tiles += 2 * (int64_t)h[i].wd + 1;
-    if (tiles > (int64_t)OMPD_LEVEL_ROUNDS * n_cu) {
-        for (int i = 0; i < n; ++i)
-            if (by_rule(h[i])) h[i].sched = SCHED_WALK;
-        return;
-    }
-    // A launch whose walk tiles leave most CUs idle is bound by its longest tile's dependent
-    // steps, not by throughput: there the level schedule (a wavefront per 32-bit column, the
-    // blocks of a level in parallel) usually finishes a CFG sooner (40 C3 CFGs alone: 0.16-0.9x
-    // the walk's time, a few small ones up to 1.1x), so the CFGs the rule put on the walk move to
-    // it while one round of level tiles holds them all.
-    int64_t walk = 0, level = 0;
+    int64_t words = 0;
+    for (int i = 0; i < n; ++i) words += (g[i].n_vars + 63) / 64 + 1;
+    return words <= 64 ? 4 : words <= 256 ? 2 : 1;
+}
+
+void ompd_settle_sched(DevCfg* h, int n, int n_cu, bool split)
+{
+    int64_t strips = 0;
     for (int i = 0; i < n; ++i) {
-        if (h[i].sched == SCHED_LEVEL) level += 2 * (int64_t)h[i].wd + 1;
-        else walk += tiles_of(h[i].wd);
+        DevCfg& d = h[i];
+        if (d.sched_rule) d.sched = split && d.strip_ok ? SCHED_LEVEL : SCHED_WALK;
+        if (d.sched == SCHED_LEVEL) strips += (d.wd + d.units) / d.units;
     }
-    if (walk == 0 || walk * OMPD_IDLE_FRACTION > n_cu) return;
+    // Blocks per wavefront: the fewer, the shorter a strip's chain of passes, and the more rounds
+    // until what one wavefront changed has reached the others.  While the GPU has room for every
+    // strip at once (a workgroup each) 32 is best; where strips queue for the compute units, their
+    // total work counts and fewer, longer runs cost less.  Solve kernels, us, at 32 / 64 / 200 / 400
+    // blocks: a lone CFG of 66 blocks 163 / 185 / 257 / 257, of 779 blocks 579 / 579 / 625 / 1060;
+    // 96 CFGs (242 strips) 1415 / 1795 / 3020 / 4420; 1024 CFGs (4266 strips) 16.9 / 12.3 / 12.1 /
+    // 12.5 ms; 2048 CFGs of about 60 blocks (2377 strips) 1170 / 841 / 493 / 493.
+    const bool idle = strips <= n_cu;
+    const int busy_per = (int)std::min<int64_t>(200, 32 * strips / std::max(n_cu, 1));
     for (int i = 0; i < n; ++i) {
-        if (h[i].sched != SCHED_WALK || !h[i].sched_rule || h[i].nb > OMPD_LEVEL_MAX_BLOCKS) continue;
-        const int64_t t = 2 * (int64_t)h[i].wd + 1;
-        if (level + t > n_cu) continue;
-        h[i].sched = SCHED_LEVEL;
-        level += t;
+        DevCfg& d = h[i];
+        d.spread = d.sched == SCHED_LEVEL && (idle || !d.sched_rule);
+        const int per = d.spread ? 32 : std::max(32, busy_per);
+        // (a caller's sweep cap counts rounds: one run of passes, so that they don't depend on timing)
+        d.waves = 1;
+        if (d.sweep_cap == 0)
+            while (d.waves < STRIP_MAX_WAVES && d.nb > per * d.waves) d.waves *= 2;
     }
 }
 
@@ -290,11 +328,11 @@ void ompd_fill_devcfg(const ompd_cfg& g, const ompd_result& r, char* base, const
     d.placement = ((flags & OMPD_F_PLACEMENT_EAGER) ? PL_EAGER : 0) | ((flags & OMPD_F_SUMMARY) ? PL_SUMMARY : 0) |
                   ((flags & OMPD_F_PLACEMENT_LAZY) ? PL_LAZY : 0) | ((flags & OMPD_F_PLACEMENT_REFINE) ? PL_REFINE : 0);
     d.sweep_cap = (int)((flags >> 16) & 0xFFFFu);
-    d.sched = (flags & OMPD_F_SCHED_LEVEL) ? SCHED_LEVEL
-            : (flags & OMPD_F_SCHED_WALK) ? SCHED_WALK
-            : ompd_default_sched(g.n_blocks, g.n_vars);
+    d.strip_ok = o.strip;
     d.sched_rule = !(flags & (OMPD_F_SCHED_LEVEL | OMPD_F_SCHED_WALK));
-    if (g.n_blocks > OMPD_LEVEL_MAX_BLOCKS) d.sched = SCHED_WALK;
+    d.sched = o.strip && !(flags & OMPD_F_SCHED_WALK) ? SCHED_LEVEL : SCHED_WALK;
+    d.units = 4 / o.rows;
+    d.waves = 1;
     d.succ_ptr = g.succ_ptr; d.succ_idx = g.succ_idx; d.kind = g.edge_kind; d.space = g.space;
     d.R = g.read_bits; d.W = g.write_bits;
     uint64_t* bnd = bnd_dev ? bnd_dev : (uint64_t*)(base + o.bnd);
@@ -335,7 +373,25 @@ void ompd_fill_devcfg(const ompd_cfg& g, const ompd_result& r, char* base, const
     d.rec_f = (int32_t*)(base + o.recf); d.rec_b = (int32_t*)(base + o.recb);
     d.step_f = (int32_t*)(base + o.stf); d.step_b = (int32_t*)(base + o.stb);
     d.lorder = (int32_t*)(base + o.lorder); d.loff = (int32_t*)(base + o.loff);
-    d.info = (int32_t*)(base + o.info);
+    d.want = ompd_want(r);
+    // (the final validity behind a call reads next use by rows)
+    if (g.call_summary) d.want |= WANT_NU_H | WANT_NU_D;
+    auto u64p = [&](size_t off) { return (uint64_t*)(base + off); };
+    auto u32p = [&](size_t off) { return (uint32_t*)(base + off); };
+    auto i32p = [&](size_t off) { return (int32_t*)(base + off); };
+    auto u16p = [&](size_t off) { return (uint16_t*)(base + off); };
+    d.p_rw = u64p(o.s_rw); d.p_1 = u64p(o.s_1); d.p_2 = u64p(o.s_2); d.p_3 = u64p(o.s_3);
+    d.p_g = u64p(o.s_g); d.p_b = u64p(o.s_b);
+    d.rec_sf = u32p(o.s_recf); d.rec_sb = u32p(o.s_recb);
+    d.link = u32p(o.s_link); d.eid = i32p(o.s_eid); d.erec = i32p(o.s_erec);
+    d.x_f = u32p(o.s_xf); d.x_b = u32p(o.s_xb);
+    d.est_f = i32p(o.s_estf); d.est_b = i32p(o.s_estb);
+    d.loc_f = u32p(o.s_locf); d.loc_b = u32p(o.s_locb);
+    d.pos = u16p(o.s_pos); d.last_f = u16p(o.s_lastf); d.last_b = u16p(o.s_lastb);
+    d.s_kc = i32p(o.s_kc); d.s_lorder = i32p(o.s_lorder); d.s_loff = i32p(o.s_loff);
+    d.facts = (uint8_t*)(base + o.s_facts);
+    d.hdr = i32p(o.s_hdr);
+    d.info = i32p(o.info);
     if (bnd_host && wd > 0) {
         uint64_t last = (g.n_vars & 63) ? ((1ull << (g.n_vars & 63)) - 1) : ~0ull;
         for (int w = 0; w < 4 * wd; ++w) bnd_host[w] = 0;
@@ -359,23 +415,39 @@ int ompd_make_shape(ompd_ctx* ctx, const std::vector<DevCfg>& cfgs, const PlanCo
     sh.items.clear();
     auto in_plan = [&](int i) { return pc.only_bucket < 0 || ompd_sched_bucket(cfgs[i].nb) == pc.only_bucket; };
     for (int i = 0; i < (int)cfgs.size(); ++i)
-        if (in_plan(i)) make_tiles(i, cfgs[i].nv, tiles);
+        if (in_plan(i) && cfgs[i].sched != SCHED_LEVEL) make_tiles(i, cfgs[i].nv, tiles);
     // a tile's work ~ its blocks times the sweeps, which grow with the CFG: longest first
     std::stable_sort(tiles.begin(), tiles.end(),
                      [&](const Tile& a, const Tile& b) { return cfgs[a.cfg].nb > cfgs[b.cfg].nb; });
-    // level tiles (after the walk tiles): each 32-bit column of a CFG on the level schedule, and
-    // its flag column (s0 = -1)
-    std::vector<Tile> lt;
-    int lv_nb = 0;
-    for (int i = 0; i < (int)cfgs.size(); ++i) {
-        if (cfgs[i].sched != SCHED_LEVEL || !in_plan(i)) continue;
-        lv_nb = std::max(lv_nb, cfgs[i].nb);
-        lt.push_back(Tile{i, -1, 0, 0});
-        for (int hc = 0; hc < 2 * cfgs[i].wd; ++hc) lt.push_back(Tile{i, hc, 1, 0});
+    const int walk_tiles = (int)tiles.size();
+    LaunchDims& dm = sh.dims;
+    // strip tiles (after the walk tiles), launch by launch: CFGs with the same wavefronts, the ones
+    // that need most time first
+    {
+        std::vector<int> order;
+        dm.n_walk = dm.n_strip = 0;
+        for (int i = 0; i < (int)cfgs.size(); ++i) {
+            if (cfgs[i].sched != SCHED_LEVEL) { ++dm.n_walk; continue; }
+            ++dm.n_strip;
+            if (in_plan(i)) order.push_back(i);
+        }
+        std::stable_sort(order.begin(), order.end(), [&](int a, int b) {
+            return cfgs[a].waves != cfgs[b].waves ? cfgs[a].waves > cfgs[b].waves : cfgs[a].nb > cfgs[b].nb;
+        });
+        dm.n_buckets = 0;
+        for (int i : order) {
+            const DevCfg& d = cfgs[i];
+            if (!dm.n_buckets || dm.bucket[dm.n_buckets - 1].waves != d.waves)
+                dm.bucket[dm.n_buckets++] = LaunchDims::Bucket{(int)tiles.size() - walk_tiles, 0, d.waves, 0};
+            LaunchDims::Bucket& k = dm.bucket[dm.n_buckets - 1];
+            for (int u = 0; u <= d.wd; u += d.units) {
+                tiles.push_back(Tile{i, u, std::min(d.units, d.wd + 1 - u), 0});
+                ++k.n;
+            }
+            k.lds = std::max(k.lds, strip_lds(d.nb, d.waves));
+        }
     }
-    std::stable_sort(lt.begin(), lt.end(), [&](const Tile& a, const Tile& b) { return cfgs[a.cfg].nb > cfgs[b.cfg].nb; });
-    sh.dims.n_level = (int)lt.size();
-    tiles.insert(tiles.end(), lt.begin(), lt.end());
+    dm.n_level = (int)tiles.size() - walk_tiles;
     // pass items: runs of up to PASS_WORDS words (the passes need no LDS, so a full wavefront of
     // words each), 64-block chunks, longest CFGs first
     {
@@ -384,55 +456,65 @@ int ompd_make_shape(ompd_ctx* ctx, const std::vector<DevCfg>& cfgs, const PlanCo
         std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return cfgs[a].nb > cfgs[b].nb; });
         for (int i : order) {
             const int wd = cfgs[i].wd;
-            if (wd <= 0 || !in_plan(i)) continue;
+            if (wd <= 0 || !in_plan(i) || cfgs[i].sched == SCHED_LEVEL) continue;
             const int runs = (wd + PASS_WORDS - 1) / PASS_WORDS;
             for (int r = 0; r < runs; ++r) {
                 const int s0 = (int)((int64_t)wd * r / runs), s1 = (int)((int64_t)wd * (r + 1) / runs);
                 for (int b0 = 0; b0 < cfgs[i].nb; b0 += 64) sh.items.push_back(EdgeItem{i, s0, s1 - s0, b0});
             }
         }
+        // transpose items of the strip CFGs: block chunks, then record chunks
+        dm.n_tblock = dm.n_tedge = 0;
+        dm.lds_prep = 0;
+        for (int edges = 0; edges < 2; ++edges)
+            for (int i : order) {
+                const DevCfg& d = cfgs[i];
+                if (d.sched != SCHED_LEVEL || !in_plan(i)) continue;
+                const size_t pl = strip_prep_lds(d.nb, d.ne);
+                if (pl <= (size_t)ctx->lds_max) dm.lds_prep = std::max(dm.lds_prep, pl);
+                if (edges && d.wd == 0) continue;
+                const int rows = edges ? strip_records(d.ne) : d.nb;
+                for (int s0 = 0; s0 < std::max(d.wd, 1); s0 += STRIP_T_WORDS)
+                    for (int r = 0; r < rows; r += STRIP_T_ROWS) {
+                        sh.items.push_back(EdgeItem{i, s0, std::min(STRIP_T_WORDS, d.wd - s0), edges ? ~r : r});
+                        ++(edges ? dm.n_tedge : dm.n_tblock);
+                    }
+            }
     }
     // result ring: a power of two of STATE_BYTES slots in [8, 64], as large as every phase's LDS allows
     const size_t want = pc.lds_bytes ? pc.lds_bytes : RING_BYTES_DEFAULT;
     int rs = 8;
     while (rs < 64 && (size_t)(2 * rs) * STATE_BYTES <= want) rs *= 2;
     while (rs > 1 && phase_lds(PH_LATER, rs) > (size_t)ctx->lds_max) rs /= 2;
-    LaunchDims& dm = sh.dims;
     dm.ring_slots = rs;
-    sh.lds_prep = 0;
     // each phase kernel: as many workgroups as it keeps resident
-    for (int ph = 0; ph < N_PHASES; ++ph) {
+    for (int ph = 0; walk_tiles && ph < N_PHASES; ++ph) {
         dm.lds[ph] = phase_lds(ph, rs);
         int n = 0;
         CK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_phases[ph], PHASE_THREADS, dm.lds[ph]));
         n = std::max(1, n);
         if (pc.wg_per_cu > 0) n = std::min(n, pc.wg_per_cu);
-        dm.grid[ph] = std::max(1, std::min((int)tiles.size(), n * ctx->n_cu));
+        dm.grid[ph] = std::max(1, std::min(walk_tiles, n * ctx->n_cu));
     }
     dm.split = pc.split;
     dm.lds_tile = 0;
     for (int ph = 0; ph < N_PHASES; ++ph) dm.lds_tile = std::max(dm.lds_tile, dm.lds[ph]);
     dm.refine = false;
-    for (int i = 0; i < (int)cfgs.size(); ++i) dm.refine |= in_plan(i) && refines(cfgs[i].placement);
-    {
+    for (int i = 0; i < (int)cfgs.size(); ++i)
+        dm.refine |= in_plan(i) && cfgs[i].sched != SCHED_LEVEL && refines(cfgs[i].placement);
+    if (walk_tiles) {
         int n = 0;
         CK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, (const void*)ompd_k_solve, PHASE_THREADS, dm.lds_tile));
         n = std::max(1, n);
         if (pc.wg_per_cu > 0) n = std::min(n, pc.wg_per_cu);
-        dm.grid_tile = std::max(1, std::min((int)tiles.size(), n * ctx->n_cu));
+        dm.grid_tile = std::max(1, std::min(walk_tiles, n * ctx->n_cu));
     }
-    dm.lds_level = align256(8 * (size_t)lv_nb);
-    if (dm.n_level) {
-        if (dm.lds_level > (size_t)ctx->lds_max)
-            return ompd_fail(OMPD_E_INVAL, "a CFG on the level schedule has more blocks than LDS holds");
-        int n = 0;
-        CK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_levels[PH_LATER], LEVEL_THREADS, dm.lds_level));
-        dm.grid_level = std::max(1, std::min(dm.n_level, std::max(1, n) * ctx->n_cu));
-    }
-    if (dm.n_level) dm.split = true;   // the per-tile kernel does not run level tiles
+    if (dm.n_level) dm.split = true;   // the per-tile kernel does not run strip tiles
+    if (!walk_tiles) return OMPD_OK;
     int pe = 1;
     CK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&pe, (const void*)ompd_k_post_ave, 64, 0));
-    dm.grid_edge = std::max(1, std::min((int)std::max<size_t>(sh.items.size(), tiles.size()), std::max(1, pe) * ctx->n_cu));
+    dm.grid_edge = std::max(1, std::min((int)std::max<size_t>(sh.items.size() - dm.n_tblock - dm.n_tedge, walk_tiles),
+                                        std::max(1, pe) * ctx->n_cu));
     return OMPD_OK;
 }
 
@@ -457,26 +539,33 @@ int ompd_plan_build(ompd_ctx* ctx, const ompd_cfg* cfgs, ompd_result* res, int32
 
     std::vector<ScratchOff> off(n);
     std::vector<size_t> base(n);
-    size_t total = 0;
-    int max_nb = 2;
-    for (int i = 0; i < n; ++i) {
-        base[i] = total;
-        total += ompd_cfg_scratch(cfgs[i], res[i], off[i]);
-        max_nb = std::max(max_nb, cfgs[i].n_blocks);
-    }
-    size_t counter_off = total;
-    total += 256;
     // default boundaries of every CFG, side by side (one upload)
     std::vector<size_t> boff(n);
-    size_t bnd_words = 0;
+    size_t bnd_words = 0, counter_off = 0, bnd_off = 0, total = 0;
+    int max_nb = 2;
     for (int i = 0; i < n; ++i) {
         boff[i] = bnd_words;
         bnd_words += 4 * (size_t)((cfgs[i].n_vars + 63) / 64);
+        max_nb = std::max(max_nb, cfgs[i].n_blocks);
     }
-    const size_t bnd_off = total;
-    total += (8 * bnd_words + 255) & ~(size_t)255;
+    // (a plan that does not fit with the room the strips like may still fit without)
+    hipError_t e = hipSuccess;
+    for (int rows : {ompd_strip_rows(cfgs, n), 0}) {
+        total = 0;
+        for (int i = 0; i < n; ++i) {
+            base[i] = total;
+            total += ompd_cfg_scratch(cfgs[i], res[i], off[i], rows);
+        }
+        counter_off = total;
+        total += 256;
+        bnd_off = total;
+        total += (8 * bnd_words + 255) & ~(size_t)255;
+        e = hipMalloc(&p->scratch, std::max<size_t>(total, 256));
+        if (e == hipSuccess) break;
+        p->scratch = nullptr;
+        (void)hipGetLastError();
+    }
     p->scratch_bytes = total;
-    hipError_t e = hipMalloc(&p->scratch, std::max<size_t>(total, 256));
     if (e != hipSuccess) {
         delete p;
         return ompd_fail(OMPD_E_NOMEM, std::string("scratch allocation: ") + hipGetErrorString(e));
@@ -493,9 +582,7 @@ int ompd_plan_build(ompd_ctx* ctx, const ompd_cfg* cfgs, ompd_result* res, int32
         if (e != hipSuccess) { ompd_plan_destroy(p); return ompd_fail(OMPD_E_DEVICE, hipGetErrorString(e)); }
     }
     p->max_nb = max_nb;
-    e = hipMalloc(&p->d_cfgs, sizeof(DevCfg) * std::max(n, 1));
-    if (e == hipSuccess && n > 0)
-        e = hipMemcpy(p->d_cfgs, p->h_cfgs.data(), sizeof(DevCfg) * n, hipMemcpyHostToDevice);
+    e = hipMalloc(&p->d_cfgs, sizeof(DevCfg) * std::max(n, 1));   // (filled by ompd_plan_retile)
     if (e != hipSuccess) { ompd_plan_destroy(p); return ompd_fail(OMPD_E_DEVICE, hipGetErrorString(e)); }
     p->h_info.assign((size_t)n * INFO_WORDS, 0);
     e = hipMalloc(&p->d_info, 4 * INFO_WORDS * (size_t)std::max(n, 1));
@@ -514,21 +601,15 @@ int ompd_plan_retile(ompd_plan* p, const PlanConfig& pc)
 {
     ompd_ctx* ctx = p->ctx;
     // the schedule of each CFG the plan's flags leave open: the bucket's choice, else the rule
-    if (!(p->flags & (OMPD_F_SCHED_LEVEL | OMPD_F_SCHED_WALK))) {
-        bool changed = false;
-        for (int i = 0; i < p->n; ++i) {
-            DevCfg& d = p->h_cfgs[i];
+    {
+        for (DevCfg& d : p->h_cfgs) {
+            if (p->flags & (OMPD_F_SCHED_LEVEL | OMPD_F_SCHED_WALK)) break;
             const int want = pc.bucket_sched[ompd_sched_bucket(d.nb)];
-            int sc = want < 0 ? ompd_default_sched(d.nb, d.nv) : want;
-            if (d.nb > OMPD_LEVEL_MAX_BLOCKS) sc = SCHED_WALK;
             d.sched_rule = want < 0;
-            if (d.sched != sc) { d.sched = sc; changed = true; }
+            if (want >= 0) d.sched = d.strip_ok ? want : SCHED_WALK;
         }
-        std::vector<int> before(p->n);
-        for (int i = 0; i < p->n; ++i) before[i] = p->h_cfgs[i].sched;
-        ompd_settle_sched(p->h_cfgs.data(), p->n, ctx->n_cu);
-        for (int i = 0; i < p->n; ++i) changed |= before[i] != p->h_cfgs[i].sched;
-        if (changed && p->d_cfgs)
+        ompd_settle_sched(p->h_cfgs.data(), p->n, ctx->n_cu, pc.split);
+        if (p->n && p->d_cfgs)
             CK(hipMemcpy(p->d_cfgs, p->h_cfgs.data(), sizeof(DevCfg) * p->n, hipMemcpyHostToDevice));
     }
     Shape sh;
@@ -536,7 +617,6 @@ int ompd_plan_retile(ompd_plan* p, const PlanConfig& pc)
     if (rc) return rc;
     p->cfg = pc;
     p->dims = sh.dims;
-    p->lds_prep = sh.lds_prep;
     p->h_tiles = sh.tiles;
     p->n_tiles = (int)sh.tiles.size();
     p->n_items = (int)sh.items.size();
@@ -552,13 +632,16 @@ int ompd_plan_retile(ompd_plan* p, const PlanConfig& pc)
     return OMPD_OK;
 }
 
-int ompd_launch_prep(const DevCfg* d_cfgs, int n, int32_t* d_counter, size_t lds, int ring_slots, hipStream_t s)
+int ompd_launch_prep(const DevCfg* d_cfgs, int n, int32_t* d_counter, const LaunchDims& dm, hipStream_t s)
 {
     if (n <= 0) return OMPD_OK;
-    hipLaunchKernelGGL(ompd_k_prep, dim3(n), dim3(256), lds, s, d_cfgs, n, d_counter, ring_slots);
+    if (dm.n_walk)
+        hipLaunchKernelGGL(ompd_k_prep, dim3(n), dim3(256), 0, s, d_cfgs, n, d_counter, dm.ring_slots);
+    if (dm.n_strip)
+        hipLaunchKernelGGL(ompd_k_sprep, dim3(n), dim3(256), dm.lds_prep, s, d_cfgs, n, (int)dm.lds_prep);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess)
-        return ompd_fail(OMPD_E_DEVICE, std::string("prep launch (lds ") + std::to_string(lds) + "): " +
+        return ompd_fail(OMPD_E_DEVICE, std::string("ingest launch (lds ") + std::to_string(dm.lds_prep) + "): " +
                                             hipGetErrorString(e));
     return OMPD_OK;
 }
@@ -567,10 +650,11 @@ int ompd_launch_solve(const DevCfg* d_cfgs, const Tile* d_tiles, int n_tiles, co
                       int32_t* d_counter, const LaunchDims& dm, hipStream_t s, hipEvent_t* after)
 {
     if (n_tiles <= 0) return OMPD_OK;
-    // the walk tiles, then the level tiles
-    const int n_level = dm.n_level;
-    n_tiles -= n_level;
-    const Tile* d_ltiles = d_tiles + n_tiles;
+    // the walk's tiles and items, then the strips'
+    n_tiles -= dm.n_level;
+    n_items -= dm.n_tblock + dm.n_tedge;
+    const Tile* d_strips = d_tiles + n_tiles;
+    const EdgeItem* d_titems = d_items + n_items;
     const int rs = dm.ring_slots, grid_edge = dm.grid_edge;
     int k = 0;
     auto mark = [&]() { if (after) (void)hipEventRecord(after[k], s); ++k; };
@@ -590,10 +674,6 @@ int ompd_launch_solve(const DevCfg* d_cfgs, const Tile* d_tiles, int n_tiles, co
         if (launch && n_tiles > 0) {
             void* args[] = {(void*)&d_cfgs, (void*)&d_tiles, (void*)&n_tiles, (void*)&d_counter, (void*)&rs};
             (void)hipLaunchKernel(k_phases[ph], dim3(dm.grid[ph]), dim3(PHASE_THREADS), args, dm.lds[ph], s);
-        }
-        if (launch && n_level > 0) {
-            void* args[] = {(void*)&d_cfgs, (void*)&d_ltiles, (void*)&n_level, (void*)&d_counter};
-            (void)hipLaunchKernel(k_levels[ph], dim3(dm.grid_level), dim3(LEVEL_THREADS), args, dm.lds_level, s);
         }
         mark();
     };
@@ -615,8 +695,29 @@ int ompd_launch_solve(const DevCfg* d_cfgs, const Tile* d_tiles, int n_tiles, co
     pass((const void*)ompd_k_post_live, dm.refine);
     phase(PH_AVF, true);
     pass((const void*)ompd_k_post_avf, true);
-    hipLaunchKernelGGL(ompd_k_varkind, dim3(grid_edge), dim3(64), 0, s, d_cfgs, d_tiles, n_tiles, d_counter);
+    if (n_tiles > 0) hipLaunchKernelGGL(ompd_k_varkind, dim3(grid_edge), dim3(64), 0, s, d_cfgs, d_tiles, n_tiles, d_counter);
     mark();
+    auto transpose = [&](const void* fn, int n) {
+        if (n > 0) {
+            void* args[] = {(void*)&d_cfgs, (void*)&d_titems};
+            (void)hipLaunchKernel(fn, dim3(n), dim3(256), args, 0, s);
+        }
+        mark();
+    };
+    auto strips = [&](const void* fn) {
+        for (int b = 0; b < dm.n_buckets; ++b) {
+            const LaunchDims::Bucket& k = dm.bucket[b];
+            const Tile* t = d_strips + k.first;
+            void* args[] = {(void*)&d_cfgs, (void*)&t};
+            (void)hipLaunchKernel(fn, dim3(k.n), dim3(64 * k.waves), args, k.lds, s);
+        }
+        mark();
+    };
+    transpose((const void*)ompd_k_tin, dm.n_tblock);
+    strips((const void*)ompd_k_strip_a);
+    transpose((const void*)ompd_k_tmid, dm.n_tblock);
+    strips((const void*)ompd_k_strip_b);
+    transpose((const void*)ompd_k_tout, dm.n_tblock + dm.n_tedge);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess)
         return ompd_fail(OMPD_E_DEVICE, std::string("solve launch (ring slots ") + std::to_string(rs) + "): " +
@@ -626,7 +727,7 @@ int ompd_launch_solve(const DevCfg* d_cfgs, const Tile* d_tiles, int n_tiles, co
 
 static int launch_prep(ompd_plan* p, hipStream_t s)
 {
-    return ompd_launch_prep((const DevCfg*)p->d_cfgs, p->n, p->d_counter, p->lds_prep, p->dims.ring_slots, s);
+    return ompd_launch_prep((const DevCfg*)p->d_cfgs, p->n, p->d_counter, p->dims, s);
 }
 
 static int launch_solve(ompd_plan* p, hipStream_t s)
@@ -865,19 +966,19 @@ extern "C" int ompd_plan_describe(ompd_plan* p, char* buf, int32_t len)
     long lanes = 0;
     for (size_t i = 0; i + p->dims.n_level < p->h_tiles.size(); ++i) lanes += p->h_tiles[i].nw;
     int level_cfgs = 0;
-    for (const DevCfg& d : p->h_cfgs) level_cfgs += d.sched == SCHED_LEVEL;
+    for (const DevCfg& d : p->h_cfgs) level_cfgs += d.spread;
     snprintf(buf, len,
              "{\"cfgs\": %d, \"tiles\": %d, \"words\": %ld, \"ring_slots\": %d, \"split\": %d, \"grid_tile\": %d, "
              "\"grid_phases\": [%d, %d, %d, %d, %d], "
              "\"lds_bytes\": %zu, \"wg_per_cu\": %d, \"graph\": %d, \"graph_captured\": %d, "
              "\"scratch_bytes\": %zu, \"bucket_sched\": [%d, %d, %d, %d, %d], \"level_cfgs\": %d, "
-             "\"level_tiles\": %d, \"lds_level\": %zu}",
+             "\"level_tiles\": %d, \"lds_level\": %zu, \"strip_launches\": %d}",
              p->n, p->n_tiles - p->dims.n_level, lanes, p->dims.ring_slots, (int)p->dims.split, p->dims.grid_tile,
              p->dims.grid[0], p->dims.grid[1], p->dims.grid[2],
              p->dims.grid[3], p->dims.grid[4], p->cfg.lds_bytes, p->cfg.wg_per_cu,
              p->cfg.use_graph ? 1 : 0, p->gx_solve ? 1 : 0, p->scratch_bytes, p->cfg.bucket_sched[0],
              p->cfg.bucket_sched[1], p->cfg.bucket_sched[2], p->cfg.bucket_sched[3], p->cfg.bucket_sched[4],
-             level_cfgs, p->dims.n_level, p->dims.lds_level);
+             level_cfgs, p->dims.n_level, p->dims.n_buckets ? p->dims.bucket[0].lds : 0, p->dims.n_buckets);
     return OMPD_OK;
 }
 
@@ -935,7 +1036,7 @@ extern "C" int ompd_plan_autotune(ompd_plan* p, void* stream, int32_t trials, fl
         for (const DevCfg& d : p->h_cfgs) {
             const int b = ompd_sched_bucket(d.nb);
             ++count[b];
-            small[b] += d.nb <= OMPD_LEVEL_MAX_BLOCKS;
+            small[b] += d.strip_ok;
         }
         for (int b = 0; b < OMPD_SCHED_BUCKETS; ++b) {
             if (!count[b]) continue;
@@ -960,7 +1061,7 @@ extern "C" int ompd_plan_autotune(ompd_plan* p, void* stream, int32_t trials, fl
         for (int b = 0; b < OMPD_SCHED_BUCKETS; ++b) rule.bucket_sched[b] = -1;
         float t_pick = 0, t_rule = 0;
         if (time_config(p, base, s, trials, t_pick) == OMPD_OK && time_config(p, rule, s, trials, t_rule) == OMPD_OK &&
-            t_rule < t_pick)
+            t_rule < 0.98f * t_pick)
             base = rule;
     }
     // 2. the launch configuration of the whole plan with those schedules
@@ -1203,39 +1304,47 @@ extern "C" int ompd_analyze_batch_noalloc(ompd_ctx* ctx, const ompd_cfg* cfgs, o
     if (flags & OMPD_F_TILE_KERNEL) pc.split = false;
     if (const uint32_t r = (flags >> 8) & 7u) pc.lds_bytes = (size_t)(4u << r) * STATE_BYTES;
     // layout of the static scratch: each CFG's solver scratch, the work counters, the default
-    // boundaries, then the launch tables (descriptors, tiles, pass items) and the gathered
-    // status words
+    // boundaries, then the launch tables (descriptors, tiles, items) and the gathered status words;
+    // a batch whose strip tables do not fit takes the walk
     char* S = ctx->static_scratch;
     std::vector<ScratchOff> off(n);
     std::vector<size_t> base(n), boff(n);
-    size_t total = 0, bnd_words = 0;
-    for (int i = 0; i < n; ++i) {
-        base[i] = total;
-        total += ompd_cfg_scratch(cfgs[i], res[i], off[i]);
-        boff[i] = bnd_words;
-        bnd_words += 4 * (size_t)((cfgs[i].n_vars + 63) / 64);
-    }
-    const size_t counter_off = total;
-    total += 256;
-    const size_t bnd_off = total;
-    total += align256(8 * bnd_words);
-    std::vector<uint64_t> bnd(std::max<size_t>(bnd_words, 1), 0);
     std::vector<DevCfg> h(n);
-    for (int i = 0; i < n; ++i)
-        ompd_fill_devcfg(cfgs[i], res[i], S + base[i], off[i], flags, ctx->wait_ticks, h[i], bnd.data() + boff[i],
-                         (uint64_t*)(S + bnd_off) + boff[i]);
-    ompd_settle_sched(h.data(), n, ctx->n_cu);
+    std::vector<uint64_t> bnd;
     Shape sh;
-    int rc = ompd_make_shape(ctx, h, pc, sh);
-    if (rc) return rc;
-    const size_t cfg_off = total;
-    total += align256(sizeof(DevCfg) * n);
-    const size_t tile_off = total;
-    total += align256(sizeof(Tile) * std::max<size_t>(sh.tiles.size(), 1));
-    const size_t item_off = total;
-    total += align256(sizeof(EdgeItem) * std::max<size_t>(sh.items.size(), 1));
-    const size_t info_off = total;
-    total += align256(4 * INFO_WORDS * (size_t)n);
+    int rc = OMPD_OK;
+    size_t total = 0, bnd_words = 0, counter_off = 0, bnd_off = 0, cfg_off = 0, tile_off = 0, item_off = 0, info_off = 0;
+    const int rows = ompd_strip_rows(cfgs, n);
+    for (uint32_t walk : {0u, OMPD_F_SCHED_WALK}) {
+        total = bnd_words = 0;
+        for (int i = 0; i < n; ++i) {
+            base[i] = total;
+            total += ompd_cfg_scratch(cfgs[i], res[i], off[i], walk ? 0 : rows);
+            boff[i] = bnd_words;
+            bnd_words += 4 * (size_t)((cfgs[i].n_vars + 63) / 64);
+        }
+        counter_off = total;
+        total += 256;
+        bnd_off = total;
+        total += align256(8 * bnd_words);
+        bnd.assign(std::max<size_t>(bnd_words, 1), 0);
+        for (int i = 0; i < n; ++i)
+            ompd_fill_devcfg(cfgs[i], res[i], S + base[i], off[i], flags | walk, ctx->wait_ticks, h[i],
+                             bnd.data() + boff[i], (uint64_t*)(S + bnd_off) + boff[i]);
+        ompd_settle_sched(h.data(), n, ctx->n_cu, pc.split);
+        sh = Shape();
+        rc = ompd_make_shape(ctx, h, pc, sh);
+        if (rc) return rc;
+        cfg_off = total;
+        total += align256(sizeof(DevCfg) * n);
+        tile_off = total;
+        total += align256(sizeof(Tile) * std::max<size_t>(sh.tiles.size(), 1));
+        item_off = total;
+        total += align256(sizeof(EdgeItem) * std::max<size_t>(sh.items.size(), 1));
+        info_off = total;
+        total += align256(4 * INFO_WORDS * (size_t)n);
+        if (total <= OMPD_STATIC_SCRATCH_BYTES || !sh.dims.n_strip) break;
+    }
     if (total > OMPD_STATIC_SCRATCH_BYTES) {
         char buf[200];
         snprintf(buf, sizeof buf, "noalloc: the batch needs %zu bytes of scratch, the static scratch holds %zu",
@@ -1252,7 +1361,7 @@ extern "C" int ompd_analyze_batch_noalloc(ompd_ctx* ctx, const ompd_cfg* cfgs, o
                           s));
     const DevCfg* dc = (const DevCfg*)(S + cfg_off);
     int32_t* counter = (int32_t*)(S + counter_off);
-    rc = ompd_launch_prep(dc, n, counter, sh.lds_prep, sh.dims.ring_slots, s);
+    rc = ompd_launch_prep(dc, n, counter, sh.dims, s);
     if (rc == OMPD_OK)
         rc = ompd_launch_solve(dc, (const Tile*)(S + tile_off), (int)sh.tiles.size(), (const EdgeItem*)(S + item_off),
                                (int)sh.items.size(), counter, sh.dims, s);

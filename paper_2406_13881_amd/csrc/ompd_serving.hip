@@ -140,6 +140,8 @@ static void launcher_main(ServingState* S)
             Req* r = st->reqs[i];
             ompd_fill_devcfg(r->dcfg, r->dres, S->dev_base + r->dev_off + r->scratch_off, r->so, r->flags,
                              S->ctx->wait_ticks, h[i], nullptr);
+            // (the device holds every output; only what the caller asked for is written)
+            h[i].want = ompd_want(*r->user) | (h[i].call ? WANT_NU_H | WANT_NU_D : 0);
         }
         ompd_settle_sched(h.data(), k, S->ctx->n_cu);
         PlanConfig pc;
@@ -173,7 +175,7 @@ static void launcher_main(ServingState* S)
                 e = hipMemcpyAsync(dtab, pin, cfg_bytes + tile_bytes, hipMemcpyHostToDevice, s);
             int32_t* counter = (int32_t*)(dtab + cfg_bytes + tile_bytes);
             if (e != hipSuccess) rc = OMPD_E_DEVICE;
-            if (rc == OMPD_OK) rc = ompd_launch_prep((const DevCfg*)dtab, k, counter, sh.lds_prep, sh.dims.ring_slots, s);
+            if (rc == OMPD_OK) rc = ompd_launch_prep((const DevCfg*)dtab, k, counter, sh.dims, s);
             if (rc == OMPD_OK)
                 rc = ompd_launch_solve((const DevCfg*)dtab, (const Tile*)(dtab + cfg_bytes), (int)tiles.size(),
                                        (const EdgeItem*)(dtab + cfg_bytes + (tile_bytes - item_bytes)),
@@ -364,15 +366,23 @@ extern "C" int ompd_submit(ompd_ctx* ctx, const ompd_cfg* cfg, ompd_result* res,
     full.var_kind = (uint8_t*)1; full.after_dev = (uint8_t*)1; full.before_dev = (uint8_t*)1;
     full.fp_clause = (uint64_t*)1;
     r->scratch_off = off;
-    off += ompd_cfg_scratch(g, full, r->so);
-    r->dev_bytes = off;
+    r->dev_bytes = off + ompd_cfg_scratch(g, full, r->so, 1);
     r->pin_bytes = r->in_bytes;
     {
-        // its share of a step's launch tables: descriptor, tiles, pass items, status words
-        const size_t tiles = (size_t)tiles_of((int)wd) + 2 * wd + 1;   // walk tiles, level tiles
-        const size_t items = wd ? ((wd + PASS_WORDS - 1) / PASS_WORDS) * ((nb + 63) / 64) : 0;
-        r->tab_bytes = ompd_pool::request_table_bytes(tiles, items, sizeof(DevCfg), sizeof(Tile), sizeof(EdgeItem),
-                                                      4 * INFO_WORDS);
+        // its share of a step's launch tables: descriptor, tiles, items, status words (a request
+        // whose strip tables do not fit takes the walk)
+        auto bytes = [&](bool strip) {
+            const size_t tiles = std::max((size_t)tiles_of((int)wd), strip ? wd + 1 : 0);
+            const size_t passes = wd ? ((wd + PASS_WORDS - 1) / PASS_WORDS) * ((nb + 63) / 64) : 0;
+            return ompd_pool::request_table_bytes(tiles, std::max(passes, strip ? ompd_transpose_items(nb, ne, wd) : 0),
+                                                  sizeof(DevCfg), sizeof(Tile), sizeof(EdgeItem), 4 * INFO_WORDS);
+        };
+        r->tab_bytes = bytes(r->so.strip);
+        if (r->so.strip && r->tab_bytes + ompd_pool::TABLE_SLACK > ServingState::TAB_REGION) {
+            r->dev_bytes = off + ompd_cfg_scratch(g, full, r->so, 0);
+            r->so.strip = false;
+            r->tab_bytes = bytes(false);
+        }
         if (r->tab_bytes + ompd_pool::TABLE_SLACK > ServingState::TAB_REGION) {
             delete r;
             return ompd_fail(OMPD_E_INVAL, "serving: request too large for a step's launch tables");
@@ -381,7 +391,13 @@ extern "C" int ompd_submit(ompd_ctx* ctx, const ompd_cfg* cfg, ompd_result* res,
     {
         std::lock_guard<std::mutex> lk(S->mu);
         if (S->reqs.size() >= S->max_reqs) { delete r; return ompd_fail(OMPD_E_BUSY, "serving: too many requests"); }
-        if (!S->dev.alloc(r->dev_bytes, r->dev_off)) {
+        bool placed = S->dev.alloc(r->dev_bytes, r->dev_off);
+        if (!placed && r->so.strip) {
+            // the walk needs less scratch than the strips
+            r->dev_bytes = off + ompd_cfg_scratch(g, full, r->so, 0);
+            placed = S->dev.alloc(r->dev_bytes, r->dev_off);
+        }
+        if (!placed) {
             delete r;
             return ompd_fail(OMPD_E_BUSY, "serving: device-memory budget full");
         }

@@ -1,0 +1,79 @@
+"""GPU parity of the strips with the oracle at the edges of their shapes: one to four words per
+strip, CFGs on both sides of each wavefront count, blocks with fewer, as many and more edges than a
+row of 16 lanes holds, long chains (a level per block) and wide levels, in launches that leave the
+GPU idle and in launches that fill it, with and without a call's and a caller's options."""
+
+import numpy as np
+import pytest
+
+import oracle
+import synth
+
+pytestmark = pytest.mark.gpu
+
+KEYS = ("nu_h", "nu_d", "ave_h", "ave_d", "avf_h", "avf_d", "ins_entry_h", "ins_entry_d",
+        "ins_edge_h", "ins_edge_d", "var_kind", "after_dev", "before_dev")
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    import paper_2406_13881_amd as ompd
+    c = ompd.Context(0)
+    yield c
+    c.close()
+
+
+def _blocks(rng, n, n_vars):
+    out = [(0, [], [])]
+    for _ in range(n):
+        out.append((int(rng.random() < 0.4), sorted(set(rng.integers(0, n_vars, 5).tolist())) if n_vars else [],
+                    sorted(set(rng.integers(0, n_vars, 2).tolist())) if n_vars else []))
+    return out + [(0, [], [])]
+
+
+def _fan(n, n_vars, seed):
+    """A switch of n cases in a loop, so that two blocks have n edges and one has a BACK edge."""
+    rng = np.random.default_rng(seed)
+    join, ex = n + 2, n + 3
+    edges = [(0, 1, 2)] + [(1, 2 + k, 0) for k in range(n)] + [(2 + k, join, 0) for k in range(n)]
+    return synth.from_edges(_blocks(rng, n + 2, n_vars), edges + [(join, 1, 1), (join, ex, 0)], n_vars)[0]
+
+
+def _chain(n, n_vars, seed):
+    """n blocks in a row, a loop around every third pair: a level per block, a BACK edge at each distance."""
+    rng = np.random.default_rng(seed)
+    edges = [(b, b + 1, 2 if b % 3 == 0 and b + 2 <= n else 0) for b in range(n + 1)]
+    edges += [(b + 2, b + 1, 1) for b in range(0, n - 1, 3)] + ([(n, 1, 1)] if n > 3 else [])
+    return synth.from_edges(_blocks(rng, n, n_vars), edges, n_vars)[0]
+
+
+def _cfgs(n_vars):
+    out = [_fan(n, n_vars, 100 + n) for n in (1, 2, 15, 16, 17, 31, 33, 64, 65)]
+    out += [_chain(n, n_vars, 200 + n) for n in (1, 6, 30, 31, 62, 63, 126, 198, 199, 254, 399)]
+    out += [synth.permute_blocks(_chain(150, n_vars, 7), 8)[0], synth.random_dag(9, 90, n_vars, p_loop_entry=0.3)]
+    return out
+
+
+@pytest.mark.parametrize("copies", [1, 60])
+@pytest.mark.parametrize("n_vars", [0, 1, 64, 65, 192, 193, 257, 449])
+def test_strip_edges(ctx, n_vars, copies):
+    cfgs = _cfgs(n_vars)
+    want = [oracle.solve(c) for c in cfgs]
+    print("strips: %d variables, %d copies" % (n_vars, copies), flush=True)
+    got = ctx.analyze_batch(cfgs * copies)
+    for i in range(len(cfgs) * copies):
+        for k in KEYS:
+            g, r = np.asarray(got[i][k]), np.asarray(want[i % len(cfgs)][k])
+            assert np.array_equal(g, r.reshape(g.shape)), (i % len(cfgs), k)
+
+
+@pytest.mark.parametrize("n_vars", [65, 193])
+def test_strip_alone(ctx, n_vars):
+    """Each CFG in a launch of its own (a row of lanes per word), also with a cap that its rounds stay under."""
+    for i, cfg in enumerate(_cfgs(n_vars)):
+        want = oracle.solve(cfg)
+        for flags in (0, 1000 << 16):
+            got = ctx.analyze_batch([cfg], flags=flags)[0]
+            for k in KEYS:
+                g = np.asarray(got[k])
+                assert np.array_equal(g, np.asarray(want[k]).reshape(g.shape)), (i, flags, k)
