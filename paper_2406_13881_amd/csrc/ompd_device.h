@@ -104,6 +104,7 @@ struct DevCfg {
     // word of reachability facts.  Block arrays [units][nb] and edge arrays [words][ne + 1] hold
     // pairs of words, host and device.
     int32_t units;              // units per strip workgroup (1, 2 or 4)
+    int32_t by_size;            // (of descriptor i) the CFG that is i-th by size, largest first
     int32_t spread;             // the launch leaves compute units idle: fewer blocks per wavefront
     int32_t waves;              // wavefronts per strip workgroup
     int32_t strip_ok;           // host side: the strips can hold the CFG
@@ -154,12 +155,10 @@ constexpr int STRIP_MAX_BLOCKS = 32000;
 // units of a strip: as many as a pass of narrow levels fills; a large CFG has wider levels, which
 // fill a pass with fewer units
 constexpr int strip_units(int nb, int wd) { return nb >= 10000 || wd < 1 ? 1 : wd < 3 ? 2 : 4; }
-// LDS bytes of the ingest kernel's peel: 16-bit successor CSR, degrees, order (0: it does not fit
-// 16 bits, and the peel runs in global memory)
-constexpr size_t strip_prep_lds(int nb, int ne)
-{
-    return ne >= 65536 ? 0 : 2 * ((size_t)((nb + 2) & ~1) + ((ne + 1) & ~1) + 2 * (size_t)((nb + 1) & ~1));
-}
+// LDS bytes of the ingest kernel's peel: a count and record per block, and with ne the lists
+// of blocks with more than two successors (which it else reads from the CSR; where the records do not
+// fit either, the peel runs in global memory)
+constexpr size_t strip_prep_lds(int nb, int ne) { return 8 * ((size_t)nb + 1) + 4 * ((ne + 1) / 2); }
 
 // How a CFG's phases visit its blocks: one block after another along the
 // block order (the walk), or a level at a time with the blocks of a level in

@@ -44,6 +44,7 @@ struct LaunchDims {
     int n_strip = 0;             // CFGs on it
     int n_level = 0;             // strip tiles: the last n_level entries of the tile array
     int n_tblock = 0, n_tedge = 0;   // transpose items: the last entries of the item array, blocks first
+    int prep_threads = 256;      // threads of the strip ingest
     size_t lds_prep = 0;         // LDS of the strip ingest (the largest CFG's peel that fits)
     // launches of each strip kernel: consecutive strip tiles whose workgroups have the same number
     // of wavefronts

@@ -287,6 +287,10 @@ int ompd_strip_rows(const ompd_cfg* g, int n)
 
 void ompd_settle_sched(DevCfg* h, int n, int n_cu, bool split)
 {
+    std::vector<int> order(n);
+    for (int i = 0; i < n; ++i) order[i] = i;
+    std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return h[a].nb > h[b].nb; });
+    for (int i = 0; i < n; ++i) h[i].by_size = order[i];
     int64_t strips = 0;
     for (int i = 0; i < n; ++i) {
         DevCfg& d = h[i];
@@ -448,6 +452,7 @@ int ompd_make_shape(ompd_ctx* ctx, const std::vector<DevCfg>& cfgs, const PlanCo
         }
     }
     dm.n_level = (int)tiles.size() - walk_tiles;
+    int max_nb = 0;
     // pass items: runs of up to PASS_WORDS words (the passes need no LDS, so a full wavefront of
     // words each), 64-block chunks, longest CFGs first
     {
@@ -463,6 +468,7 @@ int ompd_make_shape(ompd_ctx* ctx, const std::vector<DevCfg>& cfgs, const PlanCo
                 for (int b0 = 0; b0 < cfgs[i].nb; b0 += 64) sh.items.push_back(EdgeItem{i, s0, s1 - s0, b0});
             }
         }
+        max_nb = order.empty() ? 0 : cfgs[order[0]].nb;
         // transpose items of the strip CFGs: block chunks, then record chunks
         dm.n_tblock = dm.n_tedge = 0;
         dm.lds_prep = 0;
@@ -470,8 +476,11 @@ int ompd_make_shape(ompd_ctx* ctx, const std::vector<DevCfg>& cfgs, const PlanCo
             for (int i : order) {
                 const DevCfg& d = cfgs[i];
                 if (d.sched != SCHED_LEVEL || !in_plan(i)) continue;
-                const size_t pl = strip_prep_lds(d.nb, d.ne);
-                if (pl <= (size_t)ctx->lds_max) dm.lds_prep = std::max(dm.lds_prep, pl);
+                for (size_t pl : {strip_prep_lds(d.nb, d.ne), strip_prep_lds(d.nb, 0)})
+                    if (pl <= (size_t)ctx->lds_max) {
+                        dm.lds_prep = std::max(dm.lds_prep, pl);
+                        break;
+                    }
                 if (edges && d.wd == 0) continue;
                 const int rows = edges ? strip_records(d.ne) : d.nb;
                 for (int s0 = 0; s0 < std::max(d.wd, 1); s0 += STRIP_T_WORDS)
@@ -481,6 +490,10 @@ int ompd_make_shape(ompd_ctx* ctx, const std::vector<DevCfg>& cfgs, const PlanCo
                     }
             }
     }
+    // Threads of the strip ingest: what follows the peel is by block and by level, each a few dependent
+    // loads from L2 (8002 blocks: 570 us of 256 threads, 220 us of 1024); a small CFG has no work for more
+    // than 256, and a workgroup's barriers and start cost more with them.
+    dm.prep_threads = max_nb < 200 ? 256 : max_nb < 1000 ? 512 : 1024;
     // result ring: a power of two of STATE_BYTES slots in [8, 64], as large as every phase's LDS allows
     const size_t want = pc.lds_bytes ? pc.lds_bytes : RING_BYTES_DEFAULT;
     int rs = 8;
@@ -638,7 +651,7 @@ int ompd_launch_prep(const DevCfg* d_cfgs, int n, int32_t* d_counter, const Laun
     if (dm.n_walk)
         hipLaunchKernelGGL(ompd_k_prep, dim3(n), dim3(256), 0, s, d_cfgs, n, d_counter, dm.ring_slots);
     if (dm.n_strip)
-        hipLaunchKernelGGL(ompd_k_sprep, dim3(n), dim3(256), dm.lds_prep, s, d_cfgs, n, (int)dm.lds_prep);
+        hipLaunchKernelGGL(ompd_k_sprep, dim3(n), dim3(dm.prep_threads), dm.lds_prep, s, d_cfgs, n, (int)dm.lds_prep);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess)
         return ompd_fail(OMPD_E_DEVICE, std::string("ingest launch (lds ") + std::to_string(dm.lds_prep) + "): " +
