@@ -51,6 +51,7 @@ struct LaunchDims {
     struct Bucket { int first, n, waves; size_t lds; };
     static constexpr int MAX_BUCKETS = 6;
     int n_buckets = 0;
+    bool first_half = false;     // the strips stop after eager validity
     Bucket bucket[MAX_BUCKETS] = {};
 };
 
@@ -64,6 +65,7 @@ struct PlanConfig {
     // SCHED_LEVEL; CFGs whose schedule the plan's flags name keep it
     int bucket_sched[OMPD_SCHED_BUCKETS] = {-1, -1, -1, -1, -1};
     int only_bucket = -1;   // autotuning: solve only the CFGs of this bucket (-1: all)
+    bool first_half = false; // the caller reads next use and eager validity only (strips stop there)
 };
 // Size bucket of a CFG for the schedule choice: blocks below 256, 1,024, 4,096, 16,384, or more.
 inline int ompd_sched_bucket(int n_blocks)

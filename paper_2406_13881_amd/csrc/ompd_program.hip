@@ -793,12 +793,14 @@ int upload_items(const std::vector<T>& v, void (*k)(const T*, int), int threads,
     return OMPD_OK;
 }
 
-// Solve a batch of CFGs given by device-pointer descriptors.
-int run_batch(Prog& G, std::vector<ompd_cfg>& cfgs, std::vector<ompd_result>& res, uint32_t flags)
+// Solve a batch of CFGs given by device-pointer descriptors.  first_half: next use and eager validity
+// are all that is read of it (with a sweep cap the rest runs too, since it may be what reaches it).
+int run_batch(Prog& G, std::vector<ompd_cfg>& cfgs, std::vector<ompd_result>& res, uint32_t flags, bool first_half)
 {
     if (cfgs.empty()) return OMPD_OK;
     PlanConfig pc;
     pc.use_graph = false;   // one-shot plans: capturing a graph would not be replayed
+    pc.first_half = first_half && !(G.flags >> 16);
     ompd_plan* plan = nullptr;
     int rc = ompd_plan_build(G.ctx, cfgs.data(), res.data(), (int32_t)cfgs.size(), flags | OMPD_F_DEVICE_PTRS | G.flags,
                              pc, &plan);
@@ -1128,7 +1130,7 @@ int evaluate(Prog& G, const std::vector<int>& procs, int rows, int& changed)
             res.push_back(r);
         }
     }
-    rc = run_batch(G, cfgs, res, OMPD_F_SUMMARY);
+    rc = run_batch(G, cfgs, res, OMPD_F_SUMMARY, true);
     if (rc) return rc;
     std::vector<SumItem> si;
     for (int p : procs) {
@@ -1260,8 +1262,9 @@ int summarize(Prog& G)
 }
 
 // Solve a set of contexts with their current boundaries and call tables
-// (summary mode: a non-root context may leave a global valid nowhere).
-int solve_contexts(Prog& G, const std::vector<int>& xs)
+// (summary mode: a non-root context may leave a global valid nowhere).  live: for the exit-liveness
+// system, which reads their next use; the entry-validity system then solves every context anew.
+int solve_contexts(Prog& G, const std::vector<int>& xs, bool live)
 {
     const Structure& st = G.st;
     std::vector<CallTabItem> ct;
@@ -1287,7 +1290,7 @@ int solve_contexts(Prog& G, const std::vector<int>& xs)
         cfgs.push_back(d);
         res.push_back(r);
     }
-    rc = run_batch(G, cfgs, res, OMPD_F_SUMMARY);
+    rc = run_batch(G, cfgs, res, OMPD_F_SUMMARY, live);
     if (rc) return rc;
     for (size_t i = 0; i < xs.size(); ++i) memcpy(&G.sweeps[(size_t)xs[i] * 6], res[i].sweeps, sizeof res[i].sweeps);
     return OMPD_OK;
@@ -1311,7 +1314,7 @@ int boundary_system(Prog& G, int live)
     std::vector<char> is_t(nctx, 0);
     std::vector<int32_t> hc(nctx);
     while (!dirty.empty()) {
-        int rc = solve_contexts(G, dirty);
+        int rc = solve_contexts(G, dirty, live);
         if (rc) return rc;
         std::vector<int> touched;
         std::vector<ContribItem> cb;

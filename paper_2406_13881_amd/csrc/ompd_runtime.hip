@@ -305,6 +305,7 @@ void ompd_settle_sched(DevCfg* h, int n, int n_cu, bool split)
     // 96 CFGs (242 strips) 1415 / 1795 / 3020 / 4420; 1024 CFGs (4266 strips) 16.9 / 12.3 / 12.1 /
     // 12.5 ms; 2048 CFGs of about 60 blocks (2377 strips) 1170 / 841 / 493 / 493.
     const bool idle = strips <= n_cu;
+    int most = 1;
     const int busy_per = (int)std::min<int64_t>(200, 32 * strips / std::max(n_cu, 1));
     for (int i = 0; i < n; ++i) {
         DevCfg& d = h[i];
@@ -314,7 +315,13 @@ void ompd_settle_sched(DevCfg* h, int n, int n_cu, bool split)
         d.waves = 1;
         if (d.sweep_cap == 0)
             while (d.waves < STRIP_MAX_WAVES && d.nb > per * d.waves) d.waves *= 2;
+        if (d.sched == SCHED_LEVEL && d.sweep_cap == 0) most = std::max(most, d.waves);
     }
+    // With room for every strip one launch holds them all: launches for two sizes would take the
+    // longest of each in turn, and a small CFG with more wavefronts than it likes still ends first.
+    if (idle)
+        for (int i = 0; i < n; ++i)
+            if (h[i].sched == SCHED_LEVEL && h[i].sweep_cap == 0) h[i].waves = most;
 }
 
 // Fill the kernels' descriptor of one CFG whose scratch starts at `base`.
@@ -452,6 +459,7 @@ int ompd_make_shape(ompd_ctx* ctx, const std::vector<DevCfg>& cfgs, const PlanCo
         }
     }
     dm.n_level = (int)tiles.size() - walk_tiles;
+    dm.first_half = pc.first_half;
     int max_nb = 0;
     // pass items: runs of up to PASS_WORDS words (the passes need no LDS, so a full wavefront of
     // words each), 64-block chunks, longest CFGs first
@@ -729,8 +737,9 @@ int ompd_launch_solve(const DevCfg* d_cfgs, const Tile* d_tiles, int n_tiles, co
     transpose((const void*)ompd_k_tin, dm.n_tblock);
     strips((const void*)ompd_k_strip_a);
     transpose((const void*)ompd_k_tmid, dm.n_tblock);
-    strips((const void*)ompd_k_strip_b);
-    transpose((const void*)ompd_k_tout, dm.n_tblock + dm.n_tedge);
+    if (!dm.first_half) strips((const void*)ompd_k_strip_b);
+    else mark();
+    transpose((const void*)ompd_k_tout, dm.first_half ? 0 : dm.n_tblock + dm.n_tedge);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess)
         return ompd_fail(OMPD_E_DEVICE, std::string("solve launch (ring slots ") + std::to_string(rs) + "): " +
