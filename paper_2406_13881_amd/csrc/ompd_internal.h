@@ -154,6 +154,10 @@ int ompd_plan_build(ompd_ctx* ctx, const ompd_cfg* cfgs, ompd_result* res, int32
                     const PlanConfig& pc, ompd_plan** out);
 int ompd_plan_retile(ompd_plan* p, const PlanConfig& pc);
 int ompd_plan_run_locked(ompd_plan* p, hipStream_t s);
+// Run a plan again whose last run succeeded and whose CFGs have kept their edges, spaces, calls and
+// the variables no block may touch (rows, boundaries and summaries may have changed): the ingest's
+// tables still hold.
+int ompd_plan_rerun_locked(ompd_plan* p, hipStream_t s);
 int ompd_plan_collect(ompd_plan* p, int32_t* per_cfg);
 int ompd_batch_locked(ompd_ctx* ctx, const ompd_cfg* cfgs, ompd_result* res, int32_t n, uint32_t flags,
                       hipStream_t s);

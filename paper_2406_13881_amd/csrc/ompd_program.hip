@@ -38,12 +38,14 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <deque>
 #include <cstdio>
 #include <cstring>
 #include <deque>
 #include <map>
 #include <mutex>
 #include <string>
+#include <deque>
 #include <vector>
 
 #include "../../include/ompd.h"
@@ -778,38 +780,92 @@ struct Prog {
     std::vector<uint64_t*> e_out;            // [4][4][nb][wd]
     char* arena_items = nullptr;             // staging of kernel work items
     std::vector<char> cap_valid;             // per context: a cap from the previous outer round exists
-    ~Prog() { if (arena) (void)hipFree(arena); }
+    // pinned staging: inputs on their way in, work items, results on their way out
+    static constexpr size_t STAGE = (size_t)64 << 20;
+    char* stage = nullptr;
+    size_t stage_used = 0;
+    // Plans of the batches solved so far (the fixed points solve the same sets of procedures and
+    // contexts again and again, with the same buffers): what a batch costs besides its kernels is
+    // building its plan and ingesting its CFGs.  Bounded; the oldest go first.
+    struct Kept { std::vector<int> key; ompd_plan* plan; size_t bytes; };
+    static constexpr size_t KEPT_BYTES = (size_t)1 << 30;
+    std::deque<Kept> kept;
+    size_t kept_bytes = 0;
+    void drop_oldest()
+    {
+        kept_bytes -= kept.front().bytes;
+        ompd_plan_destroy(kept.front().plan);
+        kept.pop_front();
+    }
+    ~Prog()
+    {
+        while (!kept.empty()) drop_oldest();
+        if (stage) (void)hipHostFree(stage);
+        if (arena) (void)hipFree(arena);
+    }
 };
 
+// Launch a kernel over work items.  They go through the pinned staging buffer, so the host need not
+// wait; the stream orders the uses of the device copy.
 template <typename T>
-int upload_items(const std::vector<T>& v, void (*k)(const T*, int), int threads, hipStream_t s, char* scratch)
+int upload_items(Prog& G, const std::vector<T>& v, void (*k)(const T*, int), int threads)
 {
     if (v.empty()) return OMPD_OK;
-    CK(hipMemcpyAsync(scratch, v.data(), sizeof(T) * v.size(), hipMemcpyHostToDevice, s));
+    const size_t bytes = sizeof(T) * v.size();
+    if (bytes <= Prog::STAGE) {
+        if (G.stage_used + bytes > Prog::STAGE) {
+            CK(hipStreamSynchronize(G.s));
+            G.stage_used = 0;
+        }
+        char* at = G.stage + G.stage_used;
+        G.stage_used += a256(bytes);
+        memcpy(at, v.data(), bytes);
+        CK(hipMemcpyAsync(G.arena_items, at, bytes, hipMemcpyHostToDevice, G.s));
+    } else
+        CK(hipMemcpyAsync(G.arena_items, v.data(), bytes, hipMemcpyHostToDevice, G.s));
     const int grid = (int)std::min<size_t>(v.size(), 4096);
-    hipLaunchKernelGGL(k, dim3(grid), dim3(threads), 0, s, (const T*)scratch, (int)v.size());
+    hipLaunchKernelGGL(k, dim3(grid), dim3(threads), 0, G.s, (const T*)G.arena_items, (int)v.size());
     CK(hipGetLastError());
-    CK(hipStreamSynchronize(s));
+    if (bytes > Prog::STAGE) CK(hipStreamSynchronize(G.s));
     return OMPD_OK;
 }
 
-// Solve a batch of CFGs given by device-pointer descriptors.  first_half: next use and eager validity
-// are all that is read of it (with a sweep cap the rest runs too, since it may be what reaches it).
-int run_batch(Prog& G, std::vector<ompd_cfg>& cfgs, std::vector<ompd_result>& res, uint32_t flags, bool first_half)
+// Solve a batch of CFGs given by device-pointer descriptors; `key` names its procedures or contexts
+// and its kind, and so its descriptors.  first_half: next use and eager validity are all that is
+// read of it (with a sweep cap the rest runs too, since it may be what reaches it).
+template <class Make>
+int run_batch(Prog& G, std::vector<int> key, Make&& make, uint32_t flags, bool first_half, std::vector<ompd_result>& res)
 {
-    if (cfgs.empty()) return OMPD_OK;
-    PlanConfig pc;
-    pc.use_graph = false;   // one-shot plans: capturing a graph would not be replayed
-    pc.first_half = first_half && !(G.flags >> 16);
     ompd_plan* plan = nullptr;
-    int rc = ompd_plan_build(G.ctx, cfgs.data(), res.data(), (int32_t)cfgs.size(), flags | OMPD_F_DEVICE_PTRS | G.flags,
-                             pc, &plan);
-    if (rc) return rc;
-    rc = ompd_plan_run_locked(plan, G.s);
+    for (const Prog::Kept& k : G.kept)
+        if (k.key == key) { plan = k.plan; break; }
+    int rc = OMPD_OK;
+    if (plan) rc = ompd_plan_rerun_locked(plan, G.s);
+    else {
+        std::vector<ompd_cfg> cfgs;
+        make(cfgs, res);
+        if (cfgs.empty()) return OMPD_OK;
+        PlanConfig pc;
+        pc.use_graph = false;   // (a few runs: capturing a graph would not pay)
+        pc.first_half = first_half && !(G.flags >> 16);
+        auto build = [&]() {
+            return ompd_plan_build(G.ctx, cfgs.data(), res.data(), (int32_t)cfgs.size(),
+                                   flags | OMPD_F_DEVICE_PTRS | G.flags, pc, &plan);
+        };
+        rc = build();
+        if (rc == OMPD_E_NOMEM && !G.kept.empty()) {
+            while (!G.kept.empty()) G.drop_oldest();
+            rc = build();
+        }
+        if (rc) return rc;
+        while (!G.kept.empty() && G.kept_bytes + plan->scratch_bytes > Prog::KEPT_BYTES) G.drop_oldest();
+        G.kept.push_back(Prog::Kept{std::move(key), plan, plan->scratch_bytes});
+        G.kept_bytes += plan->scratch_bytes;
+        rc = ompd_plan_run_locked(plan, G.s);
+    }
     if (rc == OMPD_OK) rc = ompd_plan_collect(plan, nullptr);
-    for (size_t i = 0; i < cfgs.size(); ++i) memcpy(res[i].sweeps, plan->res[i].sweeps, sizeof res[i].sweeps);
-    ompd_plan_destroy(plan);
-    G.solves += (int64_t)cfgs.size();
+    res = plan->res;
+    G.solves += (int64_t)plan->n;
     return rc;
 }
 
@@ -817,6 +873,7 @@ int read_flag(Prog& G, int32_t* dflag, int& out)
 {
     CK(hipMemcpyAsync(&out, dflag, 4, hipMemcpyDeviceToHost, G.s));
     CK(hipStreamSynchronize(G.s));
+    G.stage_used = 0;
     return OMPD_OK;
 }
 
@@ -849,8 +906,10 @@ int setup(Prog& G)
         po[i].sbnd = take(8 * 16 * wd);
         po[i].callees = take(4 * ns);
         po[i].sitej = take(4 * ns);
-        po[i].ptab = take(8 * ns * SUM_ROWS * wd);
-        po[i].eout = take(8 * 16 * nb * wd);
+    }
+    for (int i = 0; i < n; ++i) {
+        po[i].ptab = take(8 * st.sites[i].size() * SUM_ROWS * st.wd[i]);
+        po[i].eout = take(8 * 16 * (size_t)st.nb[i] * st.wd[i]);
     }
     const size_t oS = take(8 * (size_t)n * SUM_ROWS * sw);
     const size_t oCm = take(8 * (size_t)std::max(gw, 1));
@@ -901,12 +960,43 @@ int setup(Prog& G)
         co[x].out = take(8 * (8 * nb * wd + 2 * ne * wd) + (size_t)P->procs[p].n_vars + 2 * nb + 64);
     }
     const size_t oItems = take(64ull << 20);   // staging of kernel work items
+    if (hipHostMalloc((void**)&G.stage, Prog::STAGE, hipHostMallocDefault) != hipSuccess) {
+        G.stage = nullptr;
+        return ompd_fail(OMPD_E_NOMEM, "program: pinned staging buffer");
+    }
     hipError_t e = hipMalloc(&G.arena, total);
     if (e != hipSuccess) return ompd_fail(OMPD_E_NOMEM, std::string("program arena: ") + hipGetErrorString(e));
     char* A = G.arena;
     G.sp.resize(n); G.si.resize(n); G.kind.resize(n); G.space.resize(n); G.R.resize(n); G.Rd.resize(n);
     G.W.resize(n); G.call.resize(n); G.sbnd.resize(n); G.callees.resize(n); G.ptab.resize(n); G.e_out.resize(n);
     G.sitej.resize(n);
+    // the procedures' inputs follow each other in the arena: they gather in the staging buffer, as
+    // much of them as fits, and go over together
+    size_t lo = 0, hi = 0;   // the arena's bytes in the staging buffer
+    auto flush = [&]() -> int {
+        if (hi > lo) CK(hipMemcpyAsync(A + lo, G.stage, hi - lo, hipMemcpyHostToDevice, G.s));
+        CK(hipStreamSynchronize(G.s));
+        lo = hi;
+        return OMPD_OK;
+    };
+    auto put = [&](void* dst, const void* src, size_t bytes) -> int {
+        if (!bytes) return OMPD_OK;
+        const size_t at = (size_t)((char*)dst - A);
+        if (at + bytes - lo > Prog::STAGE) {
+            const int rc = flush();
+            if (rc) return rc;
+            lo = hi = at;
+        }
+        if (bytes > Prog::STAGE) {
+            CK(hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, G.s));
+            CK(hipStreamSynchronize(G.s));
+            lo = hi = at + bytes;
+            return OMPD_OK;
+        }
+        memcpy(G.stage + (at - lo), src, bytes);
+        hi = at + bytes;
+        return OMPD_OK;
+    };
     std::vector<uint64_t> hb;
     for (int i = 0; i < n; ++i) {
         const ompd_cfg& g = P->procs[i];
@@ -918,26 +1008,21 @@ int setup(Prog& G)
         G.callees[i] = (int32_t*)(A + po[i].callees); G.ptab[i] = (uint64_t*)(A + po[i].ptab);
         G.sitej[i] = (int32_t*)(A + po[i].sitej);
         G.e_out[i] = (uint64_t*)(A + po[i].eout);
-        CK(hipMemcpyAsync(G.sp[i], g.succ_ptr, 4 * (nb + 1), hipMemcpyHostToDevice, G.s));
-        if (ne) {
-            CK(hipMemcpyAsync(G.si[i], g.succ_idx, 4 * ne, hipMemcpyHostToDevice, G.s));
-            CK(hipMemcpyAsync(G.kind[i], g.edge_kind, ne, hipMemcpyHostToDevice, G.s));
-        }
-        CK(hipMemcpyAsync(G.space[i], g.space, nb, hipMemcpyHostToDevice, G.s));
-        if (wd) {
-            CK(hipMemcpyAsync(G.R[i], g.read_bits, 8 * nb * wd, hipMemcpyHostToDevice, G.s));
-            CK(hipMemcpyAsync(G.Rd[i], g.read_bits, 8 * nb * wd, hipMemcpyHostToDevice, G.s));
-            CK(hipMemcpyAsync(G.W[i], g.write_bits, 8 * nb * wd, hipMemcpyHostToDevice, G.s));
-        }
+        int rc = put(G.sp[i], g.succ_ptr, 4 * (nb + 1));
+        if (!rc) rc = put(G.si[i], g.succ_idx, 4 * ne);
+        if (!rc) rc = put(G.kind[i], g.edge_kind, ne);
+        if (!rc) rc = put(G.space[i], g.space, nb);
+        if (!rc) rc = put(G.R[i], g.read_bits, 8 * nb * wd);
+        if (!rc) rc = put(G.Rd[i], g.read_bits, 8 * nb * wd);
+        if (!rc) rc = put(G.W[i], g.write_bits, 8 * nb * wd);
+        if (rc) return rc;
         std::vector<int32_t> call(nb, -1), cal(std::max<size_t>(ns, 1), -1), sj(std::max<size_t>(ns, 1), 0);
         for (size_t k = 0; k < ns; ++k) {
             call[P->call_block[st.sites[i][k]]] = (int32_t)k;
             cal[k] = P->callee[st.sites[i][k]];
             sj[k] = st.sites[i][k];
         }
-        CK(hipMemcpyAsync(G.call[i], call.data(), 4 * nb, hipMemcpyHostToDevice, G.s));
-        CK(hipMemcpyAsync(G.callees[i], cal.data(), 4 * cal.size(), hipMemcpyHostToDevice, G.s));
-        CK(hipMemcpyAsync(G.sitej[i], sj.data(), 4 * sj.size(), hipMemcpyHostToDevice, G.s));
+        rc = put(G.call[i], call.data(), 4 * nb);
         // summary boundaries, evaluation 2e+l: entry valid (e ? shared : none) on both spaces
         // plus the other locals on the host; the shared variables (globals and parameters) live
         // after exit in both spaces iff l
@@ -958,9 +1043,12 @@ int setup(Prog& G)
                 hb[(ev * 4 + 3) * wd + w] = ell ? gm : 0;
             }
         }
-        if (wd) CK(hipMemcpyAsync(G.sbnd[i], hb.data(), 8 * 16 * wd, hipMemcpyHostToDevice, G.s));
-        CK(hipStreamSynchronize(G.s));   // host vectors are reused
+        if (!rc) rc = put(G.sbnd[i], hb.data(), 8 * 16 * wd);
+        if (!rc) rc = put(G.callees[i], cal.data(), 4 * cal.size());
+        if (!rc) rc = put(G.sitej[i], sj.data(), 4 * sj.size());
+        if (rc) return rc;
     }
+    if (const int rc = flush()) return rc;
     G.S = (uint64_t*)(A + oS);
     G.cmask = (uint64_t*)(A + oCm);
     G.d_ap = (int32_t*)(A + oAp);
@@ -1101,36 +1189,39 @@ ompd_cfg dev_cfg(Prog& G, int p)
 }
 
 // Evaluate the summaries of a set of procedures (4 boundary solves each) and
-// gather the rows selected by `rows` (bit 0 next use, bit 1 validity tables).
-int evaluate(Prog& G, const std::vector<int>& procs, int rows, int& changed)
+// gather the rows selected by `rows` (bit 0 next use, bit 1 validity tables);
+// *changed: whether a row changed (not read back for NULL).
+int evaluate(Prog& G, const std::vector<int>& procs, int rows, int* changed)
 {
     const Structure& st = G.st;
-    changed = 0;
+    if (changed) *changed = 0;
     if (procs.empty()) return OMPD_OK;
     std::vector<CallTabItem> ct;
     for (int p : procs) calltab_items(G, p, -1, ct);
-    int rc = upload_items(ct, k_calltab, 256, G.s, G.arena_items);
+    int rc = upload_items(G, ct, k_calltab, 256);
     if (rc) return rc;
-    std::vector<ompd_cfg> cfgs;
-    std::vector<ompd_result> res;
-    for (int p : procs) {
-        const size_t wd = st.wd[p], bv = (size_t)st.nb[p] * wd;
-        for (int ev = 0; ev < 4; ++ev) {
-            ompd_cfg d = dev_cfg(G, p);
-            if (d.call_summary) d.summaries = G.ptab[p];
-            d.entry_valid_host = G.sbnd[p] + (ev * 4 + 0) * wd;
-            d.entry_valid_dev = G.sbnd[p] + (ev * 4 + 1) * wd;
-            d.exit_live_host = G.sbnd[p] + (ev * 4 + 2) * wd;
-            d.exit_live_dev = G.sbnd[p] + (ev * 4 + 3) * wd;
-            ompd_result r;
-            memset(&r, 0, sizeof r);
-            uint64_t* o = G.e_out[p] + (size_t)ev * 4 * bv;
-            r.nu_host = o; r.nu_dev = o + bv; r.ave_host = o + 2 * bv; r.ave_dev = o + 3 * bv;
-            cfgs.push_back(d);
-            res.push_back(r);
-        }
-    }
-    rc = run_batch(G, cfgs, res, OMPD_F_SUMMARY, true);
+    std::vector<ompd_result> results;
+    auto make = [&](std::vector<ompd_cfg>& cfgs, std::vector<ompd_result>& res) {
+        for (int p : procs)
+            for (int ev = 0; ev < 4; ++ev) {
+                const size_t wd = st.wd[p], bv = (size_t)st.nb[p] * wd;
+                ompd_cfg d = dev_cfg(G, p);
+                if (d.call_summary) d.summaries = G.ptab[p];
+                d.entry_valid_host = G.sbnd[p] + (ev * 4 + 0) * wd;
+                d.entry_valid_dev = G.sbnd[p] + (ev * 4 + 1) * wd;
+                d.exit_live_host = G.sbnd[p] + (ev * 4 + 2) * wd;
+                d.exit_live_dev = G.sbnd[p] + (ev * 4 + 3) * wd;
+                ompd_result r;
+                memset(&r, 0, sizeof r);
+                uint64_t* o = G.e_out[p] + (size_t)ev * 4 * bv;
+                r.nu_host = o; r.nu_dev = o + bv; r.ave_host = o + 2 * bv; r.ave_dev = o + 3 * bv;
+                cfgs.push_back(d);
+                res.push_back(r);
+            }
+    };
+    std::vector<int> key(procs);
+    key.push_back(-1);
+    rc = run_batch(G, std::move(key), make, OMPD_F_SUMMARY, true, results);
     if (rc) return rc;
     std::vector<SumItem> si;
     for (int p : procs) {
@@ -1148,12 +1239,12 @@ int evaluate(Prog& G, const std::vector<int>& procs, int rows, int& changed)
     }
     rc = zero_flag(G, G.flag);
     if (rc) return rc;
-    rc = upload_items(si, k_sumgather, 64, G.s, G.arena_items);
+    rc = upload_items(G, si, k_sumgather, 64);
     if (rc) return rc;
-    return read_flag(G, G.flag, changed);
+    return changed ? read_flag(G, G.flag, *changed) : OMPD_OK;
 }
 
-int may_rows(Prog& G, const std::vector<int>& procs, int& changed)
+int may_rows(Prog& G, const std::vector<int>& procs, int* changed)
 {
     const Structure& st = G.st;
     std::vector<MayItem> mi;
@@ -1170,9 +1261,9 @@ int may_rows(Prog& G, const std::vector<int>& procs, int& changed)
     }
     int rc = zero_flag(G, G.flag);
     if (rc) return rc;
-    rc = upload_items(mi, k_may, 64, G.s, G.arena_items);
+    rc = upload_items(G, mi, k_may, 64);
     if (rc) return rc;
-    return read_flag(G, G.flag, changed);
+    return changed ? read_flag(G, G.flag, *changed) : OMPD_OK;
 }
 
 // The rows of the calls made inside kernels of a set of procedures, from their callees' current
@@ -1192,7 +1283,7 @@ int device_calls(Prog& G, const std::vector<int>& procs)
             I.block = G.P->call_block[j]; I.wd = st.wd[p]; I.gw = st.gw; I.sw = st.sw; I.G = st.G;
             it.push_back(I);
         }
-    return upload_items(it, k_devcall, 64, G.s, G.arena_items);
+    return upload_items(G, it, k_devcall, 64);
 }
 
 // Bottom-up: components by level; a non-recursive procedure is evaluated
@@ -1224,9 +1315,9 @@ int summarize(Prog& G)
         // calls made inside kernels read their callees' may sets (final below this level)
         int rc = device_calls(G, single);
         if (rc) return rc;
-        rc = evaluate(G, single, 3, ch);
+        rc = evaluate(G, single, 3, nullptr);
         if (rc) return rc;
-        rc = may_rows(G, single, ch);
+        rc = may_rows(G, single, nullptr);
         if (rc) return rc;
         if (recur_procs.empty()) continue;
         // recursive components: validity tables start at all ones over the shared variables
@@ -1248,12 +1339,12 @@ int summarize(Prog& G)
         do {
             rc = device_calls(G, recur_procs);
             if (rc) return rc;
-            rc = may_rows(G, recur_procs, ch);
+            rc = may_rows(G, recur_procs, &ch);
             if (rc) return rc;
         } while (ch);
         for (int rows : {1, 2}) {
             do {
-                rc = evaluate(G, recur_procs, rows, ch);
+                rc = evaluate(G, recur_procs, rows, &ch);
                 if (rc) return rc;
             } while (ch);
         }
@@ -1269,30 +1360,33 @@ int solve_contexts(Prog& G, const std::vector<int>& xs, bool live)
     const Structure& st = G.st;
     std::vector<CallTabItem> ct;
     for (int x : xs) calltab_items(G, st.cproc[x], x, ct);
-    int rc = upload_items(ct, k_calltab, 256, G.s, G.arena_items);
+    int rc = upload_items(G, ct, k_calltab, 256);
     if (rc) return rc;
-    std::vector<ompd_cfg> cfgs;
-    std::vector<ompd_result> res;
-    for (int x : xs) {
-        const int p = st.cproc[x];
-        const size_t wd = st.wd[p];
-        ompd_cfg d = dev_cfg(G, p);
-        if (d.call_summary) d.summaries = G.ctab[x];
-        d.entry_valid_host = G.bnd[x]; d.entry_valid_dev = G.bnd[x] + wd;
-        d.exit_live_host = G.bnd[x] + 2 * wd; d.exit_live_dev = G.bnd[x] + 3 * wd;
-        ompd_result r;
-        memset(&r, 0, sizeof r);
-        r.nu_host = G.o_nu_h[x]; r.nu_dev = G.o_nu_d[x]; r.ave_host = G.o_ave_h[x]; r.ave_dev = G.o_ave_d[x];
-        r.avf_host = G.o_avf_h[x]; r.avf_dev = G.o_avf_d[x];
-        r.ins_entry_to_host = G.o_ie_h[x]; r.ins_entry_to_dev = G.o_ie_d[x];
-        r.ins_edge_to_host = G.o_ig_h[x]; r.ins_edge_to_dev = G.o_ig_d[x];
-        r.var_kind = G.o_vk[x]; r.after_dev = G.o_ad[x]; r.before_dev = G.o_bd[x];
-        cfgs.push_back(d);
-        res.push_back(r);
-    }
-    rc = run_batch(G, cfgs, res, OMPD_F_SUMMARY, live);
+    std::vector<ompd_result> results;
+    auto make = [&](std::vector<ompd_cfg>& cfgs, std::vector<ompd_result>& res) {
+        for (int x : xs) {
+            const int p = st.cproc[x];
+            const size_t wd = st.wd[p];
+            ompd_cfg d = dev_cfg(G, p);
+            if (d.call_summary) d.summaries = G.ctab[x];
+            d.entry_valid_host = G.bnd[x]; d.entry_valid_dev = G.bnd[x] + wd;
+            d.exit_live_host = G.bnd[x] + 2 * wd; d.exit_live_dev = G.bnd[x] + 3 * wd;
+            ompd_result r;
+            memset(&r, 0, sizeof r);
+            r.nu_host = G.o_nu_h[x]; r.nu_dev = G.o_nu_d[x]; r.ave_host = G.o_ave_h[x]; r.ave_dev = G.o_ave_d[x];
+            r.avf_host = G.o_avf_h[x]; r.avf_dev = G.o_avf_d[x];
+            r.ins_entry_to_host = G.o_ie_h[x]; r.ins_entry_to_dev = G.o_ie_d[x];
+            r.ins_edge_to_host = G.o_ig_h[x]; r.ins_edge_to_dev = G.o_ig_d[x];
+            r.var_kind = G.o_vk[x]; r.after_dev = G.o_ad[x]; r.before_dev = G.o_bd[x];
+            cfgs.push_back(d);
+            res.push_back(r);
+        }
+    };
+    std::vector<int> key(xs);
+    key.push_back(live ? -2 : -3);
+    rc = run_batch(G, std::move(key), make, OMPD_F_SUMMARY, live, results);
     if (rc) return rc;
-    for (size_t i = 0; i < xs.size(); ++i) memcpy(&G.sweeps[(size_t)xs[i] * 6], res[i].sweeps, sizeof res[i].sweeps);
+    for (size_t i = 0; i < xs.size(); ++i) memcpy(&G.sweeps[(size_t)xs[i] * 6], results[i].sweeps, sizeof results[i].sweeps);
     return OMPD_OK;
 }
 
@@ -1335,7 +1429,7 @@ int boundary_system(Prog& G, int live)
                 cb.push_back(I);
             }
         }
-        rc = upload_items(cb, k_contrib, 64, G.s, G.arena_items);
+        rc = upload_items(G, cb, k_contrib, 64);
         if (rc) return rc;
         int32_t* chg = G.flag + 16;
         CK(hipMemsetAsync(chg, 0, 4 * (size_t)nctx, G.s));
@@ -1349,7 +1443,7 @@ int boundary_system(Prog& G, int live)
             I.wd = st.wd[q]; I.sw = sw; I.sh = st.sh[q]; I.nv = P->procs[q].n_vars; I.live = live;
             mi.push_back(I);
         }
-        rc = upload_items(mi, k_meet, 64, G.s, G.arena_items);
+        rc = upload_items(G, mi, k_meet, 64);
         if (rc) return rc;
         CK(hipMemcpyAsync(hc.data(), chg, 4 * (size_t)nctx, hipMemcpyDeviceToHost, G.s));
         CK(hipStreamSynchronize(G.s));
@@ -1380,7 +1474,7 @@ int contexts(Prog& G)
         I.dst = G.bnd[x]; I.src = G.bnd0 + G.bnd0_off[x]; I.n = (int32_t)(G.bnd0_off[x + 1] - G.bnd0_off[x]);
         cp.push_back(I);
     }
-    int rc = upload_items(cp, k_copy, 64, G.s, G.arena_items);
+    int rc = upload_items(G, cp, k_copy, 64);
     if (rc) return rc;
     rc = boundary_system(G, 1);
     if (rc) return rc;
@@ -1406,19 +1500,19 @@ int contexts(Prog& G)
         O.gw = st.gw; O.sw = sw; O.G = st.G; O.sh_caller = st.sh[P->call_proc[j]]; O.all = 0;
         oi.push_back(O);
     }
-    rc = upload_items(gi, k_gap, 64, G.s, G.arena_items);
+    rc = upload_items(G, gi, k_gap, 64);
     if (rc) return rc;
     int32_t flags[2];
     CK(hipMemcpyAsync(flags, any, 8, hipMemcpyDeviceToHost, G.s));
     CK(hipStreamSynchronize(G.s));
     if (!flags[0]) return OMPD_OK;
-    rc = upload_items(oi, k_own, 64, G.s, G.arena_items);
+    rc = upload_items(G, oi, k_own, 64);
     if (rc) return rc;
     CK(hipMemcpyAsync(flags, any, 8, hipMemcpyDeviceToHost, G.s));
     CK(hipStreamSynchronize(G.s));
     if (flags[1]) return OMPD_OK;
     for (auto& O : oi) O.all = 1;
-    return upload_items(oi, k_own, 64, G.s, G.arena_items);
+    return upload_items(G, oi, k_own, 64);
 }
 
 }  // namespace
@@ -1482,7 +1576,7 @@ extern "C" int ompd_analyze_program(ompd_ctx* ctx, const ompd_program* prog, omp
         // previous caps, for the comparison
         if (sw) CK(hipMemcpyAsync(capv.data(), G.caps, 8 * capv.size(), hipMemcpyDeviceToHost, G.s));
         CK(hipStreamSynchronize(G.s));
-        rc = upload_items(ci, k_cap, 64, G.s, G.arena_items);
+        rc = upload_items(G, ci, k_cap, 64);
         if (rc) return rc;
         if (sw) CK(hipMemcpyAsync(capn.data(), G.caps, 8 * capn.size(), hipMemcpyDeviceToHost, G.s));
         if (st.nc && sw) CK(hipMemcpyAsync(dnew.data(), G.demand_new, 8 * (size_t)st.nc * sw, hipMemcpyDeviceToHost, G.s));
@@ -1514,7 +1608,7 @@ extern "C" int ompd_analyze_program(ompd_ctx* ctx, const ompd_program* prog, omp
             I.block = prog->call_block[j]; I.wd = st.wd[p]; I.gw = st.gw; I.G = st.G;
             di.push_back(I);
         }
-        rc = upload_items(di, k_demand, 64, G.s, G.arena_items);
+        rc = upload_items(G, di, k_demand, 64);
         if (rc) return rc;
     }
     out->rounds = rounds;
@@ -1553,11 +1647,8 @@ extern "C" int ompd_analyze_program(ompd_ctx* ctx, const ompd_program* prog, omp
         if (r.fp_clause && bv) memset(r.fp_clause, 0, 8 * bv);   // procedures' scalar marks are not used
         memcpy(r.sweeps, &G.sweeps[(size_t)x * 6], sizeof r.sweeps);
     };
-    const size_t STAGE = (size_t)64 << 20;
-    char* stage = nullptr;
-    if (hipHostMalloc((void**)&stage, STAGE, hipHostMallocDefault) != hipSuccess)
-        return ompd_fail(OMPD_E_NOMEM, "program: pinned staging buffer");
-    struct StageGuard { char* p; ~StageGuard() { (void)hipHostFree(p); } } stg{stage};
+    const size_t STAGE = Prog::STAGE;
+    char* const stage = G.stage;
     CK(hipStreamSynchronize(G.s));
     std::vector<char> big;   // a context larger than the staging buffer (not in the shapes this targets)
     for (int x = 0; x < nctx;) {

@@ -845,6 +845,31 @@ int ompd_plan_run_locked(ompd_plan* p, hipStream_t s)
     return launch_all(p, s);
 }
 
+// The status words of a launch as its ingest left them.
+__global__ void __launch_bounds__(256) ompd_k_info_clear(const DevCfg* __restrict__ cfgs, int n)
+{
+    const int total = n * INFO_WORDS;
+    for (int t = blockIdx.x * blockDim.x + threadIdx.x; t < total; t += gridDim.x * blockDim.x) {
+        const int w = t % INFO_WORDS;
+        if (w != INFO_LEVELS && w != INFO_ORDER) cfgs[t / INFO_WORDS].info[w] = 0;
+    }
+}
+
+int ompd_plan_rerun_locked(ompd_plan* p, hipStream_t s)
+{
+    if (p->dims.n_walk) return ompd_plan_run_locked(p, s);
+    CK(hipSetDevice(p->ctx->device));
+    p->last_stream = s;
+    CK(hipEventRecord(p->ev0, s));
+    hipLaunchKernelGGL(ompd_k_info_clear, dim3(std::min((p->n * INFO_WORDS + 255) / 256, 1024)), dim3(256), 0, s,
+                       (const DevCfg*)p->d_cfgs, p->n);
+    CK(hipEventRecord(p->ev1, s));
+    int rc = launch_solve(p, s);
+    if (rc) return rc;
+    CK(hipEventRecord(p->ev2, s));
+    return OMPD_OK;
+}
+
 extern "C" int ompd_plan_run(ompd_plan* p, void* stream)
 {
     if (!p) return ompd_fail(OMPD_E_INVAL, "plan is NULL");
@@ -895,8 +920,10 @@ static int gather_info(const DevCfg* d_cfgs, int n, int32_t* d_out, int32_t* h_o
 int ompd_plan_collect(ompd_plan* p, int32_t* per_cfg)
 {
     CK(hipSetDevice(p->ctx->device));
-    CK(hipStreamSynchronize(p->last_stream));
-    if (p->n == 0) return OMPD_OK;
+    if (p->n == 0) {
+        CK(hipStreamSynchronize(p->last_stream));
+        return OMPD_OK;
+    }
     // info words live per CFG inside the scratch arena
     int rg = gather_info(p->d_cfgs, p->n, p->d_info, p->h_info.data(), p->last_stream);
     if (rg) return rg;
