@@ -140,6 +140,7 @@ constexpr int strip_records(int ne) { return ne + 1; }
 constexpr int STRIP_T_WORDS = 16, STRIP_T_ROWS = 64;
 // most wavefronts of a strip workgroup, and the control words of its LDS
 constexpr int STRIP_MAX_WAVES = 8;
+constexpr int STRIP_BUSY_WAVES = 4;   // wavefronts of a strip where strips queue for the compute units
 constexpr int STRIP_CTL_WORDS = 64;
 // passes whose results a wavefront keeps in LDS (64 lanes, a pair of words each)
 constexpr int STRIP_RING = 8;

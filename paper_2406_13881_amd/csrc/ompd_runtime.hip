@@ -299,29 +299,42 @@ void ompd_settle_sched(DevCfg* h, int n, int n_cu, bool split)
     }
     // Blocks per wavefront: the fewer, the shorter a strip's chain of passes, and the more rounds
     // until what one wavefront changed has reached the others.  While the GPU has room for every
-    // strip at once (a workgroup each) 32 is best; where strips queue for the compute units, their
-    // total work counts and fewer, longer runs cost less.  Solve kernels, us, at 32 / 64 / 200 / 400
-    // blocks: a lone CFG of 66 blocks 163 / 185 / 257 / 257, of 779 blocks 579 / 579 / 625 / 1060;
-    // 96 CFGs (242 strips) 1415 / 1795 / 3020 / 4420; 1024 CFGs (4266 strips) 16.9 / 12.3 / 12.1 /
-    // 12.5 ms; 2048 CFGs of about 60 blocks (2377 strips) 1170 / 841 / 493 / 493.
+    // strip at once (a workgroup each) 32 blocks and up to 8 wavefronts are best; where strips queue
+    // for the compute units, their total work counts and longer runs cost less, and 4 wavefronts:
+    // 8 of them fill a compute unit's registers, which idles while they wait for each other, where
+    // two workgroups of 4 fill each other's waits.  Solve kernels, us, at 32 / 64 / 200 / 400 blocks
+    // and up to 8 wavefronts: a lone CFG of 66 blocks 163 / 185 / 257 / 257, of 779 blocks 579 / 579 /
+    // 625 / 1060; 96 CFGs (242 strips) 1415 / 1795 / 3020 / 4420; 2048 CFGs of about 60 blocks (2377
+    // strips) 1170 / 841 / 493 / 493.  1024 CFGs (4266 strips) at 200 blocks: up to 8 wavefronts
+    // 12.2 ms, 4 9.9 ms, 2 10.6 ms.
     const bool idle = strips <= n_cu;
-    int most = 1;
     const int busy_per = (int)std::min<int64_t>(200, 32 * strips / std::max(n_cu, 1));
+    int most = 1;
     for (int i = 0; i < n; ++i) {
         DevCfg& d = h[i];
         d.spread = d.sched == SCHED_LEVEL && (idle || !d.sched_rule);
-        const int per = d.spread ? 32 : std::max(32, busy_per);
+        const int per = d.spread ? 32 : std::max(32, busy_per), limit = idle ? STRIP_MAX_WAVES : STRIP_BUSY_WAVES;
         // (a caller's sweep cap counts rounds: one run of passes, so that they don't depend on timing)
         d.waves = 1;
         if (d.sweep_cap == 0)
-            while (d.waves < STRIP_MAX_WAVES && d.nb > per * d.waves) d.waves *= 2;
-        if (d.sched == SCHED_LEVEL && d.sweep_cap == 0) most = std::max(most, d.waves);
+            while (d.waves < limit && d.nb > per * d.waves) d.waves *= 2;
+        if (d.sched == SCHED_LEVEL) most = std::max(most, d.waves);
     }
-    // With room for every strip one launch holds them all: launches for two sizes would take the
-    // longest of each in turn, and a small CFG with more wavefronts than it likes still ends first.
-    if (idle)
+    // One launch holds strips of one wavefront count, and two launches take the longest of each in
+    // turn.  So all take the largest CFG's count while the GPU has room for every strip (a small CFG
+    // with more wavefronts than it likes still ends first), or where the CFGs that would rather have
+    // fewer are at most a quarter of the work (the 1024 CFGs: 9.9 ms in three launches, 9.3 in one).
+    int64_t work = 0, less = 0;
+    auto takes_most = [&](const DevCfg& d) { return d.sched == SCHED_LEVEL && d.sweep_cap == 0; };
+    for (int i = 0; i < n; ++i)
+        if (takes_most(h[i])) {
+            const int64_t k = (int64_t)((h[i].wd + h[i].units) / h[i].units) * h[i].nb;
+            work += k;
+            if (h[i].waves < most) less += k;
+        }
+    if (idle || 4 * less <= work)
         for (int i = 0; i < n; ++i)
-            if (h[i].sched == SCHED_LEVEL && h[i].sweep_cap == 0) h[i].waves = most;
+            if (takes_most(h[i])) h[i].waves = most;
 }
 
 // Fill the kernels' descriptor of one CFG whose scratch starts at `base`.
