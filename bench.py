@@ -3,14 +3,13 @@
 Default workload (N = 1): the 4,096-procedure batch (user blocks
 log-uniform in [16, 8192], variables log-uniform in [32, 4096], loop depth
 <= 3, 30 % device blocks, read p = 0.2, write p = 0.1), resident in HBM,
-solved by one resident plan per step (ingest kernel + one persistent solve
-launch, replayed from a captured HIP graph; slice/LDS choice by the
-autotuner).  A step is one complete pass of the whole path: ingest and
+solved by one resident plan per step (ingest, transposes and the two strip
+kernels, replayed from a captured HIP graph).  A step is one complete pass of the whole path: ingest and
 validation, next use, validity, pending copies, delayed placement and its
 materialisation, validity after placement, labels and map kinds.
 
 Printed JSON line: the metric of the benchmark plus
-  roofline      HBM roofline of the dominant kernel (the persistent solve),
+  roofline      HBM roofline of the dominant kernel (a strip kernel),
   cpu_baseline  the CPU oracle timed on a bounded sample of the same batch,
   plain         the same CFGs as one plain per-CFG solve each, back to back,
   single        the 16,384-block x 2,048-variable procedure on its own,
@@ -172,7 +171,7 @@ def serving(ctx, n_pool, n_cap, n_warm, n_meas, loads):
 
 
 TRAFFIC = os.path.join(ROOT, "profiles", "hbm_traffic_c3_batch4096.json")
-KERNEL_SRC = os.path.join(ROOT, "paper_2406_13881_amd", "csrc", "ompd_kernels.hip")
+KERNEL_SRCS = [os.path.join(ROOT, "paper_2406_13881_amd", "csrc", f) for f in ("ompd_kernels.hip", "ompd_strip.hip")]
 
 
 def measured_traffic(kernel):
@@ -182,7 +181,7 @@ def measured_traffic(kernel):
     import hashlib
     try:
         rec = json.load(open(TRAFFIC))
-        sha = hashlib.sha256(open(KERNEL_SRC, "rb").read()).hexdigest()
+        sha = hashlib.sha256(b"".join(open(f, "rb").read() for f in KERNEL_SRCS)).hexdigest()
     except (OSError, ValueError):
         return None
     if rec.get("kernel_source_sha256") != sha or kernel not in rec.get("per_launch", {}):
@@ -198,7 +197,8 @@ def kernel_bytes(cfgs):
     # (the loop-entry refinement, ompd_k_live and ompd_k_post_live, is not requested here: no launch)
     out = dict.fromkeys(("ompd_k_prep", "ompd_k_nu", "ompd_k_ave", "ompd_k_post_ave", "ompd_k_mayp",
                          "ompd_k_post_mayp", "ompd_k_later", "ompd_k_post_later", "ompd_k_live",
-                         "ompd_k_post_live", "ompd_k_avf", "ompd_k_post_avf", "ompd_k_varkind"), 0)
+                         "ompd_k_post_live", "ompd_k_avf", "ompd_k_post_avf", "ompd_k_varkind", "ompd_k_tin",
+                         "ompd_k_strip_a", "ompd_k_tmid", "ompd_k_strip_b", "ompd_k_tout"), 0)
     for c in cfgs:
         wd = (c.n_vars + 63) // 64
         nb, ne = c.n_blocks, c.n_edges
@@ -214,8 +214,15 @@ def kernel_bytes(cfgs):
         out["ompd_k_avf"] += 3 * bv + 2 * ev + 2 * bv          # copies before blocks, W, copies on edges in; validity after out
         out["ompd_k_post_avf"] += 2 * bv + 2 * ev + 4 * bv + 2 * bv + 3 * wd * 8   # copies, validity after, R, W in; validity before, map masks out
         out["ompd_k_varkind"] += 3 * wd * 8 + c.n_vars         # map masks in; map kinds out
+        # the strip kernels: what a phase must read and write once, in the strips' layout
+        out["ompd_k_tin"] += 2 * bv + 2 * bv                   # R, W rows in; pairs out
+        out["ompd_k_strip_a"] += 2 * bv + 6 * bv + 3 * ev + 2 * nb   # R, W in; next use, validity after and before, EAG, both out
+        out["ompd_k_tmid"] += 4 * bv + 4 * bv                  # next use, validity before: pairs in, rows out
+        out["ompd_k_strip_b"] += 2 * bv + 3 * ev + 4 * bv + 2 * ev   # R, W, EAG, both in; copies and validity out
+        out["ompd_k_tout"] += 2 * (4 * bv + 2 * ev)            # copies, final validity: pairs in, rows out
     # the per-tile kernel runs every phase and pass
-    out["ompd_k_solve"] = sum(v for k, v in out.items() if k != "ompd_k_prep")
+    strips = ("ompd_k_tin", "ompd_k_strip_a", "ompd_k_tmid", "ompd_k_strip_b", "ompd_k_tout")
+    out["ompd_k_solve"] = sum(v for k, v in out.items() if k != "ompd_k_prep" and k not in strips)
     return out
 
 

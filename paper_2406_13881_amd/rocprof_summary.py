@@ -23,7 +23,7 @@ import sqlite3
 import sys
 
 HERE = os.path.dirname(os.path.abspath(__file__))
-KERNEL_SRC = os.path.join(HERE, "csrc", "ompd_kernels.hip")
+KERNEL_SRCS = [os.path.join(HERE, "csrc", f) for f in ("ompd_kernels.hip", "ompd_strip.hip")]
 
 
 def kernel_durations(db_path):
@@ -106,7 +106,7 @@ def main(argv=None):
         return 0
     rec = traffic(args.fetch, args.write, args.cal_fetch, args.cal_write, args.cal_bytes)
     rec = dict({"workload": args.workload,
-                "kernel_source_sha256": hashlib.sha256(open(KERNEL_SRC, "rb").read()).hexdigest()}, **rec)
+                "kernel_source_sha256": hashlib.sha256(b"".join(open(f, "rb").read() for f in KERNEL_SRCS)).hexdigest()}, **rec)
     with open(args.json, "w") as fh:
         json.dump(rec, fh, indent=1)
     print("calibration: a copy of %d bytes reads %.1f KiB (FETCH_SIZE) and writes %.1f KiB (WRITE_SIZE): "
