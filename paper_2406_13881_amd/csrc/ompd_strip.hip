@@ -17,9 +17,9 @@
 // bound by the instructions one wavefront issues, so a pass takes as many words as fit.
 //
 // ompd_k_tin transposes the accesses into that layout, ompd_k_tmid and ompd_k_tout the results
-// back to the caller's rows (bound by memory: 3.5-5.1 TB/s on 4096 CFGs).  One workgroup runs all phases of its words (ompd_k_strip_a: next use
-// and eager validity; ompd_k_strip_b: pending copies, placement, refinement, final validity, map
-// kinds).
+// back to the caller's rows (bound by memory: 3.5-5.1 TB/s on 4096 CFGs).  One workgroup runs all
+// phases of its words (ompd_k_strip_a: next use and eager validity; ompd_k_strip_b: pending copies,
+// placement, refinement, final validity, map kinds).
 //
 // A phase is a sequence of rounds.  The passes of a direction are cut into one run per wavefront;
 // a round visits every run in level order.  After a round only readers of a neighbour that is not
@@ -1280,8 +1280,8 @@ __device__ __forceinline__ void after_avf(const DevCfg& c, const Strip& t, int n
 // kernels move data at 3.1-3.7 TB/s (a copy: 4.9).  Rows of 8 lanes and 8 words per strip need a quarter
 // fewer passes but twice the arrays per strip: 1024 CFGs the same or slower (strip_b 8.0 -> 8.8 ms);
 // 4 wavefronts per SIMD with inputs loaded 3-4 passes ahead are no faster either.
-// This kernel, before -> now (the five phases and passes it and ompd_k_strip_b replace, walk or
-// levels): 66 blocks x 32 variables 0.55 -> 0.17 ms both kernels, 8002 x 1500 31 -> 2.6 ms, 16386 x
+// Both strip kernels, before (the phase and pass kernels of the walk or of the old level schedule) ->
+// now: 66 blocks x 32 variables 0.55 -> 0.17 ms, 8002 x 1500 31 -> 2.6 ms, 16386 x
 // 2048 68 -> 5.2 ms, 1024 CFGs 76 -> 9.3 ms.
 extern "C" __global__ void __launch_bounds__(64 * STRIP_MAX_WAVES)
 ompd_k_strip_a(const DevCfg* __restrict__ cfgs, const Tile* __restrict__ tiles)
