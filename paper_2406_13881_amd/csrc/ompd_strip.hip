@@ -390,25 +390,59 @@ extern "C" __global__ void __launch_bounds__(1024, 8) ompd_k_sprep(const DevCfg*
     auto flags_of = [&](int b, int k) -> uint32_t {
         return (c.space[b] ? 1u << R1_DEV : 0u) | (kind_of(b, k) << R1_KIND);
     };
+    // A thread takes a block and its edges [e, z); past the first WIDE of them (a switch, its join)
+    // the wavefront's lanes share what is left of each such block, one after another: `first` per
+    // edge of the lane's own block, `rest` per edge of lane l's block, `end` after it.  (One thread
+    // per block throughout: 1.1 / 10.2 ms for a switch of 300 / 3000 cases in a loop; this: 0.6 / 5.5 ms.)
+    constexpr int WIDE = 16;
+    const int wl = tid & 63;
+    auto edges = [&](int e, int z, auto&& first, auto&& rest, auto&& end) {
+        const int own = min(z, e + WIDE);
+        for (int k = e; k < own; ++k) first(k);
+        for (u64 m = __ballot(z - e > WIDE); m; m &= m - 1) {
+            const int l = __builtin_ctzll(m);
+            const int from = __builtin_amdgcn_readlane(e, l) + WIDE, to = __builtin_amdgcn_readlane(z, l);
+            for (int k = from + wl; k < to; k += 64) rest(k, l);
+            end(l);
+        }
+    };
+    auto of = [](auto v, int l) { return (decltype(v))__builtin_amdgcn_readlane((int)v, l); };
+    // the last reader of a block, gathered over a wide block's lanes into lane l's
+    struct Readers { int last = 0; uint32_t xs = 0; };
+    auto gather = [&](Readers& mine, Readers& part, int l) {
+        int v = part.last;
+        for (int d = 1; d < 64; d <<= 1) v = max(v, __shfl_xor(v, d, 64));
+        const bool x = __ballot(part.xs != 0u) != 0ull;
+        if (wl == l) {
+            mine.last = max(mine.last, v);
+            if (x) mine.xs = 0x8000u;
+        }
+        part = Readers{};
+    };
+    auto reader = [&](int dir, Readers& r, int p, int pr) {
+        if (cross(dir, p, pr)) r.xs = 0x8000u;
+        else r.last = max(r.last, pr);
+    };
     // what a block's writer needs to know of its readers: the last pass of its run that reads it
     // later in a round, and (bit 15) whether a cross link does; forward first
-    for (int b = tid; b < nb; b += nt) {
-        const int i = c.pos[b], pf = pass_of(c.loc_f[i]);
-        int last = 0;
-        uint32_t xs = 0;
-        for (int e = c.succ_ptr[b]; e < c.succ_ptr[b + 1]; ++e) {
-            const int pq = pass_of(c.loc_f[c.pos[c.succ_idx[e]]]);
-            if (cross(0, pf, pq)) xs = 0x8000u;
-            else last = max(last, pq);
-        }
-        c.last_f[i] = (uint16_t)((uint32_t)last | xs);
+    for (int b0 = 0; b0 < nb; b0 += nt) {
+        const int b = b0 + tid;
+        const bool on = b < nb;
+        const int i = on ? c.pos[b] : 0, pf = on ? pass_of(c.loc_f[i]) : 0;
+        Readers mine, part;
+        auto look = [&](Readers& r, int p, int e) { reader(0, r, p, pass_of(c.loc_f[c.pos[c.succ_idx[e]]])); };
+        edges(on ? c.succ_ptr[b] : 0, on ? c.succ_ptr[b + 1] : 0, [&](int e) { look(mine, pf, e); },
+              [&](int e, int l) { look(part, of(pf, l), e); }, [&](int l) { gather(mine, part, l); });
+        if (on) c.last_f[i] = (uint16_t)((uint32_t)mine.last | mine.xs);
     }
     __syncthreads();
     // forward records, entries and cross links, by edge
-    for (int b = tid; b < nb; b += nt) {
-        const int i = c.pos[b], kb = c.est_f[i + 1] - c.est_f[i];
-        const uint32_t lb = c.loc_f[i];
-        for (int e = c.succ_ptr[b]; e < c.succ_ptr[b + 1]; ++e) {
+    for (int b0 = 0; b0 < nb; b0 += nt) {
+        const int b = b0 + tid;
+        const bool on = b < nb;
+        const int i = on ? c.pos[b] : 0, kb = on ? c.est_f[i + 1] - c.est_f[i] : 0;
+        const uint32_t lb = on ? c.loc_f[i] : 0u;
+        auto edge = [&](int i, int kb, uint32_t lb, int e) {
             const int q = c.succ_idx[e], iq = c.pos[q], a = c.est_f[iq], k = c.est_f[iq + 1] - a;
             const int slot = atomicSub(&kc[q], 1) - 1;
             const uint32_t lq = c.loc_f[iq];
@@ -420,8 +454,10 @@ extern "C" __global__ void __launch_bounds__(1024, 8) ompd_k_sprep(const DevCfg*
                 record(0, iq, lq, k, slot, i, lb, kb, a + slot,
                        flags_of(q, k) | (le ? 1u << R1_LE : 0u) | ((c.last_f[iq] & 0x8000u) ? 1u << R1_XSRC : 0u));
             if (cross(0, pass_of(lb), pass_of(lq))) c.x_f[atomicAdd(&s_x[0], 1)] = (uint32_t)i | ((uint32_t)pass_of(lq) << 16);
-        }
-        if (b == c.entry) {
+        };
+        edges(on ? c.succ_ptr[b] : 0, on ? c.succ_ptr[b + 1] : 0, [&](int e) { edge(i, kb, lb, e); },
+              [&](int e, int l) { edge(of(i, l), of(kb, l), of(lb, l), e); }, [](int) {});
+        if (on && b == c.entry) {
             const int a = c.est_f[i];
             c.link[a] = (uint32_t)i | ((uint32_t)i << 16);
             c.eid[a] = -1;
@@ -432,27 +468,36 @@ extern "C" __global__ void __launch_bounds__(1024, 8) ompd_k_sprep(const DevCfg*
     __syncthreads();
     // backward records and cross links: a block reads its successors, its readers are its
     // predecessors
-    for (int b = tid; b < nb; b += nt) {
-        const int i = c.pos[b], e0 = c.succ_ptr[b], d = c.succ_ptr[b + 1] - e0;
-        const uint32_t lb = c.loc_b[i];
+    for (int b0 = 0; b0 < nb; b0 += nt) {
+        const int b = b0 + tid;
+        const bool on = b < nb;
+        const int i = on ? c.pos[b] : 0, e0 = on ? c.succ_ptr[b] : 0, d = on ? c.succ_ptr[b + 1] - e0 : 0;
+        const uint32_t lb = on ? c.loc_b[i] : 0u;
         const int pb = pass_of(lb);
-        int last = 0;
-        uint32_t xs = 0;
-        if (b != c.entry)
-            for (int r = c.est_f[i]; r < c.est_f[i + 1]; ++r) {
-                const int pp = pass_of(c.loc_b[c.link[r] & 0x7FFFu]);
-                if (cross(1, pb, pp)) xs = 0x8000u;
-                else last = max(last, pp);
-            }
-        c.last_b[i] = (uint16_t)((uint32_t)last | xs);
-        const uint32_t fl = flags_of(b, d) | (xs ? 1u << R1_XSRC : 0u);
-        for (int j = 0; j < d; ++j) {
-            const int iq = c.pos[c.succ_idx[e0 + j]];
-            const uint32_t lq = c.loc_b[iq];
-            if (j < ROW) record(1, i, lb, d, j, iq, lq, c.est_b[nb - iq] - c.est_b[nb - 1 - iq], c.erec[e0 + j], fl);
-            if (cross(1, pass_of(lq), pb)) c.x_b[atomicAdd(&s_x[1], 1)] = (uint32_t)iq | ((uint32_t)pb << 16);
-        }
-        if (d == 0) record(1, i, lb, 1, 0, -1, 0, 0, 0, fl | (1u << R1_NOEDGE));
+        Readers mine, part;
+        auto look = [&](Readers& r, int p, int e) { reader(1, r, p, pass_of(c.loc_b[c.link[e] & 0x7FFFu])); };
+        const bool read = on && b != c.entry;
+        edges(read ? c.est_f[i] : 0, read ? c.est_f[i + 1] : 0, [&](int e) { look(mine, pb, e); },
+              [&](int e, int l) { look(part, of(pb, l), e); }, [&](int l) { gather(mine, part, l); });
+        if (on) c.last_b[i] = (uint16_t)((uint32_t)mine.last | mine.xs);
+        const uint32_t fl = on ? flags_of(b, d) | (mine.xs ? 1u << R1_XSRC : 0u) : 0u;
+        auto crosses = [&](int iq, uint32_t lq, int p) {
+            if (cross(1, pass_of(lq), p)) c.x_b[atomicAdd(&s_x[1], 1)] = (uint32_t)iq | ((uint32_t)p << 16);
+        };
+        static_assert(WIDE >= ROW, "the records of a block are its own thread's");
+        edges(e0, e0 + d,
+              [&](int e) {
+                  const int j = e - e0, iq = c.pos[c.succ_idx[e]];
+                  const uint32_t lq = c.loc_b[iq];
+                  if (j < ROW) record(1, i, lb, d, j, iq, lq, c.est_b[nb - iq] - c.est_b[nb - 1 - iq], c.erec[e], fl);
+                  crosses(iq, lq, pb);
+              },
+              [&](int e, int l) {
+                  const int iq = c.pos[c.succ_idx[e]];
+                  crosses(iq, c.loc_b[iq], of(pb, l));
+              },
+              [](int) {});
+        if (on && d == 0) record(1, i, lb, 1, 0, -1, 0, 0, 0, fl | (1u << R1_NOEDGE));
     }
     __syncthreads();
     if (tid == 0) {
