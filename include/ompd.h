@@ -237,7 +237,8 @@ int ompd_analyze_batch(ompd_ctx* ctx, const ompd_cfg* cfgs, ompd_result* res, in
  * (each call rewrites what it reads, so nothing carries over): calls that
  * overlap on one GPU would race, so the library serialises them, across all
  * contexts of the process, for the whole call.  Results, errors and sweeps
- * are those of ompd_analyze_batch. */
+ * are those of ompd_analyze_batch (a batch that fits the array by the walk
+ * only takes the walk and reports its sweeps). */
 #define OMPD_NOALLOC_SCRATCH_MIB 256
 int ompd_analyze_batch_noalloc(ompd_ctx* ctx, const ompd_cfg* cfgs, ompd_result* res, int32_t n,
                                uint32_t flags, void* stream);

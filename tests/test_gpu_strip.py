@@ -77,3 +77,11 @@ def test_strip_alone(ctx, n_vars):
             for k in KEYS:
                 g = np.asarray(got[k])
                 assert np.array_equal(g, np.asarray(want[k]).reshape(g.shape)), (i, flags, k)
+
+
+def test_strip_sweeps_repeat(ctx):
+    """The sweeps reported do not depend on which wavefront of a strip is ahead."""
+    cfgs = [synth.c3_item(i) for i in range(8)] + [_chain(1500, 130, 3), _fan(40, 130, 4)]
+    runs = [[r["sweeps"] for r in ctx.analyze_batch(cfgs)] for _ in range(6)]
+    for again in runs[1:]:
+        assert np.array_equal(np.asarray(runs[0]), np.asarray(again))
