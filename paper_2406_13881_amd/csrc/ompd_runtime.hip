@@ -306,7 +306,8 @@ void ompd_settle_sched(DevCfg* h, int n, int n_cu, bool split)
     // and up to 8 wavefronts: a lone CFG of 66 blocks 163 / 185 / 257 / 257, of 779 blocks 579 / 579 /
     // 625 / 1060; 96 CFGs (242 strips) 1415 / 1795 / 3020 / 4420; 2048 CFGs of about 60 blocks (2377
     // strips) 1170 / 841 / 493 / 493.  1024 CFGs (4266 strips) at 200 blocks: up to 8 wavefronts
-    // 12.2 ms, 4 9.9 ms, 2 10.6 ms.
+    // 12.2 ms, 4 9.9 ms, 2 10.6 ms.  (All measured before cross links read the states of the round
+    // before, which adds 4-11 %.)
     const bool idle = strips <= n_cu;
     const int busy_per = (int)std::min<int64_t>(200, 32 * strips / std::max(n_cu, 1));
     int most = 1;

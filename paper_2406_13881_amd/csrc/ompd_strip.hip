@@ -1344,12 +1344,12 @@ __device__ __forceinline__ void after_avf(const DevCfg& c, const Strip& t, int n
 // registers (the inputs loaded ahead) leave room for two wavefronts per SIMD, whose visits then take
 // 0.4 us.  A batch's strips also wait for memory: each round reads a strip's arrays again (about 1 MB
 // for 4,000 blocks and 4 words), the resident ones exceed the last-level cache, and both strip
-// kernels move data at 3.1-3.7 TB/s (a copy: 4.9).  Rows of 8 lanes and 8 words per strip need a quarter
+// kernels move data at 3.3-3.8 TB/s (a copy: 4.9).  Rows of 8 lanes and 8 words per strip need a quarter
 // fewer passes but twice the arrays per strip: 1024 CFGs the same or slower (strip_b 8.0 -> 8.8 ms);
 // 4 wavefronts per SIMD with inputs loaded 3-4 passes ahead are no faster either.
 // Both strip kernels, before (the phase and pass kernels of the walk or of the old level schedule) ->
-// now: 66 blocks x 32 variables 0.55 -> 0.17 ms, 8002 x 1500 31 -> 2.6 ms, 16386 x
-// 2048 68 -> 5.2 ms, 1024 CFGs 76 -> 9.3 ms.
+// now: 66 blocks x 32 variables 0.55 -> 0.17 ms, 8002 x 1500 31 -> 2.8 ms, 16386 x
+// 2048 68 -> 5.7 ms, 1024 CFGs 76 -> 10.5 ms.
 extern "C" __global__ void __launch_bounds__(64 * STRIP_MAX_WAVES)
 ompd_k_strip_a(const DevCfg* __restrict__ cfgs, const Tile* __restrict__ tiles)
 {
