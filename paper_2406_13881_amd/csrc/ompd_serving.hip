@@ -53,6 +53,7 @@ struct Req {
     ompd_result dres{};
     ScratchOff so{};
     std::vector<Back> back;
+    int32_t want = 0;       // WANT_* bits of the outputs asked for, as `user` had them at submit
     size_t tab_bytes = 0;   // what the request adds to a step's launch tables
     int status = 0;
     std::string msg;   // what went wrong, when status != 0
@@ -141,7 +142,7 @@ static void launcher_main(ServingState* S)
             ompd_fill_devcfg(r->dcfg, r->dres, S->dev_base + r->dev_off + r->scratch_off, r->so, r->flags,
                              S->ctx->wait_ticks, h[i], nullptr);
             // (the device holds every output; only what the caller asked for is written)
-            h[i].want = ompd_want(*r->user) | (h[i].call ? WANT_NU_H | WANT_NU_D : 0);
+            h[i].want = r->want | (h[i].call ? WANT_NU_H | WANT_NU_D : 0);
         }
         ompd_settle_sched(h.data(), k, S->ctx->n_cu);
         PlanConfig pc;
@@ -449,6 +450,7 @@ extern "C" int ompd_submit(ompd_ctx* ctx, const ompd_cfg* cfg, ompd_result* res,
     d.summaries = o_sums != SIZE_MAX ? (const uint64_t*)(D + o_sums) : nullptr;
     d.scalar = o_sc != SIZE_MAX ? (const uint64_t*)(D + o_sc) : nullptr;
     r->dcfg = d;
+    r->want = ompd_want(*res);
     ompd_result& dr = r->dres;
     void* user_ptr[14] = {res->nu_host, res->nu_dev, res->ave_host, res->ave_dev, res->avf_host, res->avf_dev,
                           res->ins_entry_to_host, res->ins_entry_to_dev, res->ins_edge_to_host, res->ins_edge_to_dev,

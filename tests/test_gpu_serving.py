@@ -117,3 +117,24 @@ def test_serving_rejects_malformed_and_unknown_ticket():
     d = __import__("ctypes").c_int(0)
     assert ompd.lib().ompd_poll(ctx.h, 987654321, __import__("ctypes").byref(d)) == ompd.OMPD_E_UNKNOWN_TICKET
     ctx.close()
+
+
+def test_outputs_are_those_asked_for_at_submit():
+    """The output pointers count as they are at submit: a caller that clears or reuses its result
+    struct's pointers while the request waits still gets every array it asked for."""
+    import paper_2406_13881_amd as ompd
+    ctx = ompd.Context(0, 4 << 30)
+    try:
+        first = ompd.submit(ctx, synth.c2(0), want=("var_kind",))   # keeps the launcher waiting for a while
+        cfg = synth.c3_item(7, n_user=300, n_vars=130)
+        req = ompd.submit(ctx, cfg)
+        assert first.admitted and req.admitted
+        for name, _ in ompd._Res._fields_:
+            if name != "sweeps":
+                setattr(req._R, name, None)
+        out, ref = req.wait(), oracle.solve(cfg)
+        first.wait()
+        for k in ompd.OUTPUTS:
+            assert np.array_equal(out[k], np.asarray(ref[k]).reshape(out[k].shape)), k
+    finally:
+        ctx.close()
