@@ -778,7 +778,7 @@ struct Prog {
     std::vector<int32_t> sweeps;             // [nctx][6]
     // summary evaluation outputs (per procedure, 4 evaluations, nu/ave H/D)
     std::vector<uint64_t*> e_out;            // [4][4][nb][wd]
-    char* arena_items = nullptr;             // staging of kernel work items
+    char* arena_items = nullptr;             // [STAGE bytes] kernel work items
     std::vector<char> cap_valid;             // per context: a cap from the previous outer round exists
     // pinned staging: inputs on their way in, work items, results on their way out
     static constexpr size_t STAGE = (size_t)64 << 20;
@@ -805,28 +805,27 @@ struct Prog {
     }
 };
 
-// Launch a kernel over work items.  They go through the pinned staging buffer, so the host need not
-// wait; the stream orders the uses of the device copy.
+// Launch a kernel over work items, as many at a time as their place on the device (STAGE bytes)
+// holds.  They go through the pinned staging buffer, so the host need not wait; the stream orders the
+// uses of the device copy.
 template <typename T>
 int upload_items(Prog& G, const std::vector<T>& v, void (*k)(const T*, int), int threads)
 {
-    if (v.empty()) return OMPD_OK;
-    const size_t bytes = sizeof(T) * v.size();
-    if (bytes <= Prog::STAGE) {
+    constexpr size_t most = Prog::STAGE / sizeof(T);
+    for (size_t i = 0; i < v.size(); i += most) {
+        const size_t n = std::min(most, v.size() - i), bytes = sizeof(T) * n;
         if (G.stage_used + bytes > Prog::STAGE) {
             CK(hipStreamSynchronize(G.s));
             G.stage_used = 0;
         }
         char* at = G.stage + G.stage_used;
         G.stage_used += a256(bytes);
-        memcpy(at, v.data(), bytes);
+        memcpy(at, v.data() + i, bytes);
         CK(hipMemcpyAsync(G.arena_items, at, bytes, hipMemcpyHostToDevice, G.s));
-    } else
-        CK(hipMemcpyAsync(G.arena_items, v.data(), bytes, hipMemcpyHostToDevice, G.s));
-    const int grid = (int)std::min<size_t>(v.size(), 4096);
-    hipLaunchKernelGGL(k, dim3(grid), dim3(threads), 0, G.s, (const T*)G.arena_items, (int)v.size());
-    CK(hipGetLastError());
-    if (bytes > Prog::STAGE) CK(hipStreamSynchronize(G.s));
+        const int grid = (int)std::min<size_t>(n, 4096);
+        hipLaunchKernelGGL(k, dim3(grid), dim3(threads), 0, G.s, (const T*)G.arena_items, (int)n);
+        CK(hipGetLastError());
+    }
     return OMPD_OK;
 }
 
@@ -959,7 +958,7 @@ int setup(Prog& G)
         co[x].ctab = take(8 * ns * SUM_ROWS * wd);
         co[x].out = take(8 * (8 * nb * wd + 2 * ne * wd) + (size_t)P->procs[p].n_vars + 2 * nb + 64);
     }
-    const size_t oItems = take(64ull << 20);   // staging of kernel work items
+    const size_t oItems = take(Prog::STAGE);   // kernel work items
     if (hipHostMalloc((void**)&G.stage, Prog::STAGE, hipHostMallocDefault) != hipSuccess) {
         G.stage = nullptr;
         return ompd_fail(OMPD_E_NOMEM, "program: pinned staging buffer");

@@ -1,0 +1,89 @@
+"""CPU tests of the library's host code: libompd on a stand-in for the HIP runtime
+(tests/cpp/hip_standin.cpp), which checks every copy against the allocations, bounds the device
+memory, and counts kernels instead of running them.  Each test is a program of its own, so that the
+stand-in is the only runtime in the process."""
+import os
+import subprocess
+import sys
+import textwrap
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+PRELUDE = """
+import sys
+sys.modules["torch"] = None   # (it brings a HIP runtime of its own)
+sys.path.insert(0, %r)
+import ctypes, json
+from types import SimpleNamespace
+import numpy as np
+import paper_2406_13881_amd as ompd
+import synth
+lib = ompd.lib()
+hip = ctypes.CDLL("libamdhip64.so.7")
+hip.standin_first.restype = hip.standin_events.restype = ctypes.c_char_p
+hip.standin_live.restype = ctypes.c_size_t
+for f in ("launches", "items"):
+    getattr(hip, "standin_" + f).argtypes = [ctypes.c_char_p]
+    getattr(hip, "standin_" + f).restype = ctypes.c_long
+hip.standin_allocs.restype = hip.standin_violations.restype = ctypes.c_long
+hip.standin_budget.argtypes = [ctypes.c_size_t]
+hip.standin_fail_alloc.argtypes = [ctypes.c_long]
+
+def chain(n, n_vars, seed=1):
+    rng = np.random.default_rng(seed)
+    blocks = [(0, [], [])] + [(0, [int(rng.integers(0, n_vars))], []) for _ in range(n)] + [(0, [], [])]
+    return synth.from_edges(blocks, [(b, b + 1, 0) for b in range(n + 1)], n_vars)[0]
+""" % ROOT
+
+
+@pytest.fixture(scope="module")
+def standin(tmp_path_factory):
+    out = tmp_path_factory.mktemp("hip")
+    so = out / "libamdhip64.so.7"
+    subprocess.run(["g++", "-std=c++17", "-O1", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include",
+                    os.path.join(ROOT, "tests", "cpp", "hip_standin.cpp"), "-Wl,-soname,libamdhip64.so.7",
+                    "-o", str(so)], check=True)
+    return str(out)
+
+
+def run(standin, body):
+    env = dict(os.environ, LD_LIBRARY_PATH=standin)
+    code = PRELUDE + textwrap.dedent(body) + "\nassert hip.standin_violations() == 0, hip.standin_first()\n"
+    p = subprocess.run([sys.executable, "-c", code], env=env, capture_output=True, text=True, timeout=300)
+    assert p.returncode == 0, p.stdout + p.stderr
+
+
+def test_calls_stay_inside_their_allocations_and_give_them_back(standin):
+    run(standin, """
+        ctx = ompd.Context(0, 256 << 20)
+        ctx.analyze_batch([synth.c1(0), synth.c1(1), synth.c3_item(2)])
+        ctx.analyze_program(synth.c4(20))
+        r = ompd.submit(ctx, synth.c1(3))
+        assert r.admitted
+        r.wait()
+        ctx.close()
+        assert hip.standin_live() == 0, hip.standin_live()
+    """)
+
+
+def test_program_work_lists_larger_than_their_buffer(standin):
+    """96 call sites in each of three procedures in a row give 96^3 call-table items of 80 bytes,
+    more than the 64 MiB their buffers hold: every item still reaches the kernel, and no copy leaves
+    an allocation."""
+    run(standin, """
+        n = 96
+        procs = [chain(n, 2, seed) for seed in range(4)]
+        prog = SimpleNamespace(procs=procs, n_globals=1, roots=[0],
+                               call_proc=[p for p in range(3) for _ in range(n)],
+                               call_block=[1 + k for _ in range(3) for k in range(n)],
+                               callee=[p + 1 for p in range(3) for _ in range(n)])
+        ctx = ompd.Context(0, 64 << 20)
+        got = ctx.analyze_program(prog, want=("after_dev",))
+        assert len(got["contexts"]) == 1 + n + 2 * n * n
+        # the summaries' tables, then those of every context, in the liveness and in the validity system
+        per_round = 3 * n + 2 * (n + n * n + n * n * n)
+        assert hip.standin_items(b"k_calltab") == got["rounds"] * per_round, hip.standin_items(b"k_calltab")
+        ctx.close()
+    """)
