@@ -69,6 +69,17 @@ int ompd_fail(int code, const std::string& msg)
             return ompd_fail(OMPD_E_DEVICE, std::string(#x) + ": " + hipGetErrorString(e_));    \
     } while (0)
 
+// An allocation: device memory that there is not is OMPD_E_NOMEM, so that a caller can free some
+// and call again.
+#define CK_MALLOC(x)                                                                            \
+    do {                                                                                        \
+        hipError_t e_ = (x);                                                                    \
+        if (e_ != hipSuccess) {                                                                 \
+            (void)hipGetLastError();                                                            \
+            return ompd_fail(OMPD_E_NOMEM, std::string(#x) + ": " + hipGetErrorString(e_));     \
+        }                                                                                       \
+    } while (0)
+
 static inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 static void drop_graphs(ompd_plan* p);
 
@@ -617,12 +628,13 @@ int ompd_plan_build(ompd_ctx* ctx, const ompd_cfg* cfgs, ompd_result* res, int32
         if (e != hipSuccess) { ompd_plan_destroy(p); return ompd_fail(OMPD_E_DEVICE, hipGetErrorString(e)); }
     }
     p->max_nb = max_nb;
-    e = hipMalloc(&p->d_cfgs, sizeof(DevCfg) * std::max(n, 1));   // (filled by ompd_plan_retile)
-    if (e != hipSuccess) { ompd_plan_destroy(p); return ompd_fail(OMPD_E_DEVICE, hipGetErrorString(e)); }
     p->h_info.assign((size_t)n * INFO_WORDS, 0);
-    e = hipMalloc(&p->d_info, 4 * INFO_WORDS * (size_t)std::max(n, 1));
-    if (e != hipSuccess) { ompd_plan_destroy(p); return ompd_fail(OMPD_E_NOMEM, hipGetErrorString(e)); }
-    int rc = ompd_plan_retile(p, p->cfg);
+    auto tables = [&]() -> int {
+        CK_MALLOC(hipMalloc(&p->d_cfgs, sizeof(DevCfg) * std::max(n, 1)));   // (filled by ompd_plan_retile)
+        CK_MALLOC(hipMalloc(&p->d_info, 4 * INFO_WORDS * (size_t)std::max(n, 1)));
+        return ompd_plan_retile(p, p->cfg);
+    };
+    const int rc = tables();
     if (rc) { ompd_plan_destroy(p); return rc; }
     CK(hipEventCreate(&p->ev0));
     CK(hipEventCreate(&p->ev1));
@@ -657,8 +669,8 @@ int ompd_plan_retile(ompd_plan* p, const PlanConfig& pc)
     p->n_items = (int)sh.items.size();
     if (p->d_tiles) { (void)hipFree(p->d_tiles); p->d_tiles = nullptr; }
     if (p->d_items) { (void)hipFree(p->d_items); p->d_items = nullptr; }
-    CK(hipMalloc(&p->d_tiles, sizeof(Tile) * std::max(p->n_tiles, 1)));
-    CK(hipMalloc(&p->d_items, sizeof(EdgeItem) * std::max(p->n_items, 1)));
+    CK_MALLOC(hipMalloc(&p->d_tiles, sizeof(Tile) * std::max(p->n_tiles, 1)));
+    CK_MALLOC(hipMalloc(&p->d_items, sizeof(EdgeItem) * std::max(p->n_items, 1)));
     if (p->n_tiles)
         CK(hipMemcpy(p->d_tiles, sh.tiles.data(), sizeof(Tile) * p->n_tiles, hipMemcpyHostToDevice));
     if (p->n_items)

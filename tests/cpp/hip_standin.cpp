@@ -17,6 +17,7 @@ std::mutex mu;
 std::map<char*, size_t> dev;        // device allocations
 size_t live = 0, budget = (size_t)64 << 30;
 long violations = 0, allocs = 0, fail_at = -1;
+std::vector<size_t> sizes;          // of every allocation so far
 std::string first;
 struct Kernel { long launches = 0, items = 0; };
 std::map<const void*, std::string> names;
@@ -72,6 +73,7 @@ void standin_budget(size_t bytes) { budget = bytes; }
 void standin_fail_alloc(long k) { fail_at = k < 0 ? -1 : allocs + k; }   // the k-th allocation from now fails
 size_t standin_live() { return live; }
 long standin_allocs() { return allocs; }
+size_t standin_alloc_size(long k) { return sizes[k]; }
 long standin_violations() { return violations; }
 const char* standin_first() { return first.c_str(); }
 const char* standin_events() { return events.c_str(); }
@@ -91,6 +93,7 @@ void standin_clear_kernels() { kernels.clear(); }
 hipError_t hipMalloc(void** p, size_t n)
 {
     std::lock_guard<std::mutex> g(mu);
+    sizes.push_back(n);
     if (allocs++ == fail_at || live + n > budget) return hipErrorOutOfMemory;
     char* c = (char*)calloc(1, n ? n : 1);
     dev[c] = n;

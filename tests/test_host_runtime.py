@@ -23,13 +23,13 @@ import synth
 lib = ompd.lib()
 hip = ctypes.CDLL("libamdhip64.so.7")
 hip.standin_first.restype = hip.standin_events.restype = ctypes.c_char_p
-hip.standin_live.restype = ctypes.c_size_t
+hip.standin_live.restype = hip.standin_alloc_size.restype = ctypes.c_size_t
 for f in ("launches", "items"):
     getattr(hip, "standin_" + f).argtypes = [ctypes.c_char_p]
     getattr(hip, "standin_" + f).restype = ctypes.c_long
 hip.standin_allocs.restype = hip.standin_violations.restype = ctypes.c_long
 hip.standin_budget.argtypes = [ctypes.c_size_t]
-hip.standin_fail_alloc.argtypes = [ctypes.c_long]
+hip.standin_fail_alloc.argtypes = hip.standin_alloc_size.argtypes = [ctypes.c_long]
 
 def chain(n, n_vars, seed=1):
     rng = np.random.default_rng(seed)
@@ -85,5 +85,27 @@ def test_program_work_lists_larger_than_their_buffer(standin):
         # the summaries' tables, then those of every context, in the liveness and in the validity system
         per_round = 3 * n + 2 * (n + n * n + n * n * n)
         assert hip.standin_items(b"k_calltab") == got["rounds"] * per_round, hip.standin_items(b"k_calltab")
+        ctx.close()
+    """)
+
+
+def test_every_failed_allocation_is_reported_as_one(standin):
+    """Each device allocation of a call fails in turn: the call succeeds all the same or returns
+    OMPD_E_NOMEM, and gives back what it had."""
+    run(standin, """
+        cfgs, prog = [synth.c1(0), synth.c3_item(2)], synth.c4(12)
+        ctx = ompd.Context(0, 64 << 20)
+        for call in (lambda: ctx.analyze_batch(cfgs), lambda: ctx.analyze_program(prog)):
+            before = hip.standin_allocs()
+            call()
+            n = hip.standin_allocs() - before
+            for k in range(n):
+                hip.standin_fail_alloc(k)
+                try:
+                    call()
+                except ompd.OmpdError as e:
+                    assert e.code == ompd.OMPD_E_NOMEM, (k, e)
+                hip.standin_fail_alloc(-1)
+                assert hip.standin_live() == 0, k
         ctx.close()
     """)
