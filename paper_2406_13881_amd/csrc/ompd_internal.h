@@ -65,6 +65,7 @@ struct PlanConfig {
     // SCHED_LEVEL; CFGs whose schedule the plan's flags name keep it
     int bucket_sched[OMPD_SCHED_BUCKETS] = {-1, -1, -1, -1, -1};
     int only_bucket = -1;   // autotuning: solve only the CFGs of this bucket (-1: all)
+    bool roomy = false;     // fail rather than take a smaller layout where memory is short
     bool first_half = false; // the caller reads next use and eager validity only (strips stop there)
 };
 // Size bucket of a CFG for the schedule choice: blocks below 256, 1,024, 4,096, 16,384, or more.

@@ -786,7 +786,8 @@ struct Prog {
     size_t stage_used = 0;
     // Plans of the batches solved so far (the fixed points solve the same sets of procedures and
     // contexts again and again, with the same buffers): what a batch costs besides its kernels is
-    // building its plan and ingesting its CFGs.  Bounded; the oldest go first.
+    // building its plan and ingesting its CFGs.  At most KEPT_BYTES of scratch, the oldest go first; a
+    // plan with more is not kept.
     struct Kept { std::vector<int> key; ompd_plan* plan; size_t bytes; };
     static constexpr size_t KEPT_BYTES = (size_t)1 << 30;
     std::deque<Kept> kept;
@@ -839,6 +840,7 @@ int run_batch(Prog& G, std::vector<int> key, Make&& make, uint32_t flags, bool f
     for (const Prog::Kept& k : G.kept)
         if (k.key == key) { plan = k.plan; break; }
     int rc = OMPD_OK;
+    bool keep = true;
     if (plan) rc = ompd_plan_rerun_locked(plan, G.s);
     else {
         std::vector<ompd_cfg> cfgs;
@@ -847,24 +849,28 @@ int run_batch(Prog& G, std::vector<int> key, Make&& make, uint32_t flags, bool f
         PlanConfig pc;
         pc.use_graph = false;   // (a few runs: capturing a graph would not pay)
         pc.first_half = first_half && !(G.flags >> 16);
-        auto build = [&]() {
-            return ompd_plan_build(G.ctx, cfgs.data(), res.data(), (int32_t)cfgs.size(),
-                                   flags | OMPD_F_DEVICE_PTRS | G.flags, pc, &plan);
-        };
-        rc = build();
-        if (rc == OMPD_E_NOMEM && !G.kept.empty()) {
-            while (!G.kept.empty()) G.drop_oldest();
-            rc = build();
+        // (where memory is short the kept plans go, one by one, before this one takes a smaller layout
+        // or fails)
+        for (;;) {
+            pc.roomy = !G.kept.empty();
+            rc = ompd_plan_build(G.ctx, cfgs.data(), res.data(), (int32_t)cfgs.size(),
+                                 flags | OMPD_F_DEVICE_PTRS | G.flags, pc, &plan);
+            if (rc != OMPD_E_NOMEM || G.kept.empty()) break;
+            G.drop_oldest();
         }
         if (rc) return rc;
-        while (!G.kept.empty() && G.kept_bytes + plan->scratch_bytes > Prog::KEPT_BYTES) G.drop_oldest();
-        G.kept.push_back(Prog::Kept{std::move(key), plan, plan->scratch_bytes});
-        G.kept_bytes += plan->scratch_bytes;
+        keep = plan->scratch_bytes <= Prog::KEPT_BYTES;
+        if (keep) {
+            while (G.kept_bytes + plan->scratch_bytes > Prog::KEPT_BYTES) G.drop_oldest();
+            G.kept.push_back(Prog::Kept{std::move(key), plan, plan->scratch_bytes});
+            G.kept_bytes += plan->scratch_bytes;
+        }
         rc = ompd_plan_run_locked(plan, G.s);
     }
     if (rc == OMPD_OK) rc = ompd_plan_collect(plan, nullptr);
     res = plan->res;
     G.solves += (int64_t)plan->n;
+    if (!keep) ompd_plan_destroy(plan);
     return rc;
 }
 

@@ -610,6 +610,7 @@ int ompd_plan_build(ompd_ctx* ctx, const ompd_cfg* cfgs, ompd_result* res, int32
         if (e == hipSuccess) break;
         p->scratch = nullptr;
         (void)hipGetLastError();
+        if (pc.roomy) break;
     }
     p->scratch_bytes = total;
     if (e != hipSuccess) {

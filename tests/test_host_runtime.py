@@ -109,3 +109,23 @@ def test_every_failed_allocation_is_reported_as_one(standin):
                 assert hip.standin_live() == 0, k
         ctx.close()
     """)
+
+
+def test_kept_plans_give_way_to_the_next(standin):
+    """A program in memory that holds its arena and any one of its batches, but not several: plans
+    kept from earlier batches go before the next one takes a smaller layout (the walk's ingest would
+    show it) or fails."""
+    run(standin, """
+        prog = synth.c4(60)
+        ctx = ompd.Context(0, 64 << 20)
+        first = hip.standin_allocs()
+        ctx.analyze_program(prog)
+        size = [hip.standin_alloc_size(k) for k in range(first, hip.standin_allocs())]
+        assert hip.standin_launches(b"ompd_k_prep") == 0
+        small = max(x for x in size if x < max(size[1:]) // 4)   # tables
+        hip.standin_budget(size[0] + max(size[1:]) + 4 * small)   # size[0]: the arena
+        ctx.analyze_program(prog)
+        assert hip.standin_launches(b"ompd_k_prep") == 0
+        ctx.close()
+        assert hip.standin_live() == 0
+    """)
