@@ -644,39 +644,48 @@ int ompd_plan_build(ompd_ctx* ctx, const ompd_cfg* cfgs, ompd_result* res, int32
     return OMPD_OK;
 }
 
-// (Re)build tiles and launch shapes for a configuration (drops captured graphs).
+// (Re)build tiles and launch shapes for a configuration (drops captured graphs).  The plan changes
+// only once everything new is in device memory and its last run is over: on an error it stays as it
+// was.
 int ompd_plan_retile(ompd_plan* p, const PlanConfig& pc)
 {
     ompd_ctx* ctx = p->ctx;
     // the schedule of each CFG the plan's flags leave open: the bucket's choice, else the rule
-    {
-        for (DevCfg& d : p->h_cfgs) {
-            if (p->flags & (OMPD_F_SCHED_LEVEL | OMPD_F_SCHED_WALK)) break;
-            const int want = pc.bucket_sched[ompd_sched_bucket(d.nb)];
-            d.sched_rule = want < 0;
-            if (want >= 0) d.sched = d.strip_ok ? want : SCHED_WALK;
-        }
-        ompd_settle_sched(p->h_cfgs.data(), p->n, ctx->n_cu, pc.split);
-        if (p->n && p->d_cfgs)
-            CK(hipMemcpy(p->d_cfgs, p->h_cfgs.data(), sizeof(DevCfg) * p->n, hipMemcpyHostToDevice));
+    std::vector<DevCfg> cfgs = p->h_cfgs;
+    for (DevCfg& d : cfgs) {
+        if (p->flags & (OMPD_F_SCHED_LEVEL | OMPD_F_SCHED_WALK)) break;
+        const int want = pc.bucket_sched[ompd_sched_bucket(d.nb)];
+        d.sched_rule = want < 0;
+        if (want >= 0) d.sched = d.strip_ok ? want : SCHED_WALK;
     }
+    ompd_settle_sched(cfgs.data(), p->n, ctx->n_cu, pc.split);
     Shape sh;
-    int rc = ompd_make_shape(ctx, p->h_cfgs, pc, sh);
+    int rc = ompd_make_shape(ctx, cfgs, pc, sh);
     if (rc) return rc;
+    struct Tables {
+        Tile* tiles = nullptr;
+        EdgeItem* items = nullptr;
+        ~Tables()
+        {
+            if (tiles) (void)hipFree(tiles);
+            if (items) (void)hipFree(items);
+        }
+    } t;
+    CK_MALLOC(hipMalloc(&t.tiles, sizeof(Tile) * std::max<size_t>(sh.tiles.size(), 1)));
+    CK_MALLOC(hipMalloc(&t.items, sizeof(EdgeItem) * std::max<size_t>(sh.items.size(), 1)));
+    if (!sh.tiles.empty()) CK(hipMemcpy(t.tiles, sh.tiles.data(), sizeof(Tile) * sh.tiles.size(), hipMemcpyHostToDevice));
+    if (!sh.items.empty()) CK(hipMemcpy(t.items, sh.items.data(), sizeof(EdgeItem) * sh.items.size(), hipMemcpyHostToDevice));
+    if (p->ev2) CK(hipEventSynchronize(p->ev2));   // (the last run, on whatever stream, reads the descriptors)
+    if (p->n) CK(hipMemcpy(p->d_cfgs, cfgs.data(), sizeof(DevCfg) * p->n, hipMemcpyHostToDevice));
+    drop_graphs(p);
+    std::swap(p->d_tiles, t.tiles);
+    std::swap(p->d_items, t.items);
+    p->h_cfgs.swap(cfgs);
     p->cfg = pc;
     p->dims = sh.dims;
-    p->h_tiles = sh.tiles;
     p->n_tiles = (int)sh.tiles.size();
     p->n_items = (int)sh.items.size();
-    if (p->d_tiles) { (void)hipFree(p->d_tiles); p->d_tiles = nullptr; }
-    if (p->d_items) { (void)hipFree(p->d_items); p->d_items = nullptr; }
-    CK_MALLOC(hipMalloc(&p->d_tiles, sizeof(Tile) * std::max(p->n_tiles, 1)));
-    CK_MALLOC(hipMalloc(&p->d_items, sizeof(EdgeItem) * std::max(p->n_items, 1)));
-    if (p->n_tiles)
-        CK(hipMemcpy(p->d_tiles, sh.tiles.data(), sizeof(Tile) * p->n_tiles, hipMemcpyHostToDevice));
-    if (p->n_items)
-        CK(hipMemcpy(p->d_items, sh.items.data(), sizeof(EdgeItem) * p->n_items, hipMemcpyHostToDevice));
-    drop_graphs(p);
+    p->h_tiles.swap(sh.tiles);
     return OMPD_OK;
 }
 

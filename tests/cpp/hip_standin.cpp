@@ -129,6 +129,9 @@ hipError_t hipLaunchKernel(const void* f, dim3, dim3, void** args, size_t, hipSt
     Kernel& k = kernels[n];
     ++k.launches;
     if (n.find("CallTabItem") != std::string::npos) k.items += *(int*)args[1];
+    for (const char* part : {"k_nu", "k_ave", "k_mayp", "k_later", "k_live", "k_avf", "k_post", "k_varkind", "k_solve",
+                             "k_strip", "k_tin", "k_tmid", "k_tout"})   // (descriptors, tiles or items, ...)
+        if (n.find(part) != std::string::npos && !inside(*(void**)args[1], 16)) violate(n + " without its table");
     events += "launch ";
     return hipSuccess;
 }
@@ -179,7 +182,7 @@ hipError_t hipEventCreate(hipEvent_t* e) { *e = (hipEvent_t)malloc(1); return hi
 hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) { *e = (hipEvent_t)malloc(1); return hipSuccess; }
 hipError_t hipEventDestroy(hipEvent_t e) { free(e); return hipSuccess; }
 hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }
-hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
+hipError_t hipEventSynchronize(hipEvent_t) { note("sync"); return hipSuccess; }
 static float elapsed = 1.0f;
 hipError_t hipEventElapsedTime(float* ms, hipEvent_t, hipEvent_t) { *ms = elapsed; return hipSuccess; }
 hipError_t hipFuncGetAttributes(hipFuncAttributes* a, const void*) { memset(a, 0, sizeof *a); return hipSuccess; }

@@ -31,6 +31,25 @@ hip.standin_allocs.restype = hip.standin_violations.restype = ctypes.c_long
 hip.standin_budget.argtypes = [ctypes.c_size_t]
 hip.standin_fail_alloc.argtypes = hip.standin_alloc_size.argtypes = [ctypes.c_long]
 
+def on_device(a):
+    p = ctypes.c_void_p()
+    a = np.ascontiguousarray(a)
+    assert hip.hipMalloc(ctypes.byref(p), ctypes.c_size_t(a.nbytes)) == 0
+    assert hip.hipMemcpy(p, ctypes.c_void_p(a.ctypes.data), ctypes.c_size_t(a.nbytes), 1) == 0
+    return p.value
+
+def resident(ctx, cfgs, flags=0):
+    # a plan of CFGs in device memory that asks for the map kinds and a label
+    D, R = [], []
+    for c in cfgs:
+        D.append(ompd.DeviceCFG(n_blocks=c.n_blocks, n_edges=len(c.succ_idx), n_vars=c.n_vars, entry=c.entry, exit=c.exit,
+                                succ_ptr=on_device(c.succ_ptr), succ_idx=on_device(c.succ_idx),
+                                edge_kind=on_device(c.edge_kind), space=on_device(c.space),
+                                read_bits=on_device(c.R), write_bits=on_device(c.W)))
+        R.append(ompd.DeviceResult(var_kind=on_device(np.zeros(c.n_vars, np.uint8)),
+                                   after_dev=on_device(np.zeros(c.n_blocks, np.uint8))))
+    return ompd.Plan(ctx, D, R, flags)
+
 def chain(n, n_vars, seed=1):
     rng = np.random.default_rng(seed)
     blocks = [(0, [], [])] + [(0, [int(rng.integers(0, n_vars))], []) for _ in range(n)] + [(0, [], [])]
@@ -128,4 +147,38 @@ def test_kept_plans_give_way_to_the_next(standin):
         assert hip.standin_launches(b"ompd_k_prep") == 0
         ctx.close()
         assert hip.standin_live() == 0
+    """)
+
+
+def test_a_plan_that_cannot_be_reconfigured_stays_as_it_was(standin):
+    """When an allocation of a reconfiguration fails the plan keeps its configuration and its tables,
+    and still runs; a reconfiguration waits for the plan's last run before it changes anything."""
+    run(standin, """
+        ctx = ompd.Context(0, 64 << 20)
+        plan = resident(ctx, [synth.c1(0), synth.c3_item(2)])
+        plan.run()
+        was = plan.describe()
+        for change in (lambda: plan.set_schedule([0] * 5), lambda: plan.configure(8192, 2), lambda: plan.split_kernels(False)):
+            n = hip.standin_allocs()
+            change()
+            n = hip.standin_allocs() - n
+            plan.set_schedule([-1] * 5)
+            plan.split_kernels(True)
+            plan.configure(0, 0)
+            plan.run()
+            for k in range(n):
+                hip.standin_fail_alloc(k)
+                try:
+                    change()
+                    assert False, "the allocation did not fail"
+                except ompd.OmpdError as e:
+                    assert e.code == ompd.OMPD_E_NOMEM, e
+                hip.standin_fail_alloc(-1)
+                assert plan.describe() == was, (was, plan.describe())
+                plan.run()
+        hip.standin_clear_events()
+        plan.run()
+        plan.set_schedule([0] * 5)
+        events = hip.standin_events().decode().split()
+        assert events[-2:] == ["sync", "memcpy"], events   # the descriptors, which the run reads
     """)
