@@ -68,7 +68,9 @@ enum { OMPD_MAP_TO = 1, OMPD_MAP_FROM = 2, OMPD_MAP_ALLOC = 4, OMPD_FIRSTPRIVATE
 #define OMPD_F_SUMMARY (1u << 2)          /* procedure-summary evaluation: the entry boundary may
                                              leave variables valid in neither space            */
 #define OMPD_F_TILE_KERNEL (1u << 3)      /* one persistent kernel runs every phase of a tile
-                                             (same results) instead of one kernel per phase */
+                                             (same results) instead of one kernel per phase, for
+                                             CFGs on the walk: those whose schedule no flag names
+                                             are where the launch fills the GPU, but for the largest */
 /* Schedule of the sweeps (results do not depend on it).  WALK: one block
  * after another in block order, the states of recent blocks kept in LDS
  * (15 words of variables per wavefront).  LEVEL: the blocks sorted by level

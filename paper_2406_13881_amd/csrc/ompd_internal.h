@@ -135,7 +135,8 @@ inline size_t ompd_transpose_items(size_t nb, size_t ne, size_t wd)
 int ompd_strip_rows(const ompd_cfg* g, int n);
 // Settle the schedule of each CFG of a launch (a CFG whose schedule the caller names, or that the
 // strips cannot hold, keeps the walk or the strips; the others take the strips, or the walk when
-// the launch asks for the per-tile kernel), and the shape of its strips.
+// a launch that fills the GPU asks for the per-tile kernel), and the shape of its strips.
+constexpr int STRIP_ANYWAY_BLOCKS = 12288;   // ... and the CFG has fewer blocks than this
 void ompd_settle_sched(ompd::DevCfg* h, int n, int n_cu, bool split = true);
 // Default bound of a kernel wait without progress (the longest legitimate wait is one step of
 // the other wavefront, microseconds).

@@ -302,12 +302,24 @@ void ompd_settle_sched(DevCfg* h, int n, int n_cu, bool split)
     for (int i = 0; i < n; ++i) order[i] = i;
     std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return h[a].nb > h[b].nb; });
     for (int i = 0; i < n; ++i) h[i].by_size = order[i];
+    auto strips_of = [](const DevCfg& d) -> int64_t { return (d.wd + d.units) / d.units; };
     int64_t strips = 0;
-    for (int i = 0; i < n; ++i) {
-        DevCfg& d = h[i];
-        if (d.sched_rule) d.sched = split && d.strip_ok ? SCHED_LEVEL : SCHED_WALK;
-        if (d.sched == SCHED_LEVEL) strips += (d.wd + d.units) / d.units;
-    }
+    for (int i = 0; i < n; ++i)
+        if (h[i].sched_rule ? h[i].strip_ok : h[i].sched == SCHED_LEVEL) strips += strips_of(h[i]);
+    // Who asks for the per-tile kernel gets it, on the walk, where the launch fills the GPU.  One that
+    // leaves it idle, and a large CFG, take the strips all the same (us, strips / per-tile kernel alone:
+    // 66 blocks 240 / 573, 2002 blocks x 300 variables 1,190 / 16,300, 14002 x 300 4,540 / 118,500).
+    if (!split) {
+        const bool room = strips <= n_cu;
+        strips = 0;
+        for (int i = 0; i < n; ++i) {
+            DevCfg& d = h[i];
+            if (d.sched_rule) d.sched = d.strip_ok && (room || d.nb >= STRIP_ANYWAY_BLOCKS) ? SCHED_LEVEL : SCHED_WALK;
+            if (d.sched == SCHED_LEVEL) strips += strips_of(d);
+        }
+    } else
+        for (int i = 0; i < n; ++i)
+            if (h[i].sched_rule) h[i].sched = h[i].strip_ok ? SCHED_LEVEL : SCHED_WALK;
     // Blocks per wavefront: the fewer, the shorter a strip's chain of passes, and the more rounds
     // until what one wavefront changed has reached the others.  While the GPU has room for every
     // strip at once (a workgroup each) 32 blocks and up to 8 wavefronts are best; where strips queue

@@ -182,3 +182,27 @@ def test_a_plan_that_cannot_be_reconfigured_stays_as_it_was(standin):
         events = hip.standin_events().decode().split()
         assert events[-2:] == ["sync", "memcpy"], events   # the descriptors, which the run reads
     """)
+
+
+def test_per_tile_kernel_where_the_launch_fills_the_gpu(standin):
+    """OMPD_F_TILE_KERNEL and a plan's split_kernels(False): the per-tile kernel runs on the walk,
+    which a launch that leaves the GPU idle and a large CFG do not take unless the caller names it."""
+    run(standin, """
+        ctx = ompd.Context(0, 64 << 20)
+        small, big = synth.c1(0), chain(13000, 2)
+        def kernels(f):
+            hip.standin_clear_kernels()
+            f()
+            return [hip.standin_launches(k) > 0 for k in (b"k_solve", b"k_strip_b", b"k_post_avf")]
+        T, W, L = ompd.F_TILE_KERNEL, ompd.F_SCHED_WALK, ompd.F_SCHED_LEVEL
+        solve = lambda cfgs, flags: kernels(lambda: ctx.analyze_batch(cfgs, flags=flags, want=("after_dev",)))
+        assert solve([small], T) == [False, True, False]
+        assert solve([small], T | W) == [True, False, False]
+        assert solve([small] * 300, T) == [True, False, False]
+        assert solve([small] * 300, T | L) == [False, True, False]
+        assert solve([small] * 300 + [big], T) == [False, True, True]   # both schedules: a kernel per phase
+        assert solve([small] * 300, 0) == [False, True, False]
+        plan = resident(ctx, [small] * 2)
+        plan.split_kernels(False)
+        assert kernels(plan.run) == [False, True, False]
+    """)
