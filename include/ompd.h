@@ -78,8 +78,8 @@ enum { OMPD_MAP_TO = 1, OMPD_MAP_FROM = 2, OMPD_MAP_ALLOC = 4, OMPD_FIRSTPRIVATE
  * up to four words of variables per workgroup, whose wavefronts share the
  * levels (as many as an idle GPU has room for).  Neither flag: by level, with
  * as many wavefronts per workgroup as the launch leaves room for.  CFGs of
- * more than 32,000 blocks, of 65,535 edges or more, and those whose strips
- * do not fit in the scratch they are given take the walk. */
+ * more than 32,000 blocks or 2^24 edges, and those whose strips do not fit in
+ * the scratch they are given, take the walk. */
 #define OMPD_F_SCHED_LEVEL (1u << 4)
 #define OMPD_F_SCHED_WALK (1u << 5)
 /* Placement variants (section "Data-Flow Analysis", the loop rule, and

@@ -108,6 +108,7 @@ struct DevCfg {
     int32_t spread;             // the launch leaves compute units idle: fewer blocks per wavefront
     int32_t waves;              // wavefronts per strip workgroup
     int32_t strip_ok;           // host side: the strips can hold the CFG
+    int32_t by_rows;            // more edge entries than the 16 bits of a lane record hold: they hold its row's
     int32_t want;               // WANT_* bits: the block and edge outputs the caller asked for
     uint64_t *p_rw;             // reads and writes
     uint64_t *p_1;              // states: next use; delayed copies; refinement; final validity
@@ -118,6 +119,7 @@ struct DevCfg {
     uint32_t *rec_sf, *rec_sb;  // [passes][4 / units][16] lane records (two words), forward and backward
     uint32_t *link;             // [ne + 1] edges by the block they enter: positions of their ends, loop entry
     int32_t *eid, *erec;        // [ne + 1] edge of each entry of `link`, [ne] the entry of each edge
+    int32_t* ebwd;              // [ne + 1] (rows only) the entry of each edge in the backward order
     uint32_t *x_f, *x_b;        // cross links: neighbour position | reader's pass << 16
     int32_t *est_f, *est_b;     // [nb + 1] first edge into each position, out of each position from the last
     uint32_t *loc_f, *loc_b;    // [nb] pass of a position | its first lane << 16
@@ -151,8 +153,11 @@ constexpr size_t strip_lds(int nb, int waves)
 {
     return (size_t)waves * STRIP_RING * 1024 + 8 * (size_t)strip_bit_words(nb) + 4 * STRIP_CTL_WORDS;
 }
-// most blocks of a CFG on the strip schedule (positions are 15-bit numbers)
-constexpr int STRIP_MAX_BLOCKS = 32000;
+// most blocks of a CFG on the strip schedule (positions are 15-bit numbers), and most edges (the byte
+// offsets of four words' edge arrays are 32-bit ones)
+constexpr int STRIP_MAX_BLOCKS = 32000, STRIP_MAX_EDGES = 1 << 24;
+// edges from which a record no longer holds its own entry (entries are 16-bit numbers there)
+constexpr int STRIP_ROW_EDGES = 65535;
 // units of a strip: as many as a pass of narrow levels fills; a large CFG has wider levels, which
 // fill a pass with fewer units
 constexpr int strip_units(int nb, int wd) { return nb >= 10000 || wd < 1 ? 1 : wd < 3 ? 2 : 4; }

@@ -47,9 +47,9 @@ struct LaunchDims {
     int prep_threads = 256;      // threads of the strip ingest
     size_t lds_prep = 0;         // LDS of the strip ingest (the largest CFG's peel that fits)
     // launches of each strip kernel: consecutive strip tiles whose workgroups have the same number
-    // of wavefronts
-    struct Bucket { int first, n, waves; size_t lds; };
-    static constexpr int MAX_BUCKETS = 6;
+    // of wavefronts and whose records hold edge entries in the same way
+    struct Bucket { int first, n, waves, by_rows; size_t lds; };
+    static constexpr int MAX_BUCKETS = 8;
     int n_buckets = 0;
     bool first_half = false;     // the strips stop after eager validity
     Bucket bucket[MAX_BUCKETS] = {};
@@ -112,7 +112,7 @@ struct ScratchOff {
     // the strips' arrays, in the same bytes (strip: the CFG can take the strip schedule)
     bool strip;
     int rows;    // rows of a pass its lane records have room for
-    size_t s_rw, s_1, s_2, s_3, s_g, s_b, s_recf, s_recb, s_link, s_eid, s_erec, s_xf, s_xb, s_estf, s_estb, s_locf,
+    size_t s_rw, s_1, s_2, s_3, s_g, s_b, s_recf, s_recb, s_link, s_eid, s_erec, s_ebwd, s_xf, s_xb, s_estf, s_estb, s_locf,
         s_locb, s_kc, s_lorder, s_loff, s_pos, s_lastf, s_lastb, s_facts, s_hdr;
     // both schedules
     size_t nu, ave, ie, ig, avf, vk, bnd, fp, info;

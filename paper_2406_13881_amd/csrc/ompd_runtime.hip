@@ -35,6 +35,7 @@ extern "C" __global__ void ompd_k_tin(const DevCfg*, const EdgeItem*);
 extern "C" __global__ void ompd_k_strip_a(const DevCfg*, const Tile*);
 extern "C" __global__ void ompd_k_tmid(const DevCfg*, const EdgeItem*);
 extern "C" __global__ void ompd_k_strip_b(const DevCfg*, const Tile*);
+extern "C" __global__ void ompd_k_strip_b_rows(const DevCfg*, const Tile*);
 extern "C" __global__ void ompd_k_tout(const DevCfg*, const EdgeItem*);
 static const void* const k_phases[N_PHASES] = {(const void*)ompd_k_nu, (const void*)ompd_k_ave,
                                                (const void*)ompd_k_mayp, (const void*)ompd_k_later,
@@ -122,7 +123,7 @@ extern "C" int ompd_ctx_create(ompd_ctx** out, int device_ordinal, uint64_t budg
     int dyn = (int)lds_max;
     for (const void* k : {k_phases[0], k_phases[1], k_phases[2], k_phases[3], k_phases[4], k_phases[5],
                           (const void*)ompd_k_prep, (const void*)ompd_k_solve, (const void*)ompd_k_sprep,
-                          (const void*)ompd_k_strip_a, (const void*)ompd_k_strip_b}) {
+                          (const void*)ompd_k_strip_a, (const void*)ompd_k_strip_b, (const void*)ompd_k_strip_b_rows}) {
         hipFuncAttributes fa{};
         int st = 0;
         if (hipFuncGetAttributes(&fa, k) == hipSuccess) st = (int)fa.sharedSizeBytes;
@@ -248,6 +249,7 @@ size_t ompd_cfg_scratch(const ompd_cfg& g, const ompd_result& r, ScratchOff& o, 
     o.s_link = put(4 * nrec);
     o.s_eid = put(4 * nrec);
     o.s_erec = put(4 * ne);
+    o.s_ebwd = put(ne >= STRIP_ROW_EDGES ? 4 * nrec : 0);
     o.s_xf = put(4 * (ne + 2));
     o.s_xb = put(4 * (ne + 2));
     o.s_estf = put(4 * (nb + 1));
@@ -262,8 +264,7 @@ size_t ompd_cfg_scratch(const ompd_cfg& g, const ompd_result& r, ScratchOff& o, 
     o.s_lastb = put(2 * nb);
     o.s_facts = put(nb);
     o.s_hdr = put(4 * SH_WORDS);
-    // positions are 15-bit numbers, edge entries 16-bit ones
-    o.strip = nb <= (size_t)STRIP_MAX_BLOCKS && ne < 65535 && (rows > 0 || total <= walk);
+    o.strip = nb <= (size_t)STRIP_MAX_BLOCKS && ne <= (size_t)STRIP_MAX_EDGES && (rows > 0 || total <= walk);
     total = align256(o.strip ? std::max(walk, total) : walk);
     o.nu = (r.nu_host && r.nu_dev) ? SIZE_MAX : take(2 * bv);
     o.ave = (r.ave_host && r.ave_dev) ? SIZE_MAX : take(2 * bv);
@@ -377,6 +378,7 @@ void ompd_fill_devcfg(const ompd_cfg& g, const ompd_result& r, char* base, const
                   ((flags & OMPD_F_PLACEMENT_LAZY) ? PL_LAZY : 0) | ((flags & OMPD_F_PLACEMENT_REFINE) ? PL_REFINE : 0);
     d.sweep_cap = (int)((flags >> 16) & 0xFFFFu);
     d.strip_ok = o.strip;
+    d.by_rows = g.n_edges >= STRIP_ROW_EDGES;
     d.sched_rule = !(flags & (OMPD_F_SCHED_LEVEL | OMPD_F_SCHED_WALK));
     d.sched = o.strip && !(flags & OMPD_F_SCHED_WALK) ? SCHED_LEVEL : SCHED_WALK;
     d.units = 4 / o.rows;
@@ -431,7 +433,7 @@ void ompd_fill_devcfg(const ompd_cfg& g, const ompd_result& r, char* base, const
     d.p_rw = u64p(o.s_rw); d.p_1 = u64p(o.s_1); d.p_2 = u64p(o.s_2); d.p_3 = u64p(o.s_3);
     d.p_g = u64p(o.s_g); d.p_b = u64p(o.s_b);
     d.rec_sf = u32p(o.s_recf); d.rec_sb = u32p(o.s_recb);
-    d.link = u32p(o.s_link); d.eid = i32p(o.s_eid); d.erec = i32p(o.s_erec);
+    d.link = u32p(o.s_link); d.eid = i32p(o.s_eid); d.erec = i32p(o.s_erec); d.ebwd = i32p(o.s_ebwd);
     d.x_f = u32p(o.s_xf); d.x_b = u32p(o.s_xb);
     d.est_f = i32p(o.s_estf); d.est_b = i32p(o.s_estb);
     d.loc_f = u32p(o.s_locf); d.loc_b = u32p(o.s_locb);
@@ -469,8 +471,8 @@ int ompd_make_shape(ompd_ctx* ctx, const std::vector<DevCfg>& cfgs, const PlanCo
                      [&](const Tile& a, const Tile& b) { return cfgs[a.cfg].nb > cfgs[b.cfg].nb; });
     const int walk_tiles = (int)tiles.size();
     LaunchDims& dm = sh.dims;
-    // strip tiles (after the walk tiles), launch by launch: CFGs with the same wavefronts, the ones
-    // that need most time first
+    // strip tiles (after the walk tiles), launch by launch: CFGs with the same wavefronts and records
+    // of the same kind, the ones that need most time first
     {
         std::vector<int> order;
         dm.n_walk = dm.n_strip = 0;
@@ -480,13 +482,16 @@ int ompd_make_shape(ompd_ctx* ctx, const std::vector<DevCfg>& cfgs, const PlanCo
             if (in_plan(i)) order.push_back(i);
         }
         std::stable_sort(order.begin(), order.end(), [&](int a, int b) {
-            return cfgs[a].waves != cfgs[b].waves ? cfgs[a].waves > cfgs[b].waves : cfgs[a].nb > cfgs[b].nb;
+            if (cfgs[a].waves != cfgs[b].waves) return cfgs[a].waves > cfgs[b].waves;
+            if (cfgs[a].by_rows != cfgs[b].by_rows) return cfgs[a].by_rows > cfgs[b].by_rows;
+            return cfgs[a].nb > cfgs[b].nb;
         });
         dm.n_buckets = 0;
         for (int i : order) {
             const DevCfg& d = cfgs[i];
-            if (!dm.n_buckets || dm.bucket[dm.n_buckets - 1].waves != d.waves)
-                dm.bucket[dm.n_buckets++] = LaunchDims::Bucket{(int)tiles.size() - walk_tiles, 0, d.waves, 0};
+            if (!dm.n_buckets || dm.bucket[dm.n_buckets - 1].waves != d.waves ||
+                dm.bucket[dm.n_buckets - 1].by_rows != d.by_rows)
+                dm.bucket[dm.n_buckets++] = LaunchDims::Bucket{(int)tiles.size() - walk_tiles, 0, d.waves, d.by_rows, 0};
             LaunchDims::Bucket& k = dm.bucket[dm.n_buckets - 1];
             for (int u = 0; u <= d.wd; u += d.units) {
                 tiles.push_back(Tile{i, u, std::min(d.units, d.wd + 1 - u), 0});
@@ -773,19 +778,19 @@ int ompd_launch_solve(const DevCfg* d_cfgs, const Tile* d_tiles, int n_tiles, co
         }
         mark();
     };
-    auto strips = [&](const void* fn) {
+    auto strips = [&](const void* fn, const void* fn_rows) {
         for (int b = 0; b < dm.n_buckets; ++b) {
             const LaunchDims::Bucket& k = dm.bucket[b];
             const Tile* t = d_strips + k.first;
             void* args[] = {(void*)&d_cfgs, (void*)&t};
-            (void)hipLaunchKernel(fn, dim3(k.n), dim3(64 * k.waves), args, k.lds, s);
+            (void)hipLaunchKernel(k.by_rows ? fn_rows : fn, dim3(k.n), dim3(64 * k.waves), args, k.lds, s);
         }
         mark();
     };
     transpose((const void*)ompd_k_tin, dm.n_tblock);
-    strips((const void*)ompd_k_strip_a);
+    strips((const void*)ompd_k_strip_a, (const void*)ompd_k_strip_a);
     transpose((const void*)ompd_k_tmid, dm.n_tblock);
-    if (!dm.first_half) strips((const void*)ompd_k_strip_b);
+    if (!dm.first_half) strips((const void*)ompd_k_strip_b, (const void*)ompd_k_strip_b_rows);
     else mark();
     transpose((const void*)ompd_k_tout, dm.first_half ? 0 : dm.n_tblock + dm.n_tedge);
     hipError_t e = hipGetLastError();

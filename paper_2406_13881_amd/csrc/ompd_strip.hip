@@ -46,7 +46,9 @@ constexpr uint32_t R0_REF = 0x7FFFu, R0_FAR = 1u << 15, R0_LAST = 1u << 31;
 constexpr int R0_POS = 16;   // 15 bits
 // Second word: the edge's entry, whether the lanes 1, 2, 4, 8 before belong to the same block, the
 // edge's and block's flags, and (the same in a pass's every lane) whether the pass holds a block
-// with a special rule and the reduction steps its longest block needs.
+// with a special rule and the reduction steps its longest block needs.  A CFG with more entries than 16
+// bits number (by_rows): a row's edges follow each other in the forward order (link) and in the
+// backward one (ebwd), so lanes 0 and 1 of a row hold the low and high half of where its first one is.
 constexpr uint32_t R1_EDGE = 0xFFFFu;
 constexpr int R1_SAME = 16, R1_LE = 20, R1_DEV = 21, R1_NOEDGE = 22, R1_XSRC = 23, R1_SPECIAL = 24, R1_CROSS = 25,
               R1_KIND = 26, R1_STEPS = 29;
@@ -104,7 +106,7 @@ __device__ __noinline__ int peel_lds(int entry, LDS3 u64* rec, const LDS3 uint16
         append(f0, w & 0x7FFFu);
         append(f1, w >> 16);
         on = list;
-        int e = !on ? 0 : si ? (int)(w & 0xFFFFu) : succ_ptr[b];
+        int e = !on ? 0 : si ? (int)(w & ~PEEL_LIST) : succ_ptr[b];
         const int z = on && !si ? succ_ptr[b + 1] : 0;
         while (__ballot(on)) {
             uint32_t q = 0;
@@ -342,6 +344,8 @@ extern "C" __global__ void __launch_bounds__(1024, 8) ompd_k_sprep(const DevCfg*
                     if (phase) {
                         const int b = lorder[i];
                         if (g % R == 0 && fill == 0) first = i;
+                        if (c.by_rows && fill == 0)   // (of a row with one edge; else its record follows)
+                            RECS[dir][((size_t)(base + g / R) * R + g % R) * ROW + 1] = make_uint2(0u, (uint32_t)at >> 16);
                         loc[i] = (uint32_t)(base + g / R) | ((uint32_t)((g % R) * ROW + fill) << LOC_LANE);
                         if (b == c.entry || b == c.exit || k > ROW || (c.call && c.call[b] >= 0)) special = LOC_SPECIAL;
                         most = max(most, k);
@@ -372,7 +376,8 @@ extern "C" __global__ void __launch_bounds__(1024, 8) ompd_k_sprep(const DevCfg*
         return (b == c.entry ? K_ENTRY : b == c.exit ? K_EXIT : (c.call && c.call[b] >= 0) ? K_CALL : 0u) + (k > ROW ? K_MULTI : 0u);
     };
     // the record of edge `slot` of the k of the block at position i (place l) whose neighbour is at
-    // position in (place ln, kn edges); `fl`: flags of the second word
+    // position in (place ln, kn edges); `fl`: flags of the second word; `entry`: the edge's (by_rows: its
+    // place in the direction's order)
     auto record = [&](int dir, int i, uint32_t l, int k, int slot, int in, uint32_t ln, int kn, int entry, uint32_t fl) {
         const int lanes = min(k, ROW), pr = pass_of(l), pn = pass_of(ln), lane = (int)(l >> LOC_LANE) & 63;
         uint32_t w0 = (uint32_t)i << R0_POS;
@@ -384,6 +389,11 @@ extern "C" __global__ void __launch_bounds__(1024, 8) ompd_k_sprep(const DevCfg*
             w0 |= (uint32_t)((pn % STRIP_RING) * 64) + (ll / ROW) * (uint32_t)(C * ROW) + ll % ROW;
         } else if (in >= 0) w0 |= R0_FAR | (uint32_t)in;
         for (int t = 0; t < 4; ++t) fl |= slot >= (1 << t) ? 1u << (R1_SAME + t) : 0u;
+        if (c.by_rows) {
+            const int in_row = (lane + slot) % ROW;
+            const uint32_t row = (uint32_t)(entry - in_row);
+            entry = in_row == 0 ? (int)(row & R1_EDGE) : in_row == 1 ? (int)(row >> 16) : 0;
+        }
         fl |= (x ? 1u << R1_CROSS : 0u) | (uint32_t)entry;
         if (lane + slot == 0) fl |= ((l & LOC_SPECIAL) ? 1u << R1_SPECIAL : 0u) | ((l >> LOC_STEPS) << R1_STEPS);
         RECS[dir][(size_t)pr * R * ROW + lane + slot] = make_uint2(w0, fl);
@@ -474,7 +484,7 @@ extern "C" __global__ void __launch_bounds__(1024, 8) ompd_k_sprep(const DevCfg*
         const bool on = b < nb;
         const int i = on ? c.pos[b] : 0, e0 = on ? c.succ_ptr[b] : 0, d = on ? c.succ_ptr[b + 1] - e0 : 0;
         const uint32_t lb = on ? c.loc_b[i] : 0u;
-        const int pb = pass_of(lb);
+        const int pb = pass_of(lb), at = on ? c.est_b[nb - 1 - i] : 0;
         Readers mine, part;
         auto look = [&](Readers& r, int p, int e) { reader(1, r, p, pass_of(c.loc_b[c.link[e] & 0x7FFFu])); };
         const bool read = on && b != c.entry;
@@ -490,15 +500,21 @@ extern "C" __global__ void __launch_bounds__(1024, 8) ompd_k_sprep(const DevCfg*
               [&](int e) {
                   const int j = e - e0, iq = c.pos[c.succ_idx[e]];
                   const uint32_t lq = c.loc_b[iq];
-                  if (j < ROW) record(1, i, lb, d, j, iq, lq, c.est_b[nb - iq] - c.est_b[nb - 1 - iq], c.erec[e], fl);
+                  if (c.by_rows) c.ebwd[at + j] = c.erec[e];
+                  if (j < ROW)
+                      record(1, i, lb, d, j, iq, lq, c.est_b[nb - iq] - c.est_b[nb - 1 - iq], c.by_rows ? at + j : c.erec[e], fl);
                   crosses(iq, lq, pb);
               },
               [&](int e, int l) {
                   const int iq = c.pos[c.succ_idx[e]];
+                  if (c.by_rows) c.ebwd[of(at, l) + e - of(e0, l)] = c.erec[e];
                   crosses(iq, c.loc_b[iq], of(pb, l));
               },
               [](int) {});
-        if (on && d == 0) record(1, i, lb, 1, 0, -1, 0, 0, 0, fl | (1u << R1_NOEDGE));
+        if (on && d == 0) {
+            if (c.by_rows) c.ebwd[at] = 0;
+            record(1, i, lb, 1, 0, -1, 0, 0, c.by_rows ? at : 0, fl | (1u << R1_NOEDGE));
+        }
     }
     __syncthreads();
     if (tid == 0) {
@@ -569,6 +585,12 @@ __device__ __forceinline__ u64 row_shr(u64 v)
     const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)v, 0x110 + S, 0xF, 0xF, true);
     const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(v >> 32), 0x110 + S, 0xF, 0xF, true);
     return (u64)lo | ((u64)hi << 32);
+}
+// lane L's value in every lane of its row
+template <int L>
+__device__ __forceinline__ uint32_t row_lane(uint32_t v)
+{
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x150 + L, 0xF, 0xF, true);   // row_newbcast
 }
 // Segmented reduction over the lanes of a block's edges: the last one gets the result (the first
 // NA words by AND, the others by OR).  w1: the lane's record, steps: of its pass.
@@ -795,7 +817,7 @@ __device__ __forceinline__ int wave_max(int v)
 // refilled with the passes before p0 (from pass `back` on), `reach` is the wavefront's horizon (the
 // last pass that reads a block changed in this round), and `more(p)`, asked before a group of
 // passes beyond it, ends the run early; true if a state of the lane's blocks changed.
-template <int PH, bool FIRST, class More>
+template <int PH, bool BY_ROWS, bool FIRST, class More>
 __device__ __forceinline__ bool run_passes(const DevCfg& c, const Strip& t, const Src<PH>& src, int p0, int p1, int back,
                                            u64 init, int& reach, More&& more)
 {
@@ -819,7 +841,14 @@ __device__ __forceinline__ bool run_passes(const DevCfg& c, const Strip& t, cons
     struct Slot { In<PH> x; Pair far, old; uint32_t last; };
     auto load = [&](const Rec& r, Slot& s) {
         const uint32_t pos = (r.x >> R0_POS) & 0x7FFFu, n = t.cn + pos;
-        load_in<PH>(src, n, t.ce + (r.y & R1_EDGE), s.x);
+        uint32_t e = r.y & R1_EDGE;
+        if constexpr (BY_ROWS && In<PH>::EDGE) {
+            // (lanes without an edge take another one's entry)
+            const uint32_t row = row_lane<0>(e) | (row_lane<1>(e) << 16);
+            e = min(row + (uint32_t)t.i, (uint32_t)t.nrec - 1u);
+            if constexpr (BWD) e = (uint32_t)G(c.ebwd)[e];
+        }
+        load_in<PH>(src, n, t.ce + e, s.x);
         const uint32_t far = 16u * (t.cn + ((r.x & R0_FAR) ? r.x & R0_REF : 0u));
         if constexpr (FIRST) s.far = ldp32(src.st, far);
         else s.far = ldp32(((r.y >> R1_CROSS) & 1u) ? src.sh : src.st, far);
@@ -933,8 +962,9 @@ __device__ __forceinline__ bool run_passes(const DevCfg& c, const Strip& t, cons
     return changed != 0u;
 }
 
-// The fixed point of a phase; false when the sweep cap stops it.
-template <int PH>
+// The fixed point of a phase; false when the sweep cap stops it.  BY_ROWS: the records hold their rows'
+// edge entries.
+template <int PH, bool BY_ROWS>
 __device__ __forceinline__ bool fixed_point(const DevCfg& c, const Strip& t)
 {
     constexpr bool BWD = backward(PH);
@@ -965,7 +995,7 @@ __device__ __forceinline__ bool fixed_point(const DevCfg& c, const Strip& t)
     int sweeps = 1;
     bool changed = false, good = true;
     int reach = -1;
-    if (p0 < p1) (void)run_passes<PH, true>(c, t, src, p0, p1, p0, init, reach, [](int) { return true; });
+    if (p0 < p1) (void)run_passes<PH, BY_ROWS, true>(c, t, src, p0, p1, p0, init, reach, [](int) { return true; });
     for (int round = 1;; ++round) {
         if (round > 1) {
             const bool any = __syncthreads_or(changed);
@@ -1008,7 +1038,7 @@ __device__ __forceinline__ bool fixed_point(const DevCfg& c, const Strip& t)
         };
         for (int p = next_mark(p0); p < p1;) {
             int end = p1;   // the passes go on to the horizon and over short gaps
-            changed |= run_passes<PH, false>(c, t, src, p, p1, p0, init, reach, [&](int q) {
+            changed |= run_passes<PH, BY_ROWS, false>(c, t, src, p, p1, p0, init, reach, [&](int q) {
                 const int m = next_mark(q);
                 if (m < p1 && m < q + 32) return true;
                 end = m;
@@ -1361,7 +1391,7 @@ ompd_k_strip_a(const DevCfg* __restrict__ cfgs, const Tile* __restrict__ tiles)
     const int tid = threadIdx.x, nt = blockDim.x, nb = t.nb, wd = c.wd;
     const bool with_facts = tl.s0 + tl.nw == wd + 1;
     const size_t fo = (size_t)wd * nb;
-    if (!fixed_point<PH_NU>(c, t)) return;
+    if (!fixed_point<PH_NU, false>(c, t)) return;
     if (with_facts) {
         // bit 0 of the host word: the block reaches EXIT; bit 1 of the device word: it reaches a
         // DEVICE block; the word takes part in the validity without next use
@@ -1375,7 +1405,7 @@ ompd_k_strip_a(const DevCfg* __restrict__ cfgs, const Tile* __restrict__ tiles)
         if (bad) set_status(c.info, OMPD_E_INVAL_);
         __syncthreads();
     }
-    if (!fixed_point<PH_AVE>(c, t)) return;
+    if (!fixed_point<PH_AVE, false>(c, t)) return;
     if (with_facts) {
         // bit 0 of the host word: not reached from ENTRY; bit 1: no DEVICE block reaches the block
         bool bad = false;
@@ -1394,11 +1424,11 @@ ompd_k_strip_a(const DevCfg* __restrict__ cfgs, const Tile* __restrict__ tiles)
 }
 
 // Pending copies, placement, refinement and final validity of a strip, and the map kinds of its
-// variables.
-extern "C" __global__ void __launch_bounds__(64 * STRIP_MAX_WAVES)
-ompd_k_strip_b(const DevCfg* __restrict__ cfgs, const Tile* __restrict__ tiles)
+// variables.  BY_ROWS has kernels of its own: a branch around those few instructions in the others
+// costs them 3 % (strip_b, 2048 small CFGs: 331 -> 343 us, 779 blocks 412 -> 424 us).
+template <bool BY_ROWS>
+__device__ __forceinline__ void strip_b(const DevCfg* __restrict__ cfgs, const Tile* __restrict__ tiles, uint32_t* smem)
 {
-    extern __shared__ __align__(16) uint32_t smem[];
     const Tile tl = tiles[blockIdx.x];
     const DevCfg& c = cfgs[tl.cfg];
     const int wd = c.wd, nu = min(tl.nw, wd - tl.s0);   // (the word of facts is done)
@@ -1410,7 +1440,7 @@ ompd_k_strip_b(const DevCfg* __restrict__ cfgs, const Tile* __restrict__ tiles)
         // every eager copy stays on its edge
         for (int b = tid; b < nu * nb; b += nt) stp(c.p_2, (size_t)tl.s0 * nb + b, Pair{0, 0});
     } else {
-        if (!fixed_point<PH_MAYP>(c, t)) return;
+        if (!fixed_point<PH_MAYP, BY_ROWS>(c, t)) return;
         // valid in both spaces on an edge: no copy pending across it
         by_units(nu, [&](auto uc) {
             constexpr int U = decltype(uc)::value;
@@ -1429,11 +1459,11 @@ ompd_k_strip_b(const DevCfg* __restrict__ cfgs, const Tile* __restrict__ tiles)
             }
         });
         __syncthreads();
-        if (!fixed_point<PH_LATER>(c, t)) return;
+        if (!fixed_point<PH_LATER, BY_ROWS>(c, t)) return;
         by_units(nu, [&](auto uc) { after_later<decltype(uc)::value>(c, t, nu); });
         __syncthreads();
         if (refines(c.placement)) {
-            if (!fixed_point<PH_LIVE>(c, t)) return;
+            if (!fixed_point<PH_LIVE, BY_ROWS>(c, t)) return;
             // a copy on a loop entry whose value nothing reads is dropped
             for (int u = tl.s0; u < tl.s0 + nu; ++u)
                 for (int e = tid; e < t.nrec; e += nt) {
@@ -1446,7 +1476,7 @@ ompd_k_strip_b(const DevCfg* __restrict__ cfgs, const Tile* __restrict__ tiles)
         }
     }
     __syncthreads();
-    if (!fixed_point<PH_AVF>(c, t)) return;
+    if (!fixed_point<PH_AVF, BY_ROWS>(c, t)) return;
     LDS3 uint32_t* kinds = (LDS3 uint32_t*)(t.ctl + 16);   // [units][to, from, used on the device, firstprivate]
     if (tid < 32) sst(kinds + tid, 0u);
     __syncthreads();
@@ -1461,6 +1491,20 @@ ompd_k_strip_b(const DevCfg* __restrict__ cfgs, const Tile* __restrict__ tiles)
         const uint32_t t1 = bit(0), f1 = bit(1), d1 = bit(2), q1 = bit(3);
         G(c.var_kind)[v] = (uint8_t)(t1 | (f1 << 1) | ((d1 && !t1 && !f1) ? 4u : 0u) | (q1 << 3));
     }
+}
+
+extern "C" __global__ void __launch_bounds__(64 * STRIP_MAX_WAVES)
+ompd_k_strip_b(const DevCfg* __restrict__ cfgs, const Tile* __restrict__ tiles)
+{
+    extern __shared__ __align__(16) uint32_t smem[];
+    strip_b<false>(cfgs, tiles, smem);
+}
+
+extern "C" __global__ void __launch_bounds__(64 * STRIP_MAX_WAVES)
+ompd_k_strip_b_rows(const DevCfg* __restrict__ cfgs, const Tile* __restrict__ tiles)
+{
+    extern __shared__ __align__(16) uint32_t smem[];
+    strip_b<true>(cfgs, tiles, smem);
 }
 
 // --------------------------------------------------------------------------

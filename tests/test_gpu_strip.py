@@ -85,3 +85,38 @@ def test_strip_sweeps_repeat(ctx):
     runs = [[r["sweeps"] for r in ctx.analyze_batch(cfgs)] for _ in range(6)]
     for again in runs[1:]:
         assert np.array_equal(np.asarray(runs[0]), np.asarray(again))
+
+
+def _dense(n, n_edges, n_vars, seed):
+    """A chain of n blocks; edges of every kind between blocks of its first half make it n_edges."""
+    rng = np.random.default_rng(seed)
+    edges = [(b, b + 1, 0) for b in range(n + 1)]
+    a, b = rng.integers(1, n // 2, n_edges), rng.integers(1, n // 2, n_edges)
+    edges += [(int(x), int(y), 1 if x >= y else 2 * int(k < 0.2)) for x, y, k in zip(a, b, rng.random(n_edges))]
+    return synth.from_edges(_blocks(rng, n, n_vars), edges[:n_edges], n_vars)[0]
+
+
+@pytest.mark.parametrize("n_edges", [65533, 65534, 65535, 65536, 70001, 140000])
+def test_strip_many_edges(ctx, n_edges):
+    """Edge entries that fit the 16 bits of a lane record and ones that do not, up to the largest 17-bit
+    ones, with the refinement (whose backward sweep reads the copies of its edges) and without; all by
+    level, alone and in a launch that fills the GPU."""
+    import json
+    import paper_2406_13881_amd as ompd
+    from paper_2406_13881_amd.resident import ResidentBatch
+    cfg = _dense(3000, n_edges, 70, n_edges)
+    assert len(cfg.succ_idx) == n_edges
+    for flags, placement in ((0, 0), (ompd.F_PLACEMENT_REFINE, oracle.PLACEMENT_REFINE)):
+        want = oracle.solve(cfg, placement=placement)
+        for copies in (1, 200):
+            print("%d edges, flags %d, %d copies" % (n_edges, flags, copies), flush=True)
+            rb = ResidentBatch(ctx, [cfg] * copies, flags=flags)
+            assert json.loads(rb.plan.describe())["tiles"] == 0   # (of the walk)
+            rb.run()
+            assert (rb.plan.status() == 0).all()
+            for i in {0, copies - 1}:
+                got = rb.fetch(i)
+                for k in KEYS:
+                    g = np.asarray(got[k])
+                    assert np.array_equal(g, np.asarray(want[k]).reshape(g.shape)), (flags, copies, i, k)
+            rb.close()
