@@ -337,7 +337,7 @@ void ompd_settle_sched(DevCfg* h, int n, int n_cu, bool split)
     int most = 1;
     for (int i = 0; i < n; ++i) {
         DevCfg& d = h[i];
-        d.spread = d.sched == SCHED_LEVEL && (idle || !d.sched_rule);
+        d.spread = d.sched == SCHED_LEVEL && idle;
         const int per = d.spread ? 32 : std::max(32, busy_per), limit = idle ? STRIP_MAX_WAVES : STRIP_BUSY_WAVES;
         // (a caller's sweep cap counts rounds: one run of passes, so that they don't depend on timing)
         d.waves = 1;

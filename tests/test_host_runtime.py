@@ -206,3 +206,19 @@ def test_per_tile_kernel_where_the_launch_fills_the_gpu(standin):
         plan.split_kernels(False)
         assert kernels(plan.run) == [False, True, False]
     """)
+
+
+def test_a_named_level_schedule_takes_the_shape_of_the_launch(standin):
+    """Naming the schedule that a CFG takes anyway changes nothing: the wavefronts of its strips follow
+    from the launch's load, whether the flags, the plan's buckets or the rule put it on the strips."""
+    run(standin, """
+        ctx = ompd.Context(0, 64 << 20)
+        for cfg, copies in ((synth.c1(0), 2), (synth.c1(0), 1500), (synth.c3_item(5, n_user=700, n_vars=500), 300)):
+            plans = [resident(ctx, [cfg] * copies, flags) for flags in (0, 0, ompd.F_SCHED_LEVEL)]
+            plans[1].set_schedule([1] * 5)
+            shapes = []
+            for p in plans:
+                d = json.loads(p.describe())
+                shapes.append({k: d[k] for k in ("level_tiles", "lds_level", "strip_launches", "level_cfgs")})
+            assert shapes[0] == shapes[1] == shapes[2], (copies, shapes)
+    """)
