@@ -1157,29 +1157,45 @@ extern "C" int ompd_plan_autotune(ompd_plan* p, void* stream, int32_t trials, fl
         }
     }
     // the buckets were timed alone, where the lower latency wins; on the whole plan the throughput
-    // may favour the default rule instead: keep whichever runs the plan faster
+    // may favour the default rule instead: keep whichever runs the plan faster (there is nothing to
+    // compare where the rule puts every CFG on the schedule picked for it)
     if (!(p->flags & (OMPD_F_SCHED_LEVEL | OMPD_F_SCHED_WALK))) {
         PlanConfig rule = base;
         for (int b = 0; b < OMPD_SCHED_BUCKETS; ++b) rule.bucket_sched[b] = -1;
+        auto schedules = [&](const PlanConfig& c, std::vector<int>& of) -> bool {
+            if (ompd_plan_retile(p, c) != OMPD_OK) return false;
+            for (const DevCfg& d : p->h_cfgs) of.push_back(d.sched);
+            return true;
+        };
+        std::vector<int> picked, ruled;
         float t_pick = 0, t_rule = 0;
-        if (time_config(p, base, s, trials, t_pick) == OMPD_OK && time_config(p, rule, s, trials, t_rule) == OMPD_OK &&
-            t_rule < 0.98f * t_pick)
+        if (schedules(base, picked) && schedules(rule, ruled) && picked != ruled &&
+            time_config(p, base, s, trials, t_pick) == OMPD_OK && time_config(p, rule, s, trials, t_rule) == OMPD_OK &&
+            t_rule < t_pick)
             base = rule;
     }
-    // 2. the launch configuration of the whole plan with those schedules
+    // 2. the launch configuration of the whole plan with those schedules; it is the walk's, so a plan
+    // without a CFG on it keeps the one it has
     PlanConfig best = base;
     float best_t = 1e30f;
-    for (size_t lds : {(size_t)16 * STATE_BYTES, (size_t)32 * STATE_BYTES, (size_t)64 * STATE_BYTES}) {
-        for (int wpc : {0, 4}) {
-            PlanConfig c = base;
-            c.lds_bytes = lds;
-            c.wg_per_cu = wpc;
-            float ms = 0;
-            if (time_config(p, c, s, trials, ms) != OMPD_OK) continue;
-            if (ms < best_t) { best_t = ms; best = c; }
-        }
+    int rc = ompd_plan_retile(p, base);
+    if (rc) return rc;
+    std::vector<PlanConfig> candidates;
+    if (p->dims.n_walk == 0) candidates.push_back(base);
+    else
+        for (size_t lds : {(size_t)16 * STATE_BYTES, (size_t)32 * STATE_BYTES, (size_t)64 * STATE_BYTES})
+            for (int wpc : {0, 4}) {
+                PlanConfig c = base;
+                c.lds_bytes = lds;
+                c.wg_per_cu = wpc;
+                candidates.push_back(c);
+            }
+    for (const PlanConfig& c : candidates) {
+        float ms = 0;
+        if (time_config(p, c, s, trials, ms) != OMPD_OK) continue;
+        if (ms < best_t) { best_t = ms; best = c; }
     }
-    int rc = ompd_plan_retile(p, best);
+    rc = ompd_plan_retile(p, best);
     if (rc) return rc;
     if (best_t >= 1e30f) return ompd_fail(OMPD_E_DEVICE, "autotune: no configuration ran");
     if (best_ms) *best_ms = best_t;

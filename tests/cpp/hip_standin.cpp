@@ -17,6 +17,7 @@ std::mutex mu;
 std::map<char*, size_t> dev;        // device allocations
 size_t live = 0, budget = (size_t)64 << 30;
 long violations = 0, allocs = 0, fail_at = -1;
+long clock_ms = 0;                  // a kernel takes one millisecond
 std::vector<size_t> sizes;          // of every allocation so far
 std::string first;
 struct Kernel { long launches = 0, items = 0; };
@@ -128,6 +129,7 @@ hipError_t hipLaunchKernel(const void* f, dim3, dim3, void** args, size_t, hipSt
     const std::string& n = names[f];
     Kernel& k = kernels[n];
     ++k.launches;
+    ++clock_ms;
     if (n.find("CallTabItem") != std::string::npos) k.items += *(int*)args[1];
     for (const char* part : {"k_nu", "k_ave", "k_mayp", "k_later", "k_live", "k_avf", "k_post", "k_varkind", "k_solve",
                              "k_strip", "k_tin", "k_tmid", "k_tout"})   // (descriptors, tiles or items, ...)
@@ -178,13 +180,21 @@ hipError_t hipDeviceSynchronize() { note("sync"); return hipSuccess; }
 hipError_t hipStreamSynchronize(hipStream_t) { note("sync"); return hipSuccess; }
 hipError_t hipStreamCreateWithFlags(hipStream_t* s, unsigned) { *s = (hipStream_t)malloc(1); return hipSuccess; }
 hipError_t hipStreamDestroy(hipStream_t s) { free(s); return hipSuccess; }
-hipError_t hipEventCreate(hipEvent_t* e) { *e = (hipEvent_t)malloc(1); return hipSuccess; }
-hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) { *e = (hipEvent_t)malloc(1); return hipSuccess; }
+hipError_t hipEventCreate(hipEvent_t* e) { *e = (hipEvent_t)calloc(1, sizeof(long)); return hipSuccess; }
+hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) { return hipEventCreate(e); }
 hipError_t hipEventDestroy(hipEvent_t e) { free(e); return hipSuccess; }
-hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }
+hipError_t hipEventRecord(hipEvent_t e, hipStream_t)
+{
+    std::lock_guard<std::mutex> g(mu);
+    *(long*)e = clock_ms;
+    return hipSuccess;
+}
 hipError_t hipEventSynchronize(hipEvent_t) { note("sync"); return hipSuccess; }
-static float elapsed = 1.0f;
-hipError_t hipEventElapsedTime(float* ms, hipEvent_t, hipEvent_t) { *ms = elapsed; return hipSuccess; }
+hipError_t hipEventElapsedTime(float* ms, hipEvent_t a, hipEvent_t b)
+{
+    *ms = (float)(*(long*)b - *(long*)a);
+    return hipSuccess;
+}
 hipError_t hipFuncGetAttributes(hipFuncAttributes* a, const void*) { memset(a, 0, sizeof *a); return hipSuccess; }
 hipError_t hipFuncSetAttribute(const void*, hipFuncAttribute, int) { return hipSuccess; }
 hipError_t hipOccupancyMaxActiveBlocksPerMultiprocessor(int* n, const void*, int, size_t) { *n = 4; return hipSuccess; }

@@ -222,3 +222,20 @@ def test_a_named_level_schedule_takes_the_shape_of_the_launch(standin):
                 shapes.append({k: d[k] for k in ("level_tiles", "lds_level", "strip_launches", "level_cfgs")})
             assert shapes[0] == shapes[1] == shapes[2], (copies, shapes)
     """)
+
+
+def test_autotuner_leaves_alone_what_has_no_effect(standin):
+    """The launch configuration is the walk's: a plan of strips keeps the one it was given, and its
+    schedules, once they are what the rule would choose, are not replaced by the rule's."""
+    run(standin, """
+        ctx = ompd.Context(0, 64 << 20)
+        plan = resident(ctx, [synth.c1(0), synth.c3_item(2)])
+        plan.configure(8192, 3)
+        plan.autotune()
+        d = json.loads(plan.describe())
+        assert (d["lds_bytes"], d["wg_per_cu"]) == (8192, 3), d
+        walk = resident(ctx, [synth.c1(0)], ompd.F_SCHED_WALK)
+        walk.autotune()
+        d = json.loads(walk.describe())
+        assert d["lds_bytes"] > 0, d
+    """)
