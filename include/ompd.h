@@ -95,7 +95,11 @@ enum { OMPD_MAP_TO = 1, OMPD_MAP_FROM = 2, OMPD_MAP_ALLOC = 4, OMPD_FIRSTPRIVATE
  * both, LAZY over REFINE. */
 #define OMPD_F_PLACEMENT_LAZY (1u << 6)
 #define OMPD_F_PLACEMENT_REFINE (1u << 7)
-#define OMPD_F_SWEEP_CAP(n) ((((uint32_t)(n)) & 0xFFFFu) << 16) /* cap sweeps per phase */
+/* Cap the sweeps of each phase.  A sweep visits every block once, after the
+ * blocks before it over edges other than BACK, so the sweeps that a CFG needs
+ * (and a capped call reports) are the walk's whatever the schedule.  By level,
+ * a capped CFG is solved by one wavefront per four words, which takes longer. */
+#define OMPD_F_SWEEP_CAP(n) ((((uint32_t)(n)) & 0xFFFFu) << 16)
 /* Ring of recently solved blocks per solve workgroup, for the one-shot entry
  * points (what ompd_plan_configure sets for a plan): n = 8, 16, 32 or 64
  * blocks (other values round down to one of these; 0 = default, 64).  Results
@@ -172,7 +176,10 @@ typedef struct {
  * iff !before_dev[q]; otherwise target update from.
  *   sweeps[6]     sweeps used per phase (next use, validity, pending,
  *                 delay, final validity, loop-entry refinement); host
- *                 memory, filled after completion; informational.         */
+ *                 memory, filled after completion; informational.  By
+ *                 level and without a cap they count rounds of wavefronts
+ *                 that see each other's results a round late: never fewer
+ *                 than the sweeps that a cap counts, often more.          */
 typedef struct {
     uint64_t *nu_host, *nu_dev;
     uint64_t *ave_host, *ave_dev;

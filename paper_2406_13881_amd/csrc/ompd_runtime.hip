@@ -339,7 +339,9 @@ void ompd_settle_sched(DevCfg* h, int n, int n_cu, bool split)
         DevCfg& d = h[i];
         d.spread = d.sched == SCHED_LEVEL && idle;
         const int per = d.spread ? 32 : std::max(32, busy_per), limit = idle ? STRIP_MAX_WAVES : STRIP_BUSY_WAVES;
-        // (a caller's sweep cap counts rounds: one run of passes, so that they don't depend on timing)
+        // (a caller's sweep cap counts sweeps in which each block sees what comes before it, as the walk
+        // does: one run of passes.  Several see each other's results a round late and take more rounds,
+        // 10 where the walk takes 4 on CFGs of 66 blocks, and would stop calls that the walk finishes)
         d.waves = 1;
         if (d.sweep_cap == 0)
             while (d.waves < limit && d.nb > per * d.waves) d.waves *= 2;

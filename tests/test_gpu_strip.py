@@ -120,3 +120,29 @@ def test_strip_many_edges(ctx, n_edges):
                     g = np.asarray(got[k])
                     assert np.array_equal(g, np.asarray(want[k]).reshape(g.shape)), (flags, copies, i, k)
             rb.close()
+
+
+@pytest.mark.parametrize("refine", [False, True])
+def test_strip_sweep_cap(ctx, refine):
+    """A cap counts the same sweeps by level as on the walk: a capped call reports the walk's, a cap of as
+    many as the slowest phase needs finishes, one less stops; uncapped rounds are never fewer."""
+    import paper_2406_13881_amd as ompd
+    base = ompd.F_PLACEMENT_REFINE if refine else 0
+    cfgs = [synth.c1(3), synth.c3_item(5, n_user=700, n_vars=300), synth.permute_blocks(synth.c1(4), 5)[0],
+            _chain(400, 130, 3), _fan(40, 130, 4), _dense(300, 4000, 70, 5), synth.random_dag(9, 90, 70, p_loop_entry=0.3),
+            synth.make_cfg(5_003, n_user=160, n_vars=90, max_loop_depth=6, device_frac=0.4, irr_loop_frac=0.2)]
+    for i, cfg in enumerate(cfgs):
+        need = ctx.analyze_cfg(cfg, flags=base | ompd.F_SCHED_WALK)["sweeps"]
+        most = int(max(need))
+        for flags in (base, base | ompd.F_SCHED_LEVEL):
+            assert (ctx.analyze_cfg(cfg, flags=flags)["sweeps"] >= need).all(), i
+            got = ctx.analyze_cfg(cfg, flags=flags | (most << 16))
+            assert np.array_equal(got["sweeps"], need), (i, got["sweeps"], need)
+            want = oracle.solve(cfg, placement=oracle.PLACEMENT_REFINE if refine else 0)
+            for k in KEYS:
+                g = np.asarray(got[k])
+                assert np.array_equal(g, np.asarray(want[k]).reshape(g.shape)), (i, k)
+            if most > 1:
+                with pytest.raises(ompd.OmpdError) as e:
+                    ctx.analyze_cfg(cfg, flags=flags | ((most - 1) << 16))
+                assert e.value.code == ompd.OMPD_E_NOCONVERGE, i
