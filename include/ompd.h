@@ -306,7 +306,10 @@ int ompd_plan_profile(ompd_plan* plan, int32_t enable);
  * tile.  OMPD_E_INVAL for a NULL plan. */
 int ompd_plan_split_kernels(ompd_plan* plan, int32_t split);
 int ompd_plan_kernel_ms(ompd_plan* plan, float* ms, int32_t capacity, int32_t* n_kernels);
-/* Describe the plan's current configuration as a NUL-terminated string. */
+/* Describe the plan's current configuration as a NUL-terminated string
+ * (JSON): among others the CFGs solved by level (strip_cfgs; level_cfgs: those
+ * whose strips have the shape of a launch that leaves the GPU idle) and the
+ * tiles of each schedule (tiles: the walk's, level_tiles). */
 int ompd_plan_describe(ompd_plan* plan, char* buf, int32_t len);
 /* Duration (ms) of the last ompd_plan_run measured with HIP events on its
  * stream: total, and the solve kernel alone. */

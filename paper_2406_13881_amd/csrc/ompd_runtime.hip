@@ -1069,6 +1069,8 @@ extern "C" int ompd_plan_describe(ompd_plan* p, char* buf, int32_t len)
     if (!p || !buf || len <= 0) return ompd_fail(OMPD_E_INVAL, "bad arguments");
     long lanes = 0;
     for (size_t i = 0; i + p->dims.n_level < p->h_tiles.size(); ++i) lanes += p->h_tiles[i].nw;
+    // strip_cfgs: the CFGs solved by level; level_cfgs: those of them in the shape of a launch that leaves
+    // the GPU idle
     int level_cfgs = 0;
     for (const DevCfg& d : p->h_cfgs) level_cfgs += d.spread;
     snprintf(buf, len,
@@ -1076,13 +1078,13 @@ extern "C" int ompd_plan_describe(ompd_plan* p, char* buf, int32_t len)
              "\"grid_phases\": [%d, %d, %d, %d, %d], "
              "\"lds_bytes\": %zu, \"wg_per_cu\": %d, \"graph\": %d, \"graph_captured\": %d, "
              "\"scratch_bytes\": %zu, \"bucket_sched\": [%d, %d, %d, %d, %d], \"level_cfgs\": %d, "
-             "\"level_tiles\": %d, \"lds_level\": %zu, \"strip_launches\": %d}",
+             "\"strip_cfgs\": %d, \"level_tiles\": %d, \"lds_level\": %zu, \"strip_launches\": %d}",
              p->n, p->n_tiles - p->dims.n_level, lanes, p->dims.ring_slots, (int)p->dims.split, p->dims.grid_tile,
              p->dims.grid[0], p->dims.grid[1], p->dims.grid[2],
              p->dims.grid[3], p->dims.grid[4], p->cfg.lds_bytes, p->cfg.wg_per_cu,
              p->cfg.use_graph ? 1 : 0, p->gx_solve ? 1 : 0, p->scratch_bytes, p->cfg.bucket_sched[0],
              p->cfg.bucket_sched[1], p->cfg.bucket_sched[2], p->cfg.bucket_sched[3], p->cfg.bucket_sched[4],
-             level_cfgs, p->dims.n_level, p->dims.n_buckets ? p->dims.bucket[0].lds : 0, p->dims.n_buckets);
+             level_cfgs, p->dims.n_strip, p->dims.n_level, p->dims.n_buckets ? p->dims.bucket[0].lds : 0, p->dims.n_buckets);
     return OMPD_OK;
 }
 

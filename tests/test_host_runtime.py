@@ -239,3 +239,19 @@ def test_autotuner_leaves_alone_what_has_no_effect(standin):
         d = json.loads(walk.describe())
         assert d["lds_bytes"] > 0, d
     """)
+
+
+def test_describe_counts_the_cfgs_of_each_schedule(standin):
+    """strip_cfgs is every CFG solved by level, also in a launch that fills the GPU."""
+    run(standin, """
+        ctx = ompd.Context(0, 64 << 20)
+        small = synth.c1(0)
+        for copies, flags, sched, strips in ((2, 0, -1, 2), (1500, 0, -1, 1500), (2, ompd.F_SCHED_WALK, None, 0),
+                                             (3, ompd.F_SCHED_LEVEL, None, 3), (3, 0, 0, 0)):
+            plan = resident(ctx, [small] * copies, flags)
+            if sched is not None:
+                plan.set_schedule([sched] * 5)
+            d = json.loads(plan.describe())
+            assert d["strip_cfgs"] == strips and (d["tiles"] > 0) == (strips == 0), d
+            assert (d["level_tiles"] > 0) == (strips > 0), d
+    """)
