@@ -146,3 +146,64 @@ def test_strip_sweep_cap(ctx, refine):
                 with pytest.raises(ompd.OmpdError) as e:
                     ctx.analyze_cfg(cfg, flags=flags | ((most - 1) << 16))
                 assert e.value.code == ompd.OMPD_E_NOCONVERGE, i
+
+
+@pytest.mark.parametrize("n_blocks,strips", [(0, 1), (1, 1), (25_000, 1), (32_000, 1), (32_001, 0)])
+def test_strip_most_blocks(ctx, n_blocks, strips):
+    """CFGs whose peel is the last that LDS holds (0: 8 bytes a block and 8 more), the first that global
+    memory does (1), and the largest that the strips take; ids in order and shuffled."""
+    import json
+    from paper_2406_13881_amd.resident import ResidentBatch
+    if n_blocks < 2:
+        n_blocks += ctx.device_info()["lds_bytes"] // 8 - 1
+    cfg = synth.make_cfg(n_blocks, n_user=n_blocks - 2, n_vars=70, max_loop_depth=4, device_frac=0.3,
+                         irr_loop_frac=0.01, p_read=0.05, p_write=0.02)
+    assert cfg.n_blocks == n_blocks
+    cfgs = [cfg, synth.permute_blocks(cfg, 1)[0], _chain(n_blocks - 2, 70, 2)]
+    print("%d blocks" % n_blocks, flush=True)
+    rb = ResidentBatch(ctx, cfgs)
+    assert json.loads(rb.plan.describe())["strip_cfgs"] == strips * len(cfgs)
+    rb.run()
+    assert (rb.plan.status() == 0).all()
+    for i, c in enumerate(cfgs):
+        got, want = rb.fetch(i), oracle.solve(c)
+        for k in KEYS:
+            g = np.asarray(got[k])
+            assert np.array_equal(g, np.asarray(want[k]).reshape(g.shape)), (i, k)
+    rb.close()
+
+
+def test_strips_that_do_not_fit_their_scratch(ctx):
+    """The allocation-free entry point and the serving loop solve by the walk what their memory holds
+    only that way (the sweeps show it: the strips' rounds are more)."""
+    import paper_2406_13881_amd as ompd
+    from paper_2406_13881_amd.resident import ResidentBatch
+    cfg = synth.c3_item(5, n_user=300, n_vars=32)
+    walk = ctx.analyze_cfg(cfg, flags=ompd.F_SCHED_WALK)
+    assert (ctx.analyze_cfg(cfg)["sweeps"] > walk["sweeps"]).any()
+
+    def same(got, tag):
+        for k in KEYS:
+            g = np.asarray(got[k])
+            assert np.array_equal(g, np.asarray(walk[k]).reshape(g.shape)), (tag, k)
+
+    for copies, by_walk in ((100, False), (2000, True)):   # of 256 MiB
+        rb = ResidentBatch(ctx, [cfg] * copies)
+        sweeps = ompd.analyze_device(ctx, rb.dcfgs, rb.dres, 0, noalloc=True)
+        assert (sweeps == walk["sweeps"]).all() == by_walk, copies
+        for i in (0, copies - 1):
+            same(rb.fetch(i), "no allocation, %d" % copies)
+        rb.close()
+    for budget in range(100 << 10, 4 << 20, 20 << 10):   # the least that admits the request holds its walk
+        small = ompd.Context(0, budget)
+        try:
+            r = ompd.submit(small, cfg)
+            if r.admitted:
+                got = r.wait()
+                assert np.array_equal(got["sweeps"], walk["sweeps"]), budget
+                same(got, "serving, %d bytes" % budget)
+                break
+        finally:
+            small.close()
+    else:
+        assert False, "no budget admitted the request"

@@ -255,3 +255,34 @@ def test_describe_counts_the_cfgs_of_each_schedule(standin):
             assert d["strip_cfgs"] == strips and (d["tiles"] > 0) == (strips == 0), d
             assert (d["level_tiles"] > 0) == (strips > 0), d
     """)
+
+
+def test_schedule_limits(standin):
+    """Which CFGs the strips take: up to 32,000 blocks and 2^24 edges, however many words."""
+    run(standin, """
+        ctx = ompd.Context(0, 64 << 20)
+        at = on_device(np.zeros(64, np.uint8))   # (never read here)
+        for blocks, edges, n_vars, strips in ((2, 1, 0, 1), (32000, 65534, 1, 1), (32000, 65535, 1, 1), (32001, 65534, 1, 0),
+                                              (100, 1 << 24, 1, 1), (100, (1 << 24) + 1, 1, 0), (500, 700, 20000, 1)):
+            g = ompd.DeviceCFG(n_blocks=blocks, n_edges=edges, n_vars=n_vars, entry=0, exit=blocks - 1, succ_ptr=at,
+                               succ_idx=at, edge_kind=at, space=at, read_bits=at, write_bits=at)
+            d = json.loads(ompd.Plan(ctx, [g], [ompd.DeviceResult(after_dev=at)]).describe())
+            assert d["strip_cfgs"] == strips, (blocks, edges, d)
+    """)
+
+
+def test_plan_without_room_for_its_strips_takes_the_walk(standin):
+    run(standin, """
+        ctx = ompd.Context(0, 64 << 20)
+        cfgs = [synth.c1(0)] * 50
+        def walks():
+            hip.standin_clear_kernels()
+            ctx.analyze_batch(cfgs)
+            return hip.standin_launches(b"ompd_k_prep") > 0
+        before = hip.standin_allocs()
+        assert not walks()
+        hip.standin_fail_alloc(1)   # the plan's scratch, after the staging of inputs and outputs
+        assert walks()
+        hip.standin_fail_alloc(-1)
+        assert not walks()
+    """)
