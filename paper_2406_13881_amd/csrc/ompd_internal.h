@@ -132,7 +132,7 @@ inline size_t ompd_transpose_items(size_t nb, size_t ne, size_t wd)
     auto chunks = [](size_t rows) { return (rows + ompd::STRIP_T_ROWS - 1) / ompd::STRIP_T_ROWS; };
     return runs * (chunks(nb) + (wd ? chunks(ne + 1) : 0));
 }
-int ompd_strip_rows(const ompd_cfg* g, int n);
+int ompd_strip_rows(const ompd_cfg* g, int n, uint32_t flags);
 // Settle the schedule of each CFG of a launch (a CFG whose schedule the caller names, or that the
 // strips cannot hold, keeps the walk or the strips; the others take the strips, or the walk when
 // a launch that fills the GPU asks for the per-tile kernel), and the shape of its strips.

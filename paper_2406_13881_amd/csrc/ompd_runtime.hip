@@ -290,8 +290,9 @@ int32_t ompd_want(const ompd_result& r)
 // variables does the least work per word, 4 rows for one word the fewest passes.  A lone CFG of 8002
 // blocks and 24 words solves in 3.1 ms with one row, 2.6 ms with four; 1024 CFGs (4266 strips of 4
 // words) in 12.1 ms with one row, 16.4 ms with two, 27.2 ms with four.
-int ompd_strip_rows(const ompd_cfg* g, int n)
+int ompd_strip_rows(const ompd_cfg* g, int n, uint32_t flags)
 {
+    if (flags & OMPD_F_SCHED_WALK) return 0;   // (no room for what the walk does not use)
     int64_t words = 0;
     for (int i = 0; i < n; ++i) words += (g[i].n_vars + 63) / 64 + 1;
     return words <= 64 ? 4 : words <= 256 ? 2 : 1;
@@ -615,7 +616,7 @@ int ompd_plan_build(ompd_ctx* ctx, const ompd_cfg* cfgs, ompd_result* res, int32
     }
     // (a plan that does not fit with the room the strips like may still fit without)
     hipError_t e = hipSuccess;
-    for (int rows : {ompd_strip_rows(cfgs, n), 0}) {
+    for (int rows : {ompd_strip_rows(cfgs, n, flags), 0}) {
         total = 0;
         for (int i = 0; i < n; ++i) {
             base[i] = total;
@@ -1436,7 +1437,7 @@ extern "C" int ompd_analyze_batch_noalloc(ompd_ctx* ctx, const ompd_cfg* cfgs, o
     Shape sh;
     int rc = OMPD_OK;
     size_t total = 0, bnd_words = 0, counter_off = 0, bnd_off = 0, cfg_off = 0, tile_off = 0, item_off = 0, info_off = 0;
-    const int rows = ompd_strip_rows(cfgs, n);
+    const int rows = ompd_strip_rows(cfgs, n, flags);
     for (uint32_t walk : {0u, OMPD_F_SCHED_WALK}) {
         total = bnd_words = 0;
         for (int i = 0; i < n; ++i) {

@@ -367,7 +367,7 @@ extern "C" int ompd_submit(ompd_ctx* ctx, const ompd_cfg* cfg, ompd_result* res,
     full.var_kind = (uint8_t*)1; full.after_dev = (uint8_t*)1; full.before_dev = (uint8_t*)1;
     full.fp_clause = (uint64_t*)1;
     r->scratch_off = off;
-    r->dev_bytes = off + ompd_cfg_scratch(g, full, r->so, 1);
+    r->dev_bytes = off + ompd_cfg_scratch(g, full, r->so, (flags & OMPD_F_SCHED_WALK) ? 0 : 1);
     r->pin_bytes = r->in_bytes;
     {
         // its share of a step's launch tables: descriptor, tiles, items, status words (a request

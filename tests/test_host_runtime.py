@@ -257,6 +257,29 @@ def test_describe_counts_the_cfgs_of_each_schedule(standin):
     """)
 
 
+def test_a_caller_that_names_the_walk_pays_for_the_walk(standin):
+    """The strips' larger scratch is not reserved for a plan, an allocation-free call or a request that
+    names the walk."""
+    run(standin, """
+        ctx = ompd.Context(0, 64 << 20)
+        cfg = synth.c3_item(5, n_user=3000, n_vars=64)
+        W = ompd.F_SCHED_WALK
+        nb, ne, words = cfg.n_blocks, len(cfg.succ_idx), 1
+        # the walk's arrays (three pairs of block rows, a tile's four flag words, 20 words of records; three
+        # edge rows and the predecessor lists) and the results not asked for (three pairs and an edge pair)
+        most = 8 * (nb * ((6 + 6) * words + 4 + 20) + ne * ((3 + 2) * words + 1)) + 65536
+        size = {f: json.loads(resident(ctx, [cfg], f).describe())["scratch_bytes"] for f in (0, W)}
+        assert size[W] < most < size[0], (size, most)
+        used = {}
+        for f in (0, W):
+            r = ompd.submit(ctx, cfg, flags=f)
+            used[f] = ompd.serving_stats(ctx)["bytes_in_use"]
+            r.wait()
+        assert used[0] - used[W] > (size[0] - size[W]) // 4, (used, size)
+        ctx.close()
+    """)
+
+
 def test_schedule_limits(standin):
     """Which CFGs the strips take: up to 32,000 blocks and 2^24 edges, however many words."""
     run(standin, """
