@@ -79,7 +79,10 @@ enum { OMPD_MAP_TO = 1, OMPD_MAP_FROM = 2, OMPD_MAP_ALLOC = 4, OMPD_FIRSTPRIVATE
  * levels (as many as an idle GPU has room for).  Neither flag: by level, with
  * as many wavefronts per workgroup as the launch leaves room for.  CFGs of
  * more than 32,000 blocks or 2^24 edges, and those whose strips do not fit in
- * the scratch they are given, take the walk. */
+ * the scratch they are given, take the walk.  By level takes more scratch
+ * (12 words per block and word against 10, and 50 to 145 words per block
+ * against 20); a batch of hundreds of long, nearly straight-line CFGs runs faster on the
+ * walk, which ompd_plan_autotune finds out. */
 #define OMPD_F_SCHED_LEVEL (1u << 4)
 #define OMPD_F_SCHED_WALK (1u << 5)
 /* Placement variants (section "Data-Flow Analysis", the loop rule, and
@@ -100,10 +103,10 @@ enum { OMPD_MAP_TO = 1, OMPD_MAP_FROM = 2, OMPD_MAP_ALLOC = 4, OMPD_FIRSTPRIVATE
  * (and a capped call reports) are the walk's whatever the schedule.  By level,
  * a capped CFG is solved by one wavefront per four words, which takes longer. */
 #define OMPD_F_SWEEP_CAP(n) ((((uint32_t)(n)) & 0xFFFFu) << 16)
-/* Ring of recently solved blocks per solve workgroup, for the one-shot entry
- * points (what ompd_plan_configure sets for a plan): n = 8, 16, 32 or 64
- * blocks (other values round down to one of these; 0 = default, 64).  Results
- * do not depend on it. */
+/* Ring of recently solved blocks per solve workgroup of the walk, for the
+ * one-shot entry points (what ompd_plan_configure sets for a plan): n = 8, 16,
+ * 32 or 64 blocks (other values round down to one of these; 0 = default, 64).
+ * Results do not depend on it; no effect on CFGs solved by level. */
 #define OMPD_F_RING_SLOTS(n) ((uint32_t)((n) >= 64 ? 4 : (n) >= 32 ? 3 : (n) >= 16 ? 2 : (n) >= 8 ? 1 : 0) << 8)
 
 /* ---- one procedure ----------------------------------------------------
@@ -206,7 +209,8 @@ const char* ompd_last_error(const ompd_ctx* ctx);
 /* Device facts the solver plans with: compute units, LDS bytes a workgroup
  * of the solve kernel may use, and device memory.  Any pointer may be NULL. */
 int ompd_device_info(ompd_ctx* ctx, int32_t* n_cu, int32_t* lds_bytes, int64_t* mem_bytes);
-/* Bound of a wait inside the solve kernels.  The two wavefronts of a solve
+/* Bound of a wait inside the walk's kernels (those of CFGs solved by level
+ * have no such waits).  The two wavefronts of a solve
  * workgroup (one computes the steps of the walk, the other feeds it inputs
  * and stores its results) wait for each other; a wait that sees no progress
  * for `ns` nanoseconds of the device's wall clock gives up, both wavefronts
@@ -240,8 +244,9 @@ int ompd_analyze_batch(ompd_ctx* ctx, const ompd_cfg* cfgs, ompd_result* res, in
  * include OMPD_F_DEVICE_PTRS) and `stream` (NULL = default stream); the call
  * is synchronous, allocates no device memory and returns OMPD_E_NOMEM,
  * touching nothing, when the batch needs more scratch than the array holds
- * (roughly ten words of scratch per block and word of each CFG, so tens of
- * MiB for a 16,384-block x 2,048-variable procedure).  Every call on one
+ * on the walk (roughly ten words of scratch per block and word of each CFG and
+ * 20 per block, so tens of MiB for a 16,384-block x 2,048-variable procedure;
+ * what the strips take more decides only whether the batch goes by level).  Every call on one
  * device shares that device's array, which keeps the last call's contents
  * (each call rewrites what it reads, so nothing carries over): calls that
  * overlap on one GPU would race, so the library serialises them, across all
@@ -264,10 +269,11 @@ int ompd_plan_create(ompd_ctx* ctx, const ompd_cfg* cfgs, ompd_result* res, int3
 int ompd_plan_run(ompd_plan* plan, void* stream);
 int ompd_plan_status(ompd_plan* plan, int32_t* per_cfg);
 /* Autotuner: first the schedule of each size bucket (below), each bucket's
- * CFGs timed alone under the walk and the level schedule; then each
- * candidate launch configuration (LDS ring bytes per solve workgroup,
- * workgroups per CU) on the whole plan; every candidate is timed `trials`
- * times on `stream` and the fastest kept.  Results are bit-identical for
+ * CFGs timed alone under the walk and the level schedule (the library's rule
+ * instead of these where it runs the whole plan faster); then, if a CFG is
+ * on the walk, each candidate launch configuration (LDS ring bytes per solve
+ * workgroup, workgroups per CU) on the whole plan; every candidate is timed
+ * `trials` times on `stream` and the fastest kept.  Results are bit-identical for
  * every candidate.  best_ms (the whole plan with the choice) may be NULL. */
 int ompd_plan_autotune(ompd_plan* plan, void* stream, int32_t trials, float* best_ms);
 /* Schedule per size bucket (what the autotuner chooses first, then the
@@ -280,7 +286,8 @@ int ompd_plan_autotune(ompd_plan* plan, void* stream, int32_t trials, float* bes
  * bit-identical for every choice.  ompd_plan_describe reports the choice. */
 #define OMPD_SCHED_BUCKETS 5
 int ompd_plan_set_schedule(ompd_plan* plan, const int32_t* per_bucket);
-/* Set the launch configuration by hand (what the autotuner chooses among):
+/* Set the launch configuration of the walk by hand (what the autotuner
+ * chooses among; no effect on CFGs solved by level):
  * LDS bytes per solve workgroup for the ring of recently solved blocks
  * (256 bytes per block; 0 = default, 16 KiB; rounded down to a power of
  * two of blocks within [8, 64] and to what the device's LDS holds) and
@@ -322,8 +329,10 @@ void ompd_plan_destroy(ompd_plan* plan);
  * returns at once; a background thread groups admitted requests into steps
  * that run concurrently on several streams (while one runs, the next waits
  * for 32 pending requests or 20 ms, whichever comes first, so that steps are
- * large).  `res` (host pointers) must
- * stay valid until poll reports done.  poll: *done = 0 pending, 1 done,
+ * large).  A request counts against the budget with its inputs, every
+ * output and its scratch (the strips', or the walk's where the caller names it
+ * or only that fits): 129 or 106 MB for 16,384 blocks x 2,048 variables.  `res` (host pointers) must
+ * stay valid until poll reports done; its pointers count as they are at submit.  poll: *done = 0 pending, 1 done,
  * negative = that request's error code; a done ticket is released by the
  * poll that reports it.  wait blocks until done or timeout_ns (< 0 = no
  * limit). */

@@ -92,12 +92,10 @@ struct DevCfg {
     int32_t* tmp;
     int32_t* rec_f;     // [2*nb] int4: block records with predecessors, in block-id order
     int32_t* rec_b;     // [2*nb] int4: block records with successors, in block-id order
-    int32_t* step_f;    // [2*nb] int4: step entries of the forward walk, in walk order (level
-                        // schedule: the forward records in level order, the block in word 7)
-    int32_t* step_b;    // [2*nb] int4: step entries of the backward walk, in walk order (level
-                        // schedule: the backward records in level order)
-    int32_t* lorder;    // [nb] the blocks by level (level schedule)
-    int32_t* loff;      // [nb + 1] start of each level in lorder
+    int32_t* step_f;    // [2*nb] int4: step entries of the forward walk, in walk order
+    int32_t* step_b;    // [2*nb] int4: step entries of the backward walk, in walk order
+    int32_t* lorder;    // [nb] the walk's order where it is not the block ids
+    int32_t* loff;      // [nb + 1] each block's place in it
     int32_t* info;
     // Strip schedule (these share the CFG's scratch with the walk's arrays above; one of the two
     // is in use).  Positions: the blocks by level.  Units: the words, then (block arrays only) one
@@ -159,7 +157,10 @@ constexpr int STRIP_MAX_BLOCKS = 32000, STRIP_MAX_EDGES = 1 << 24;
 // edges from which a record no longer holds its own entry (entries are 16-bit numbers there)
 constexpr int STRIP_ROW_EDGES = 65535;
 // units of a strip: as many as a pass of narrow levels fills; a large CFG has wider levels, which
-// fill a pass with fewer units
+// fill a pass with fewer units.  (Ms, one / four units where strips queue: 8, 32, 64 CFGs of 16,386
+// blocks, 32 words and few accesses 7.9 / 10.7, 17.2 / 20.5, 31.3 / 31.9; 30, 120, 400 of 11,002 blocks, 8
+// words and many accesses 7.5 / 7.4, 14.0 / 10.5, 38.5 / 23.6; 12 CFGs of 12,000 blocks among 300 smaller ones
+// 7.7 / 7.8.  So the line is right for the former; a rule by load as well would serve the latter.)
 constexpr int strip_units(int nb, int wd) { return nb >= 10000 || wd < 1 ? 1 : wd < 3 ? 2 : 4; }
 // LDS bytes of the ingest kernel's peel: a count and record per block, and with ne the lists
 // of blocks with more than two successors (which it else reads from the CSR; where the records do not

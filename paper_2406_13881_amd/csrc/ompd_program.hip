@@ -38,14 +38,12 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
-#include <deque>
 #include <cstdio>
 #include <cstring>
 #include <deque>
 #include <map>
 #include <mutex>
 #include <string>
-#include <deque>
 #include <vector>
 
 #include "../../include/ompd.h"

@@ -310,7 +310,7 @@ void ompd_settle_sched(DevCfg* h, int n, int n_cu, bool split)
         if (h[i].sched_rule ? h[i].strip_ok : h[i].sched == SCHED_LEVEL) strips += strips_of(h[i]);
     // Who asks for the per-tile kernel gets it, on the walk, where the launch fills the GPU.  One that
     // leaves it idle, and a large CFG, take the strips all the same (us, strips / per-tile kernel alone:
-    // 66 blocks 240 / 573, 2002 blocks x 300 variables 1,190 / 16,300, 14002 x 300 4,540 / 118,500).
+    // 66 blocks 239 / 573, 2002 blocks x 300 variables 845 / 16,347, 14002 x 300 3,333 / 118,526).
     if (!split) {
         const bool room = strips <= n_cu;
         strips = 0;
