@@ -207,3 +207,91 @@ def test_strips_that_do_not_fit_their_scratch(ctx):
             small.close()
     else:
         assert False, "no budget admitted the request"
+
+
+def _wild(seed):
+    """A random graph with nothing structured about it: edges of any kind in any direction (cycles
+    without a BACK edge, BACK edges that go forward, repeated edges, self loops), ids shuffled, random
+    boundaries, now and then marked scalars."""
+    rng = np.random.default_rng(seed)
+    n, nv = int(rng.integers(1, 160)), int(rng.choice([1, 31, 64, 65, 130, 260, 520]))
+    edges = [(int(rng.integers(0, b)), b) for b in range(1, n + 1)]
+    edges += [(b, int(rng.integers(b + 1, n + 2))) for b in range(1, n + 1)]
+    extra = int(rng.integers(0, 1 + int(n * rng.choice([0.2, 1, 4]))))
+    edges += [(int(a), int(b)) for a, b in zip(rng.integers(1, n + 1, extra), rng.integers(1, n + 1, extra))]
+    kinds = [0 if b == n + 1 else int(rng.choice([0, 2])) if a == 0 else
+             int(rng.choice([0, 0, 1, 2])) if a >= b else int(rng.choice([0, 0, 0, 0, 2, 1])) for a, b in edges]
+    cfg = synth.from_edges(_blocks(rng, n, nv), [(a, b, k) for (a, b), k in zip(edges, kinds)], nv)[0]
+    if rng.random() < 0.5:
+        cfg = synth.permute_blocks(cfg, seed)[0]
+    m = synth.var_mask(nv)
+    word = lambda: rng.integers(0, 1 << 63, size=cfg.wd, dtype=np.uint64) & m
+    if rng.random() < 0.5:
+        cfg.entry_valid_d = word()
+        cfg.entry_valid_h = (~cfg.entry_valid_d | word()) & m
+        cfg.exit_live_h, cfg.exit_live_d = word(), word()
+    if rng.random() < 0.4:
+        synth.mark_scalars(cfg, seed)
+    return cfg
+
+
+@pytest.mark.parametrize("variant", ["DEFAULT", "EAGER", "LAZY", "REFINE"])
+def test_strip_wild_graphs(ctx, variant):
+    import paper_2406_13881_amd as ompd
+    flag = 0 if variant == "DEFAULT" else getattr(ompd, "F_PLACEMENT_" + variant)
+    cfgs = [_wild(1000 + s) for s in range(150)]
+    want = [oracle.solve(c, placement=0 if variant == "DEFAULT" else getattr(oracle, "PLACEMENT_" + variant)) for c in cfgs]
+    for copies, flags in ((1, flag), (4, flag), (1, flag | (3000 << 16))):   # room for every strip, queueing, one run each
+        print("wild graphs: %s, %d copies, flags %x" % (variant, copies, flags), flush=True)
+        got = ctx.analyze_batch(cfgs * copies, flags=flags)
+        for i in range(len(cfgs) * copies):
+            for k in KEYS + ("fp_clause",):
+                g = np.asarray(got[i][k])
+                assert np.array_equal(g, np.asarray(want[i % len(cfgs)][k]).reshape(g.shape)), (i % len(cfgs), copies, flags, k)
+
+
+def test_strip_malformed(ctx):
+    """What the walk refuses the strips refuse, and the CFGs beside it are solved."""
+    import copy
+    import paper_2406_13881_amd as ompd
+    good = _chain(40, 70, 1)
+    n = good.n_blocks
+
+    def change(field, at, value):
+        c = copy.deepcopy(good)
+        getattr(c, field)[at] = value
+        return c
+
+    def edges(extra, blocks=None):
+        rng = np.random.default_rng(3)
+        base = [(b, b + 1, 0) for b in range(n - 1)]
+        return synth.from_edges(_blocks(rng, n - 2, 70), base + extra if blocks is None else blocks, 70)[0]
+
+    cut = [(b, b + 1, 0) for b in range(n - 1) if b != 20]
+    bad = {"row start": change("succ_ptr", 0, 1), "row end": change("succ_ptr", n, 3), "rows out of order": change("succ_ptr", 7, 30),
+           "successor": change("succ_idx", 5, n), "negative successor": change("succ_idx", 5, -1),
+           "edge into ENTRY": change("succ_idx", 5, good.entry), "kind": change("edge_kind", 5, 3), "space": change("space", 5, 2),
+           "ENTRY on the device": change("space", good.entry, 1), "padding": change("R", (5, 1), np.uint64(1) << np.uint64(63)),
+           "ENTRY reads": change("R", (good.entry, 0), np.uint64(1)), "BACK out of ENTRY": change("edge_kind", 0, 1),
+           "BACK into EXIT": change("edge_kind", list(good.succ_idx).index(good.exit), 1), "edge out of EXIT": edges([(n - 1, 5, 0)]),
+           "no way in": edges(None, cut + [(20, 22, 0)]), "no way out": edges(None, cut + [(19, 21, 0)]),
+           "cycle without a way in": edges(None, [e for e in cut if e[0] not in (19, 21)] + [(19, 22, 0), (20, 21, 0), (21, 20, 0), (21, 22, 0)]),
+           "cycle without a way out": edges(None, [e for e in cut if e[0] not in (19, 21)] + [(19, 20, 0), (19, 22, 0), (20, 21, 0), (21, 20, 1)])}
+    gap = copy.deepcopy(good)
+    gap.entry_valid_h, gap.entry_valid_d = np.zeros(2, np.uint64), np.zeros(2, np.uint64)
+    bad["variables valid nowhere"] = gap
+    from paper_2406_13881_amd.resident import ResidentBatch
+    want = oracle.solve(good)
+    for copies in (1, 400):   # room for every strip, and not
+        rb = ResidentBatch(ctx, [good] + list(bad.values()) + [good] * copies)
+        rb.run()
+        status = rb.plan.status()
+        for i, name in enumerate(bad):
+            assert status[1 + i] == ompd.OMPD_E_INVAL, (name, status[1 + i])
+        for i in (0, 1 + len(bad), len(bad) + copies):
+            assert status[i] == 0
+            got = rb.fetch(i)
+            for k in KEYS:
+                g = np.asarray(got[k])
+                assert np.array_equal(g, np.asarray(want[k]).reshape(g.shape)), (i, k)
+        rb.close()
